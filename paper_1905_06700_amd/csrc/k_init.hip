@@ -12,87 +12,138 @@
 // only.  Intensity = own photons in the claimed bins minus background over
 // the IRF mass there; background = own photons outside the claimed bins.
 //
-// Mapping: one wavefront per pixel, four pixels per workgroup.  The window's
-// rows are contiguous ranges of the photon lists (pixel-major CSR), so the
-// pooled photons are (2 r_init + 1) ranges.  The argmax over tau is an exact
-// branch and bound over blocks of 64 consecutive tau (one tau per lane): an
-// upper bound of every block's best score, sum over pooled photons of z *
-// max q over the lags the block can see, is scattered into LDS with integer
-// atomics; blocks are then scored exactly in decreasing bound order until no
-// remaining bound can beat (or tie at a smaller tau) the best score found.
-// The bound only counts photons, so it stays valid after photons are claimed.
-// Only a few blocks per pixel are ever scored exactly, so the cost follows the
-// active bins, not T.
+// Mapping: one wavefront per pixel (several consecutive pixels in turn).  The
+// window's rows are contiguous ranges of the photon lists (pixel-major CSR);
+// their photons are added into a dense histogram of bytes in LDS, so the
+// score of every tau is a contraction of that histogram with the weights: a
+// Toeplitz product on the integer matrix cores.  With q = 2^k qc - e, qc =
+// ceil(q / 2^k) <= 127 and 0 <= e < 2^k,
+//   2^k sum z qc            bounds the score of every tau from above, and
+//   2^k sum z qc - sum z e  is the score, exactly.
+// One pass of the first product over all tau (v_mfma_i32_16x16x64_i8: 16 tau
+// of 16 blocks against 64 bins per instruction) leaves the largest bound of
+// every block of 16 tau in LDS; the search then takes the block with the
+// largest bound, computes the exact scores of the 16 blocks around it (the
+// second product, e in two digits), and stops once no remaining bound reaches
+// the best score.  The gap between bound and score is about half of 2^k per
+// photon in the IRF's support (1% of a peak's score): 1.15 such tiles are
+// scored per peak sought on head-shaped scenes.  An accepted peak's bins drop to zero and
+// the blocks that see them are bounded again (one tile).
 //
-// When the pooled photons fit (INIT_ELDS entries, T <= INIT_SB x INIT_NB_LDS)
-// and the weights are staged in LDS, the photons are read once into registers
-// and staged in LDS bucketed by 64-bin block; the bounds are kept per
-// sub-block of INIT_SB tau (tighter, so fewer 64-tau blocks are scored) from a
-// sliding-maximum weight table; each lane keeps the bound and cached best of
-// the blocks lane and lane + 64; after an accepted peak only the blocks that
-// peak changes (tau that can see its claimed bins or fall under its
-// suppression) are scored again.  This path also needs the pixel's photon
-// total times the largest weight to fit 32 bits: every score and bound then
-// does, and the search runs on 32-bit integers (24-bit multiply-adds, exact
-// here).  Pixels outside these limits read their photons from HBM and score
-// every round afresh with 64-bit sums.
+// Bound by vector instruction issue (1,138 VALU instructions a pixel, 0.76 of
+// the slots; 90 of them on the matrix cores, 57 for the bounds of 4613 bins and
+// a 137-bin IRF).  32 head-shaped frames (636 k pixels, pools of 490 entries):
+// 1.69 ms, where photon-by-photon bounds in LDS and scores on the vector ALU
+// took 4.20 ms; 65 k pixels of 2000 bins with pools of 880 entries: 0.18
+// against 1.29 ms.  Five workgroups per CU (96 VGPRs): four 1.89, six (spills)
+// 1.77 ms.
+//
+// Pixels with more than 127 pooled photons in one bin are left to a second
+// kernel, which holds the counts as two 7-bit digits in two planes of bytes
+// and adds both planes' products.  Where the tables do not apply (IRFs over
+// INIT_L_MAX bins, histograms over INIT_T_MAX bins, more than 16383 photons in
+// one bin, scores past 32 bits) an exact branch and bound over blocks of 64
+// tau reads the photons from memory.
 #include "rt3d_dev.h"
+#include "rt3d_init.h"
 
 namespace rt3d {
 
-// Accepted peaks of one pixel, held in registers (every index below is a
-// compile-time constant after unrolling, so nothing spills to scratch).
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// Accepted peaks of one pixel, held in scalar registers (every index below is
+// a compile-time constant after unrolling, so nothing spills to scratch).
+// Slots at or past n hold a tau no bin is near.
+constexpr int NO_PEAK = -(1 << 28);
+
 struct Peaks {
-    int t[KM], a[KM], c[KM], w[KM];
+    int t[KM], w[KM];       // tau; unclaimed bins of its window when it was accepted
     int n;
 
-    // first accepted peak whose window [a, c] holds bin tb, or -1
-    __device__ __forceinline__ int owner(int tb) const
+    __device__ __forceinline__ void clear()
+    {
+        n = 0;
+#pragma unroll
+        for (int k = 0; k < KM; ++k) {
+            t[k] = NO_PEAK;
+            w[k] = 0;
+        }
+    }
+
+    // whether the window [t - wl, t + wr] of peak j holds bin tb (0 <= tb < T)
+    __device__ __forceinline__ bool holds(const DevModel& m, int j, int tb) const
+    {
+        return (unsigned)(tb - (t[j] - m.wl)) <= (unsigned)(m.wl + m.wr);
+    }
+
+    // first accepted peak whose window holds bin tb, or -1
+    __device__ __forceinline__ int owner(const DevModel& m, int tb) const
     {
         int ow = -1;
 #pragma unroll
         for (int j = KM - 1; j >= 0; --j)
-            if (j < n && tb >= a[j] && tb <= c[j]) ow = j;
+            if (j < n) ow = holds(m, j, tb) ? j : ow;
         return ow;
     }
 
-    __device__ __forceinline__ bool suppressed(int tau, int wnms) const
-    {
-        bool sup = false;
-#pragma unroll
-        for (int j = 0; j < KM; ++j)
-            if (j < n && abs(tau - t[j]) <= wnms) sup = true;
-        return sup;
-    }
-
-    // any accepted peak's suppression reaching tau in [lo, hi] (wave-uniform)
-    __device__ __forceinline__ bool suppresses_any(int lo, int hi, int wnms) const
+    __device__ __forceinline__ bool claimed(const DevModel& m, int tb) const
     {
         bool any = false;
 #pragma unroll
         for (int j = 0; j < KM; ++j)
-            if (j < n && t[j] - wnms <= hi && t[j] + wnms >= lo) any = true;
+            if (j < n) any = any || holds(m, j, tb);
+        return any;
+    }
+
+    __device__ __forceinline__ bool suppressed(int tau, int wnms) const
+    {
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < KM; ++j)
+            if (j < n) any = any || (unsigned)(tau - t[j] + wnms) <= (unsigned)(2 * wnms);
         return any;
     }
 
     // (wave-uniform values: kept in scalar registers)
-    __device__ __forceinline__ void push(int tt, int aa, int cc, int ww)
+    __device__ __forceinline__ void push(int tt, int ww)
     {
         tt = __builtin_amdgcn_readfirstlane(tt);
-        aa = __builtin_amdgcn_readfirstlane(aa);
-        cc = __builtin_amdgcn_readfirstlane(cc);
         ww = __builtin_amdgcn_readfirstlane(ww);
 #pragma unroll
         for (int j = 0; j < KM; ++j)
             if (j == n) {
                 t[j] = tt;
-                a[j] = aa;
-                c[j] = cc;
                 w[j] = ww;
             }
         ++n;
     }
 };
+
+// A kernel's arguments, read through a pointer the compiler cannot see
+// through: what a stage of the kernel needs is loaded (scalar, from the
+// constant cache) where it is needed.  Loaded once for the whole kernel, the
+// arguments would not fit the scalar registers beside the search's state and
+// wait in vector lanes, an instruction per use.
+struct InitArgs {
+    DevModel m;
+    DevParams p;
+    Shape sh;
+    const uint32_t* off;
+    const uint32_t* ent;
+    const float* gain;
+    DevState s;
+    int ppw;            // pixels per wavefront
+    int area;           // LDS bytes of one wavefront
+    int all;            // k_init_rest: every live pixel of the launch
+    int wide;           // k_init_rest: two planes of bytes fit the wavefront's LDS
+};
+
+__device__ __forceinline__ const InitArgs& init_args()
+{
+    auto k = (const __attribute__((address_space(4))) InitArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return *(const InitArgs*)k;
+}
 
 // Orders LDS traffic between the lanes of one wavefront.
 __device__ __forceinline__ void wave_sync()
@@ -114,665 +165,554 @@ __device__ __forceinline__ int q_range_max(const int* qst, int L, int lo, int hi
 
 __device__ __forceinline__ int popc_ballot(bool x) { return __popcll(__ballot(x)); }
 
-constexpr int INIT_WAVES = 4;
-constexpr int INIT_ELDS = 608;    // pooled entries a wavefront scores from LDS (held in registers)
-constexpr int INIT_EPL = (INIT_ELDS + 63) / 64;   // pooled entries per lane
-// Pixels whose pool is larger, up to INIT_WIDE_ELDS entries, are listed and
-// scored from LDS by a second kernel that stages their photons in passes over
-// HBM; larger pools take the HBM path.
-constexpr int INIT_WIDE_ELDS = 1536;
-constexpr unsigned INIT_WIDE_GRID = 2048;
-
-// The list of those pixels: INIT_LIST_SEGS counters INIT_LIST_STRIDE words
-// apart (separate cache lines, so that appends from many wavefronts do not
-// queue on one address), then one segment of init_list_cap(P) pixels per
-// counter; workgroup b of the main kernel appends to segment b mod
-// INIT_LIST_SEGS, which holds at most init_list_cap(P) of its pixels.
-constexpr int INIT_LIST_SEGS = 64;      // one per lane of the wide kernel's segment scan
-constexpr int INIT_LIST_STRIDE = 64;
-constexpr size_t INIT_LIST_HDR = (size_t)INIT_LIST_SEGS * INIT_LIST_STRIDE;
-
-__host__ __device__ inline size_t init_list_cap(long long P)
+__device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c)
 {
-    const long long nblk = (P + INIT_WAVES - 1) / INIT_WAVES;
-    return (size_t)((nblk + INIT_LIST_SEGS - 1) / INIT_LIST_SEGS) * INIT_WAVES;
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
 }
-constexpr int INIT_QLDS = 4096;   // IRF weight tables (ints) up to this size are staged in LDS
-constexpr int INIT_QPAD = 96;     // zero weights on either side of the staged IRF weights (at least 94)
-constexpr int INIT_BWS = 5;       // the LDS path buckets photons by 2^INIT_BWS bins
+
+// Maximum over the four rows of 16 lanes, column by column (every lane ends
+// with its column's): the halves swapped, then the rows of each half.
+__device__ __forceinline__ uint32_t rows_max(uint32_t v)
+{
+    auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = max(h[0], h[1]);
+    auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return max(r[0], r[1]);
+}
+
+// The same for four values at once: row g of the lanes ends with the column
+// maxima of v[g].
+__device__ __forceinline__ uint32_t rows_max4(const uint32_t (&v)[4])
+{
+    auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+    auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+    auto r = __builtin_amdgcn_permlane16_swap(max(a[0], a[1]), max(b[0], b[1]), false, false);
+    return max(r[0], r[1]);
+}
+
+__device__ __forceinline__ uint32_t max4(v4i d)
+{
+    return (uint32_t)max(max(d[0], d[1]), max(d[2], d[3]));
+}
+
+// Whole-wavefront sum, maximum and minimum: four moves inside the rows of 16
+// lanes that have a source for every lane (quad permutations, half-row and
+// row mirrors: one instruction each with the operation), then the rows and
+// halves swapped.  Every lane must be active; the result is wave-uniform.
+struct OpAdd { static __device__ __forceinline__ uint32_t f(uint32_t a, uint32_t b) { return a + b; } };
+struct OpMax { static __device__ __forceinline__ uint32_t f(uint32_t a, uint32_t b) { return a > b ? a : b; } };
+struct OpMin { static __device__ __forceinline__ uint32_t f(uint32_t a, uint32_t b) { return a < b ? a : b; } };
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_move(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+
+template <class OP>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v)
+{
+    v = OP::f(v, row_move<0xB1>(v));
+    v = OP::f(v, row_move<0x4E>(v));
+    v = OP::f(v, row_move<0x141>(v));
+    v = OP::f(v, row_move<0x140>(v));
+    auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = OP::f(r[0], r[1]);
+    auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)OP::f(h[0], h[1]));
+}
+
 constexpr int NO_TAU = 0x7fffffff;
 
-// Width (tau) of the sub-blocks the LDS path bounds, and the number of
-// sub-blocks up to which it keeps their tables (at most two 64-tau blocks per
-// lane).  Narrow sub-blocks give tight bounds (the largest weight over 8
-// lags rather than 16 roughly halves the blocks scored on head-shaped
-// scenes) at the price of more bound terms per photon.
-constexpr int INIT_SB = 8;
-constexpr int INIT_SB2 = 2 * INIT_SB;   // the bins of one pair of sub-blocks
-constexpr int INIT_NB_LDS = 1024;
-static_assert(INIT_NB_LDS * INIT_SB <= 128 * 64, "two blocks per lane");
-static_assert((INIT_SB & (INIT_SB - 1)) == 0 && 64 % INIT_SB == 0, "sub-blocks tile a block");
+// Scores: 32 bits where the caller has checked that they fit, else 64.
+template <bool WIDE> struct ScoreOf { typedef uint32_t T; };
+template <> struct ScoreOf<true> { typedef unsigned long long T; };
 
-// The LDS path adds a photon to the bounds of the sub-blocks in pairs (one
-// 64-bit LDS atomic per two sub-blocks): for a photon at bin t, with
-// t + o = 2 SB h + r (0 <= r < 2 SB, SB = INIT_SB), the pairs cover
-// sub-blocks 2h - 2 np + 2 .. 2h + 1, which hold every sub-block whose tau
-// can see t.  The pair count np = ceil((ceil((L - 1) / SB) + 2) / 2); the
-// bounds carry 2 np - 2 guard entries in front (indices below 0) and reach
-// index 2 floor((T - 1 + o) / (2 SB)) + 1 at the back.
-inline __host__ __device__ int init_np(int L) { return ((((L - 1) + INIT_SB - 1) / INIT_SB) + 3) >> 1; }
-inline __host__ __device__ size_t init_bound_words(int T, int L, int o)
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return wave_reduce<OpMax>(v); }
+__device__ __forceinline__ unsigned long long wave_max(unsigned long long v)
 {
-    return (size_t)init_np(L) + (size_t)(T - 1 + o) / INIT_SB2;
+    const uint32_t hi = (uint32_t)(v >> 32), mh = wave_reduce<OpMax>(hi);
+    return ((unsigned long long)mh << 32) | wave_reduce<OpMax>(hi == mh ? (uint32_t)v : 0u);
 }
 
-// 8-byte LDS words of one wavefront: either the LDS path's sub-block bounds
-// (with their guards), bucketed photons and bucket ends, or the HBM path's
-// per-pixel photon ranges and block bounds.  (The areas are sized so that
-// seven four-wavefront workgroups of the head-shaped scenes' init, 4613 bins
-// and a 137-bin IRF, fit one compute unit's LDS.)
-inline __host__ __device__ size_t init_wave_words(int T, int L, int o, int r_init, size_t elds = INIT_ELDS)
-{
-    const size_t nb = (size_t)(T + 63) / 64, nbs = (size_t)(T + INIT_SB - 1) / INIT_SB;
-    const size_t side = 2 * (size_t)r_init + 1;
-    const size_t nk = ((size_t)T + (1u << INIT_BWS) - 1) >> INIT_BWS;
-    const size_t staged = nbs <= INIT_NB_LDS ? init_bound_words(T, L, o) + (elds + 1) / 2 + (nk + 3) / 4 : 0;
-    const size_t hbm = side * side + nb;
-    return hbm > staged ? hbm : staged;
-}
+// One wavefront's dense pool and the matrix products over it.  KS: steps of
+// 64 bins that hold a block's lags (L + 15 of them), or 0: m.ks of them, with
+// the weights read from global memory.
+//
+// Pooled bin t is byte t + o of Z, so that block a (tau 16 a .. 16 a + 15)
+// sees bytes 16 a .. 16 a + L + 14: row i of the weights' matrix holds
+// q[kk - i] at kk, and lane (column j, group g) reads the 16-byte chunk
+// a_j + g + 4 step.  Over all blocks, tile n takes blocks n + NS j (NS odd: 8
+// neighbouring lanes then read 8 distinct bank groups), so that the chunks of
+// tile n + 4 at one step are those of tile n at the next: each chunk is read
+// once, into a rolling window of KS x 4 registers.  WIDE: a second plane
+// of bytes, `plane` chunks on, holds the counts' multiples of 128 (KS = 0).
+template <int KS, bool WIDE>
+struct InitPool {
+    static_assert(!WIDE || KS == 0, "two planes are built with the weights in global memory");
+    typedef typename ScoreOf<WIDE>::T Score;
+    int plane;
+    v4i* Z;                 // the pool's bytes
+    uint32_t* B;            // [16 NS] one plus the largest bound of each block, in units of 2^k
+    const v4i* e;           // the digits of e: [2][KS][64] in LDS (KS > 0)
+    const v4i* qa;          // the tables in global memory: [3][ks][64]
+    int ks, NS, lane, j, g;
+    v4i A[KS ? KS : 1];     // qc
 
-// Ints of the staged weights (with their zero padding), and of the sliding
-// maximum table: Mz[SB + x] = M[x] = max q[x - SB + 1 .. x] (q = 0 outside
-// [0, L)), with SB zeros in front and zeros past x = L + SB - 2 up to the
-// last entry a photon's pairs read.
-inline __host__ __device__ size_t q_staged_ints(int L) { return (size_t)L + 2 * INIT_QPAD; }
-inline __host__ __device__ size_t q_window_ints(int L) { return INIT_SB2 * (size_t)init_np(L) + INIT_SB; }
+    __device__ __forceinline__ uint8_t* bytes() const { return reinterpret_cast<uint8_t*>(Z); }
 
-// Largest sub-block bound of block b.
-__device__ __forceinline__ uint32_t block_bound(const uint32_t* bnd, int nbs, int b)
-{
-    uint32_t mx = 0;
-#pragma unroll
-    for (int c = 0; c < 64 / INIT_SB; ++c) {
-        const int sb = b * (64 / INIT_SB) + c;
-        if (sb < nbs) mx = max(mx, bnd[sb]);
-    }
-    return mx;
-}
-
-// Adds to the sub-block bounds (or, with SUB, takes away) the terms of a
-// photon of count z at bin t, x = t + o: sub-block sb gains z x M[x - SB sb].
-// Pair j of the photon's pairs (counted from the back) holds sub-blocks
-// 2h - 2j and 2h - 2j + 1 (x = 2 SB h + r) and gains z x M[r + 2 SB j] and
-// z x M[r + 2 SB j - SB] in its low and high words; every other sub-block of
-// the pairs gets a zero weight (its lag lies outside M).  bnd2: the bounds as
-// 64-bit words from the first guard entry.  A bound is an exact sum below
-// 2^32, and a photon's term is part of it while it is taken away, so the low
-// word never carries into (or borrows from) the high one.
-template <bool SUB>
-__device__ __forceinline__ void bound_photon(unsigned long long* bnd2, const int* Mz, int np, int x, uint32_t z)
-{
-    const int h = x / INIT_SB2, r = x % INIT_SB2;           // x >= 0
-    const int* Mb = Mz + r;
-    unsigned long long* bp = bnd2 + h + np - 1;
-    auto term = [z](int hiw, int low) {
-        const unsigned long long v = ((unsigned long long)(uint32_t)__umul24(z, (uint32_t)hiw) << 32) |
-                                     (uint32_t)__umul24(z, (uint32_t)low);
-        return SUB ? 0ull - v : v;
-    };
-    // four pairs at a time: their weight reads in flight together
-    int j = 0;
-    for (; j + 4 <= np; j += 4, Mb += 4 * INIT_SB2, bp -= 4) {
-        int w0[4], w1[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            w0[k] = Mb[k * INIT_SB2];
-            w1[k] = Mb[k * INIT_SB2 + INIT_SB];
-        }
-        unsigned long long* b3 = bp - 3;          // (ascending offsets from the lowest word)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) atomicAdd(b3 + (3 - k), term(w0[k], w1[k]));
-    }
-    for (; j < np; ++j, Mb += INIT_SB2, --bp) atomicAdd(bp, term(Mb[0], Mb[INIT_SB]));
-}
-
-// Whole-wavefront maximum / minimum on the VALU: DPP quad permutations, row
-// shifts by 4 and 8, then row broadcasts of lanes 15 and 31; lane 63 ends with
-// the result, which every lane reads.  Lanes without a DPP source contribute
-// the identity (0 for the maximum of unsigned keys, all ones for the minimum).
-// Every lane must be active.
-template <int CTRL>
-__device__ __forceinline__ unsigned dpp_u32(unsigned v, unsigned identity)
-{
-    return (unsigned)__builtin_amdgcn_update_dpp((int)identity, (int)v, CTRL, 0xF, 0xF, false);
-}
-
-template <int CTRL>
-__device__ __forceinline__ unsigned long long max_step_u64(unsigned long long v)
-{
-    const unsigned long long o = ((unsigned long long)dpp_u32<CTRL>((unsigned)(v >> 32), 0u) << 32) |
-                                 dpp_u32<CTRL>((unsigned)v, 0u);
-    return o > v ? o : v;
-}
-
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
-{
-    v = max_step_u64<0xB1>(v);
-    v = max_step_u64<0x4E>(v);
-    v = max_step_u64<0x114>(v);
-    v = max_step_u64<0x118>(v);
-    v = max_step_u64<0x142>(v);
-    v = max_step_u64<0x143>(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
-template <int CTRL>
-__device__ __forceinline__ unsigned max_step_u32(unsigned v)
-{
-    const unsigned o = dpp_u32<CTRL>(v, 0u);
-    return o > v ? o : v;
-}
-
-__device__ __forceinline__ unsigned wave_max_u32(unsigned v)
-{
-    v = max_step_u32<0xB1>(v);
-    v = max_step_u32<0x4E>(v);
-    v = max_step_u32<0x114>(v);
-    v = max_step_u32<0x118>(v);
-    v = max_step_u32<0x142>(v);
-    v = max_step_u32<0x143>(v);
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-template <int CTRL>
-__device__ __forceinline__ unsigned min_step_u32(unsigned v)
-{
-    const unsigned o = dpp_u32<CTRL>(v, 0xffffffffu);
-    return o < v ? o : v;
-}
-
-__device__ __forceinline__ unsigned wave_min_u32(unsigned v)
-{
-    v = min_step_u32<0xB1>(v);
-    v = min_step_u32<0x4E>(v);
-    v = min_step_u32<0x114>(v);
-    v = min_step_u32<0x118>(v);
-    v = min_step_u32<0x142>(v);
-    v = min_step_u32<0x143>(v);
-    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// acc + z q on the VALU as one 24-bit multiply-add, z from a scalar register
-// (exact for z, q < 2^24 and a result below 2^32).
-__device__ __forceinline__ uint32_t mad_u24(uint32_t z, uint32_t q, uint32_t acc)
-{
-    asm("v_mad_u32_u24 %0, %1, %2, %0" : "+v"(acc) : "s"(z), "v"(q));
-    return acc;
-}
-
-// Bucket cursors (then ends), two 16-bit values per 32-bit LDS word: a bucket
-// holds at most INIT_WIDE_ELDS photons, so no half carries into the other.
-struct Bend16 {
-    uint32_t* w;
-    __device__ __forceinline__ int get(int b) const { return (int)((w[b >> 1] >> ((b & 1) << 4)) & 0xffffu); }
-    __device__ __forceinline__ void add1(int b) const { atomicAdd(&w[b >> 1], 1u << ((b & 1) << 4)); }
-    __device__ __forceinline__ int fetch_inc(int b) const
+    // photons in byte x, and clearing it
+    __device__ __forceinline__ uint32_t count(int x) const
     {
-        return (int)((atomicAdd(&w[b >> 1], 1u << ((b & 1) << 4)) >> ((b & 1) << 4)) & 0xffffu);
+        return bytes()[x] + (WIDE ? 128u * bytes()[16 * plane + x] : 0u);
+    }
+    __device__ __forceinline__ void clear(int x) const
+    {
+        bytes()[x] = 0;
+        if (WIDE) bytes()[16 * plane + x] = 0;
+    }
+
+    // d += A-operand a times chunk c (both planes)
+    struct Acc {
+        v4i lo, hi;
+        __device__ __forceinline__ Acc() : lo{0, 0, 0, 0}, hi{0, 0, 0, 0} {}
+        __device__ __forceinline__ v4i sum() const { return WIDE ? lo + (hi << 7) : lo; }
+    };
+    __device__ __forceinline__ void add(Acc& d, v4i a, int c) const
+    {
+        d.lo = mfma_i8(a, Z[c], d.lo);
+        if (WIDE) d.hi = mfma_i8(a, Z[plane + c], d.hi);
+    }
+
+    // bounds of every block
+    __device__ __forceinline__ void bound_all() const
+    {
+        const int NG = (NS + 3) >> 2, lb = NS * j + g;
+        if constexpr (KS > 0) {
+            v4i w[KS][4];
+#pragma unroll
+            for (int k = 0; k + 1 < KS; ++k)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[k][c] = Z[lb + 4 * k + c];
+            for (int b0 = 0; b0 < NG; b0 += KS) {
+#pragma unroll
+                for (int r = 0; r < KS; ++r) {
+                    const int b = b0 + r;
+                    if (b >= NG) break;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) w[(r + KS - 1) % KS][c] = Z[lb + 4 * (b + KS - 1) + c];
+                    uint32_t v[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        v4i d = {0, 0, 0, 0};
+#pragma unroll
+                        for (int k = 0; k < KS; ++k) d = mfma_i8(A[k], w[(r + k) % KS][c], d);
+                        v[c] = max4(d);
+                    }
+                    store4(b, v);
+                }
+            }
+        } else {
+            for (int b = 0; b < NG; ++b) {
+                Acc d[4];
+                for (int k = 0; k < ks; ++k) {
+                    const v4i a = qa[k * 64 + lane];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) add(d[c], a, lb + 4 * (b + k) + c);
+                }
+                const uint32_t v[4] = {max4(d[0].sum()), max4(d[1].sum()), max4(d[2].sum()), max4(d[3].sum())};
+                store4(b, v);
+            }
+        }
+    }
+
+    __device__ __forceinline__ void store4(int b, const uint32_t (&v)[4]) const
+    {
+        const uint32_t u = rows_max4(v);
+        const int n = 4 * b + g;
+        if (n < NS) B[n + NS * j] = u + 1u;
+    }
+
+    // bounds of the blocks a0 .. a0 + 15 again
+    __device__ __forceinline__ void bound_tile(int a0) const
+    {
+        Acc d;
+        const int at = a0 + j + g;
+        if constexpr (KS > 0) {
+#pragma unroll
+            for (int k = 0; k < KS; ++k) add(d, A[k], at + 4 * k);
+        } else {
+            for (int k = 0; k < ks; ++k) add(d, qa[k * 64 + lane], at + 4 * k);
+        }
+        const uint32_t u = rows_max(max4(d.sum()));
+        if (g == 0) B[a0 + j] = u + 1u;
+    }
+
+    // exact scores of tau 16 (a0 + j) + 4 g + r, r = 0..3 (one plane: modulo
+    // 2^32, the caller has checked that they fit)
+    __device__ __forceinline__ void score_tile(int a0, int qshift, Score (&sc)[4]) const
+    {
+        Acc ac, a1, a2;
+        const int at = a0 + j + g;
+        if constexpr (KS > 0) {
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                add(ac, A[k], at + 4 * k);
+                add(a1, e[k * 64 + lane], at + 4 * k);
+                add(a2, e[(KS + k) * 64 + lane], at + 4 * k);
+            }
+        } else {
+            for (int k = 0; k < ks; ++k) {
+                add(ac, qa[k * 64 + lane], at + 4 * k);
+                add(a1, qa[(ks + k) * 64 + lane], at + 4 * k);
+                add(a2, qa[(2 * ks + k) * 64 + lane], at + 4 * k);
+            }
+        }
+        const v4i dc = ac.sum(), d1 = a1.sum(), d0 = a2.sum();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            sc[r] = ((Score)(uint32_t)dc[r] << qshift) - ((Score)(uint32_t)d1[r] << INIT_E_BITS) - (Score)(uint32_t)d0[r];
     }
 };
 
-// Exact scores of block bb's 64 tau (one per lane): L(tau) = sum of
-// z q[t - tau + o] over the pooled photons in the window [wlo, whi] the block
-// can see (photons in claimed bins have had their count set to zero).  The
-// photons are bucketed by 2^INIT_BWS bins in LDS (bucket b ends at bend.get(b),
-// nk buckets); the window's buckets are read 64 photons at a time and each
-// photon is broadcast from the lane that loaded it, four at a time so that
-// their weight lookups overlap.  qs holds the weights with INIT_QPAD zeros on
-// either side; the window's buckets hold bins within 2^INIT_BWS - 1 of it
-// (photons with bins >= T were staged as zero counts at the last bucket's
-// last bin), so every lag lies in [-63 - 31, L + 62 + 31] and indexes the
-// padded table without a clamp.
-__device__ __forceinline__ uint32_t score_block(const uint32_t* E, const Bend16 bend, int nk, int bb, const int* qs,
-                                                int L, int o)
-{
-    const int lane = threadIdx.x & 63;
-    const int lo = INIT_QPAD + o - ((bb << 6) + lane);    // qs index of bin 0 for this lane's tau
-    const int wlo = (bb << 6) - o, whi = (bb << 6) + 63 - o + L - 1;
-    uint32_t sc = 0;
-    if (whi < 0) return sc;
-    const int b0 = max(0, wlo) >> INIT_BWS, b1 = min(nk - 1, whi >> INIT_BWS);
-    const int x0 = __builtin_amdgcn_readfirstlane(b0 > 0 ? bend.get(b0 - 1) : 0);
-    const int x1 = __builtin_amdgcn_readfirstlane(bend.get(b1));
-    for (int c0 = x0; c0 < x1; c0 += 64) {
-        const int x = c0 + lane;
-        const int vv = x < x1 ? (int)E[x] : 0;
-        const int cnt = min(64, x1 - c0);
-        int k = 0;
-        for (; k + 4 <= cnt; k += 4) {
-            uint32_t v[4];
-            int q[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                v[u] = (uint32_t)__builtin_amdgcn_readlane(vv, k + u);
-                q[u] = qs[lo + ent_bin(v[u])];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) sc = mad_u24((uint32_t)ent_cnt(v[u]), (uint32_t)q[u], sc);
-        }
-        for (; k < cnt; ++k) {
-            const uint32_t v = (uint32_t)__builtin_amdgcn_readlane(vv, k);
-            sc = mad_u24((uint32_t)ent_cnt(v), (uint32_t)qs[lo + ent_bin(v)], sc);
-        }
-    }
-    return sc;
-}
+// The window's photons: row r's entries are [rs, re) of lane r.
+struct PoolRows {
+    uint32_t rs, re;
+    int side;
+    const uint32_t* ent;
+};
 
-// Branch-and-bound search of the LDS path for the pooled photons pe (entries
-// lane + 64 u < total; bucket cursors in bend hold each bucket's start), or,
-// with STAGED, for photons the caller has already bucketed into E (bend then
-// holds the bucket ends) and added to the bounds bnd.  The
-// caller has checked that ntot x the largest weight fits 32 bits and the
-// weights 24 bits: every bound and score is then an exact 32-bit sum of exact
-// 24-bit products.  On return pk holds the accepted peaks.
-template <bool STAGED>
-__device__ __forceinline__ void lds_search(const DevModel& m, const DevParams& p, int T, int L, int o, int nb,
-                                           int nbs, int nk, const uint32_t (&pe)[INIT_EPL], int total, long long ntot,
-                                           const int* qs, const int* Mz, unsigned long long* bnd2, int np,
-                                           uint32_t* bnd, uint32_t* E, const Bend16 bend, Peaks& pk)
+// Adds the pooled photons into the dense pool (cleared here); nt gains this
+// lane's photons.  Returns whether a byte passed 127: the byte that first does
+// so still holds at most 255 (counts go in as at most 128), and the lane that
+// adds to it sees that in the value it replaced, so no overflow goes unseen.
+// Three rows of four chunks of 64 entries are in flight at a time.
+template <int KS>
+__device__ __forceinline__ bool fill_pool(const InitPool<KS, false>& P, const PoolRows& W, int T, int o, uint32_t& nt)
 {
-    const int lane = threadIdx.x & 63;
-    // stage the photons bucketed by 2^INIT_BWS bins; bins >= T become zero
-    // counts at the last bucket's last bin
+    const int lane = P.lane;
+    const int nz = init_chunks(P.NS, KS ? KS : P.ks);
+    for (int x = lane; x < nz; x += 64) P.Z[x] = (v4i){0, 0, 0, 0};
+    wave_sync();
+    uint32_t* Zw = reinterpret_cast<uint32_t*>(P.Z);
+    uint32_t most = 0;
+    for (int r0 = 0; r0 < W.side; r0 += 3) {
+        uint32_t a[3], n[3], len = 0;
 #pragma unroll
-    for (int u = 0; u < INIT_EPL; ++u) {
-        if (STAGED || lane + 64 * u >= total) break;
-        const uint32_t v = pe[u];
-        const int t = ent_bin(v);
-        const int pos = bend.fetch_inc(min(t >> INIT_BWS, nk - 1));
-        E[pos] = t < T ? v : ((uint32_t)((nk << INIT_BWS) - 1) << 16);
-    }
-    // each photon raises the bound of every sub-block whose tau can see it by
-    // z x the largest weight over those lags (M, indexed by the lag of the
-    // sub-block's first tau, which falls by INIT_SB per sub-block)
+        for (int r = 0; r < 3; ++r) {       // (lanes past the rows hold empty ranges)
+            a[r] = (uint32_t)__builtin_amdgcn_readlane((int)W.rs, r0 + r);
+            n[r] = (uint32_t)__builtin_amdgcn_readlane((int)W.re, r0 + r) - a[r];
+            len = max(len, n[r]);
+        }
+        for (uint32_t c0 = 0; c0 < len; c0 += 256) {
+            uint32_t v[3][4];
 #pragma unroll
-    for (int u = 0; u < INIT_EPL; ++u) {
-        if (STAGED || lane + 64 * u >= total) break;
-        const int t = ent_bin(pe[u]);
-        if (t < T) bound_photon<false>(bnd2, Mz, np, t + o, (uint32_t)ent_cnt(pe[u]));
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    v[r][u] = 0xffff0000u;                             // (a bin past every histogram)
+                    if (c0 + 64 * u < n[r]) {                          // (uniform)
+                        const uint32_t x = c0 + 64 * u + lane;
+                        if (x < n[r]) v[r][u] = W.ent[a[r] + x];
+                    }
+                }
+            uint32_t old[3][4];
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    old[r][u] = 0;
+                    if (!(c0 + 64 * u < n[r])) continue;               // (uniform)
+                    const int t = ent_bin(v[r][u]);
+                    const uint32_t z = (uint32_t)ent_cnt(v[r][u]);
+                    if (t >= T) continue;
+                    nt += z;
+                    const uint32_t zs = min(z, 128u);
+                    const int x = t + o;
+                    const int sh = (x & 3) << 3;
+                    old[r][u] = ((atomicAdd(&Zw[x >> 2], zs << sh) >> sh) & 0xffu) + zs;
+                }
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) most = max(most, old[r][u]);
+        }
     }
     wave_sync();
-    // blocks lane and lane + 64: the largest sub-block bound; the cached
-    // exact best
-    uint32_t bmx[2], bsc[2];
-    int btau[2];
-    bool cached[2], has[2];
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-        const int b = lane + 64 * s2;
-        bmx[s2] = b < nb ? block_bound(bnd, nbs, b) : 0u;
-        cached[s2] = b >= nb;     // blocks past the end are never picked
-        has[s2] = false;
-        bsc[s2] = 0;
-        btau[s2] = NO_TAU;
-    }
-    // Blocks are picked by one wave maximum of a key: the block's bound
-    // rounded up to 24 significant bits (shift sh; bounds only fall later),
-    // plus one, above 127 - the block's index (smallest index on ties).  Any
-    // unscored block's bound is at most the largest key's rounded bound.
-    const uint32_t ball = wave_max_u32(max(bmx[0], bmx[1]));
-    const int sh = max(0, 32 - (int)__clz(ball) - 24);
-    const uint32_t rmask = (1u << sh) - 1u;
-    const double k2 = p.kappa * p.kappa;
-    for (int it = 0; it < p.k_init; ++it) {
-        // best over the blocks whose exact best is known
-        uint32_t best = 0;
-        int bestt = NO_TAU;
-        bool hb;
-        {
-            uint32_t key = 0;
-            int kt = NO_TAU;
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-                if (cached[s2] && has[s2] && (bsc[s2] + 1 > key || (bsc[s2] + 1 == key && btau[s2] < kt))) {
-                    key = bsc[s2] + 1;
-                    kt = btau[s2];
+    return __ballot(most > 127u) != 0ull;
+}
+
+// The same into two planes, pixel by pixel of the window (the bins of one
+// pixel's list are distinct, so no two lanes meet in a byte and a byte holds at
+// most 254 before its 128 moves to the upper plane).  Returns whether a bin
+// passed 16383 photons.
+__device__ __forceinline__ bool fill_planes(const InitPool<0, true>& P, const PoolRows& W, const uint32_t* off,
+                                            long long base, int cols, int i, int j, int rows, int T, int o, uint32_t& nt)
+{
+    const int lane = P.lane, R = W.side >> 1;
+    for (int x = lane; x < 2 * P.plane; x += 64) P.Z[x] = (v4i){0, 0, 0, 0};
+    wave_sync();
+    uint32_t* lo = reinterpret_cast<uint32_t*>(P.Z);
+    uint32_t* hi = reinterpret_cast<uint32_t*>(P.Z + P.plane);
+    bool over = false;
+    for (int di = max(-R, -i); di <= min(R, rows - 1 - i); ++di)
+        for (int dj = max(-R, -j); dj <= min(R, cols - 1 - j); ++dj) {
+            const uint32_t* q = off + base + (long long)di * cols + dj;
+            const uint32_t e0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[0]);
+            const uint32_t e1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)q[1]);
+            for (uint32_t x0 = e0; x0 < e1; x0 += 64) {
+                const uint32_t v = x0 + lane < e1 ? W.ent[x0 + lane] : 0xffff0000u;
+                const int t = ent_bin(v);
+                const uint32_t z = (uint32_t)ent_cnt(v);
+                if (t < T) {
+                    nt += z;
+                    const int x = t + o, sh = (x & 3) << 3;
+                    const uint32_t zl = z & 127u;
+                    const bool carry = ((atomicAdd(&lo[x >> 2], zl << sh) >> sh) & 0xffu) + zl > 127u;
+                    if (carry) atomicSub(&lo[x >> 2], 128u << sh);
+                    const uint32_t zh = min((z >> 7) + (carry ? 1u : 0u), 128u);
+                    if (zh) over = over || ((atomicAdd(&hi[x >> 2], zh << sh) >> sh) & 0xffu) + zh > 127u;
                 }
-            const uint32_t mx = wave_max_u32(key);
-            hb = mx != 0;
-            if (hb) {
-                best = mx - 1;
-                bestt = (int)wave_min_u32(key == mx ? (unsigned)kt : 0xffffffffu);
+            }
+            wave_sync();
+        }
+    return __ballot(over) != 0ull;
+}
+
+// The unscored block with the largest bound: the bounds of blocks lane + 64 u
+// in registers (u < PICK_REGS; 0: scored or past the last block), reloaded
+// every round.
+constexpr int PICK_REGS = 8;
+
+struct PickRegs {
+    uint32_t v[PICK_REGS];
+
+    __device__ __forceinline__ void load(const uint32_t* B, int nblk, int lane)
+    {
+#pragma unroll
+        for (int u = 0; u < PICK_REGS; ++u) {
+            v[u] = 0;
+            if (64 * u < nblk) {                         // (uniform)
+                const uint32_t x = B[min(lane + 64 * u, nblk - 1)];
+                v[u] = lane + 64 * u < nblk ? x : 0u;
             }
         }
-        while (true) {
-            // the unscored block with the largest rounded bound
-            uint32_t key = 0;
+    }
+
+    // whether some bound plus one is above thr
+    __device__ __forceinline__ bool above(uint32_t thr) const { return __ballot(most() > thr) != 0ull; }
+
+    // the largest bound plus one (0: none is left) and its block
+    __device__ __forceinline__ uint32_t pick(int& block) const
+    {
+        const uint32_t mx = wave_reduce<OpMax>(most());
+        block = 0;
 #pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-                if (!cached[s2]) {
-                    const uint32_t k = (bmx[s2] >> sh) + ((bmx[s2] & rmask) != 0u) + 1u;
-                    key = max(key, (k << 7) | (uint32_t)(127 - (lane + 64 * s2)));
-                }
-            const uint32_t mx = wave_max_u32(key);
-            if (mx == 0) break;                                   // every block scored
-            const int bb = 127 - (int)(mx & 127u);
-            const unsigned long long bu = (unsigned long long)((mx >> 7) - 1u) << sh;
-            if (hb && bu < best) break;                           // no unscored tau can reach best
-            const int hi = bb >> 6;                               // wave-uniform
-            // exact scores of its 64 tau, and their best (tau rises with the lane)
-            const int tau = (bb << 6) + lane;
-            const uint32_t sc = score_block(E, bend, nk, bb, qs, L, o);
-            const bool valid = tau < T && !(pk.suppresses_any(bb << 6, (bb << 6) + 63, m.wnms) &&
-                                            pk.suppressed(tau, m.wnms));
-            const uint32_t sk = valid ? sc + 1 : 0;
-            const uint32_t smx = wave_max_u32(sk);
-            int st = NO_TAU;
-            if (smx != 0) st = (bb << 6) + (int)__ffsll((long long)__ballot(sk == smx)) - 1;
-            if (lane == (bb & 63)) {
-                if (hi) {
-                    cached[1] = true;
-                    has[1] = smx != 0;
-                    bsc[1] = smx - 1;
-                    btau[1] = st;
-                } else {
-                    cached[0] = true;
-                    has[0] = smx != 0;
-                    bsc[0] = smx - 1;
-                    btau[0] = st;
-                }
+        for (int u = PICK_REGS - 1; u >= 0; --u) {
+            const unsigned long long hit = __ballot(v[u] == mx);
+            block = hit ? 64 * u + __builtin_ctzll(hit) : block;
+        }
+        return mx;
+    }
+
+    __device__ __forceinline__ uint32_t most() const
+    {
+        uint32_t key = 0;
+#pragma unroll
+        for (int u = 0; u < PICK_REGS; ++u) key = max(key, v[u]);
+        return key;
+    }
+
+    // blocks d0 .. d0 + n - 1 are scored (n <= 16)
+    __device__ __forceinline__ void mark(int d0, int n, int lane)
+    {
+#pragma unroll
+        for (int u = 0; u < PICK_REGS; ++u)
+            if (u == d0 >> 6 || u == (d0 + n - 1) >> 6) {  // (uniform)
+                if ((unsigned)(lane + 64 * u - d0) < (unsigned)n) v[u] = 0;
             }
-            if (smx != 0 && (!hb || smx - 1 > best || (smx - 1 == best && st < bestt))) {
+    }
+};
+
+// The same for any number of blocks, from LDS with a bit per block.
+struct PickLoop {
+    const uint32_t* B;
+    int nblk, lane;
+    uint32_t done;          // bit u: block lane + 64 u scored
+
+    __device__ __forceinline__ void load(const uint32_t* b, int n, int l)
+    {
+        B = b;
+        nblk = n;
+        lane = l;
+        done = 0;
+    }
+
+    __device__ __forceinline__ uint32_t most(int& kb) const
+    {
+        uint32_t key = 0;
+        kb = 0;
+        for (int u = 0, b = lane; b < nblk; ++u, b += 64) {
+            const uint32_t v = (done >> u) & 1u ? 0u : B[b];
+            if (v > key) {
+                key = v;
+                kb = b;
+            }
+        }
+        return key;
+    }
+
+    __device__ __forceinline__ bool above(uint32_t thr) const
+    {
+        int kb;
+        return __ballot(most(kb) > thr) != 0ull;
+    }
+
+    __device__ __forceinline__ uint32_t pick(int& block) const
+    {
+        int kb;
+        const uint32_t key = most(kb);
+        const uint32_t mx = wave_reduce<OpMax>(key);
+        block = __builtin_amdgcn_readlane(kb, __builtin_ctzll(__ballot(key == mx)));
+        return mx;
+    }
+
+    __device__ __forceinline__ void mark(int d0, int n, int)
+    {
+        const int d1 = d0 + n - 1, u = (d1 - lane) >> 6;     // the last block of this lane at or below d1
+        if (d1 >= lane && lane + 64 * u >= d0) done |= 1u << u;
+    }
+};
+
+template <bool REGS> struct PickOf { typedef PickRegs T; };
+template <> struct PickOf<false> { typedef PickLoop T; };
+
+// d * d >= k2 * bw and d >= 0 for d = nwin - bw, bw = ntot * win / T, as the
+// FP64 expressions decide: first in FP32, whose error is below 1e-6 of the
+// terms, and in FP64 where that is too close.
+__device__ __forceinline__ bool stands_out(uint32_t nwin, uint32_t ntot, int win, int T, double kappa)
+{
+    const float bwf = (float)ntot * (float)win * __builtin_amdgcn_rcpf((float)T);
+    const float df = (float)nwin - bwf, big = (float)nwin + bwf;
+    const float k2f = (float)kappa * (float)kappa;
+    const float l = df * df, r = k2f * bwf, tol = 1e-4f * (big * big + r);
+    const bool yes = df > 1e-4f * big && l > r + tol, no = df < -1e-4f * big || l < r - tol;
+    if (__builtin_amdgcn_readfirstlane((int)(yes || no))) return __builtin_amdgcn_readfirstlane((int)yes) != 0;
+    const double bw = (double)ntot * (double)win / (double)T;
+    const double d = (double)nwin - bw;
+    const double k2 = kappa * kappa;
+    return d >= 0.0 && d * d >= k2 * bw;
+}
+
+// The search over the dense pool.  The caller has checked that the scores fit
+// their type: ntot x the largest weight below 2^32 - 1 with one plane.
+template <int KS, bool WIDE>
+__device__ __forceinline__ void dense_search(const InitPool<KS, WIDE>& P, uint32_t ntot, Peaks& pk)
+{
+    const int lane = P.lane;
+    P.bound_all();
+    wave_sync();
+    typename PickOf<(KS > 0)>::T pick;
+    for (int it = 0;; ++it) {
+        const InitArgs& A = init_args();
+        const DevModel& m = A.m;
+        const int T = m.T, o = m.o, nblk = (T + 15) >> 4, a0max = 16 * P.NS - 16;
+        const int up = m.qshift;
+        pick.load(P.B, nblk, lane);
+        typedef typename InitPool<KS, WIDE>::Score Score;
+        Score best = 0;
+        int bestt = NO_TAU;
+        int bb = 0;
+        while (pick.pick(bb) != 0) {
+            // exact scores of the blocks around it (one tile), plus one (0: past
+            // the last bin or under a peak's suppression)
+            int st = NO_TAU;
+            const int d0 = min(max(bb - 8, 0), a0max);
+            constexpr Score NONE = ~(Score)0;
+            Score sc[4], sk = 0;
+            P.score_tile(d0, m.qshift, sc);
+            const int t0 = 16 * (d0 + P.j) + 4 * P.g;
+            if (16 * d0 + 255 >= T) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sc[r] = t0 + r < T ? sc[r] : NONE;
+            }
+#pragma unroll
+            for (int k = 0; k < KM; ++k)
+                if (k < pk.n && (unsigned)(pk.t[k] + m.wnms - 16 * d0) <= (unsigned)(255 + 2 * m.wnms)) {
+                    const int x = t0 - pk.t[k] + m.wnms;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        sc[r] = (unsigned)(x + r) <= (unsigned)(2 * m.wnms) ? NONE : sc[r];
+                }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                ++sc[r];
+                sk = max(sk, sc[r]);
+            }
+            pick.mark(d0, 16, lane);
+            const Score smx = wave_max(sk);
+            if (smx != 0) {
+                // the first tau that reaches it
+                int tk = NO_TAU;
+#pragma unroll
+                for (int r = 3; r >= 0; --r) tk = sc[r] == smx ? t0 + r : tk;
+                const unsigned long long hit = __ballot(sk == smx);
+                st = hit & (hit - 1ull) ? (int)wave_reduce<OpMin>((uint32_t)tk)
+                                        : __builtin_amdgcn_readlane(tk, __builtin_ctzll(hit));
+            }
+            if (smx != 0 && (bestt == NO_TAU || smx - 1 > best || (smx - 1 == best && st < bestt))) {
                 best = smx - 1;
                 bestt = st;
-                hb = true;
             }
+            // a block whose bound is at least best may still reach (or tie) it:
+            // bound 2^up >= best, i.e. bound + 1 > ceil(best / 2^up)
+            const uint32_t thr = (uint32_t)(((unsigned long long)best + ((1ull << up) - 1ull)) >> up);
+            if (bestt != NO_TAU && !pick.above(thr)) break;
         }
-        if (!hb) break;                      // every tau suppressed
+        if (bestt == NO_TAU) break;          // every tau suppressed
         const int a = max(0, bestt - m.wl), c = min(T - 1, bestt + m.wr);
-        uint32_t win = 0;
-        for (int tb = a + lane; tb <= c; tb += 64) win += pk.owner(tb) < 0;
-        win = wave_sum_u32(win);
+        int win = 0;
         uint32_t nwin = 0;                                      // at most ntot
-        const int b0 = a >> INIT_BWS, b1 = min(nk - 1, c >> INIT_BWS);
-        const int x0 = b0 > 0 ? bend.get(b0 - 1) : 0, x1 = bend.get(b1);
-        for (int x = x0 + lane; x < x1; x += 64) {
-            const uint32_t v = E[x];
-            const int tb = ent_bin(v);
-            if (tb >= a && tb <= c) nwin += ent_cnt(v);        // claimed photons count zero
+        for (int t0 = a; t0 <= c; t0 += 64) {
+            const int tb = t0 + lane;
+            const bool open = tb <= c && !pk.claimed(m, tb);
+            win += popc_ballot(open);
+            if (open) nwin += P.count(tb + o);
         }
-        nwin = wave_sum_u32(nwin);
-        const double bw = (double)ntot * (double)win / (double)T;
-        const double d = (double)nwin - bw;
-        const bool accept = win > 0 && (long long)nwin >= p.n_min && d >= 0.0 && d * d >= k2 * bw;
-        if (!accept) break;
-        pk.push(bestt, a, c, (int)win);
-        // the peak claims the photons of its window: their counts drop to zero,
-        // and their terms leave the bounds (which stay exact sums over the
-        // unclaimed photons, so later rounds prune near the claimed peak)
-        for (int x = x0 + lane; x < x1; x += 64) {
-            const uint32_t v = E[x];
-            const int tb = ent_bin(v), z = ent_cnt(v);
-            if (tb >= a && tb <= c) {
-                E[x] = v & 0xffff0000u;
-                if (z > 0) bound_photon<true>(bnd2, Mz, np, tb + o, (uint32_t)z);
-            }
-        }
+        nwin = wave_reduce<OpAdd>(nwin);
+        if (!(win > 0 && (long long)nwin >= A.p.n_min && stands_out(nwin, ntot, win, T, A.p.kappa))) break;
+        pk.push(bestt, win);
+        if (it + 1 >= A.p.k_init) break;
+        // the peak claims the photons of its window, and the blocks that see
+        // those bins are bounded afresh
+        for (int tb = a + lane; tb <= c; tb += 64) P.clear(tb + o);
         wave_sync();
-        // blocks the new peak changes: tau that see its claimed bins (their
-        // bounds are recomputed) or fall under its suppression forget their
-        // best
-        const int A0 = a + o - L + 1, A1 = c + o, S0 = bestt - m.wnms, S1 = bestt + m.wnms;
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            const int b = lane + 64 * s2;
-            const int ta = b << 6, tb = (b << 6) + 63;
-            const bool seen = ta <= A1 && tb >= A0;
-            if (b < nb && (seen || (ta <= S1 && tb >= S0))) cached[s2] = false;
-            if (b < nb && seen) bmx[s2] = block_bound(bnd, nbs, b);
-        }
+        const int b0 = max(0, a + o - m.L + 1) >> 4, b1 = min(T - 1, c + o) >> 4;
+        for (int x = b0; x <= b1; x += 16) P.bound_tile(min(x, a0max));
+        wave_sync();
     }
 }
 
-// Stages the IRF weights (INIT_QPAD zeros, the L weights, INIT_QPAD zeros)
-// and their sliding maximum over INIT_SB lags (Mz, zero-padded) in LDS, with
-// the whole workgroup; returns the largest weight (wave-uniform).  Without QL
-// the weights stay in HBM and the result is 0.
-template <bool QL>
-__device__ __forceinline__ int stage_weights(const DevModel& m, int* qs, int* Mz)
-{
-    const int L = m.L, lane = threadIdx.x & 63;
-    if (QL) {
-        for (int k = threadIdx.x; k < L + 2 * INIT_QPAD; k += blockDim.x) {
-            const int lag = k - INIT_QPAD;
-            qs[k] = (lag >= 0 && lag < L) ? m.q[lag] : 0;
-        }
-        __syncthreads();
-        const int nz = (int)q_window_ints(L);
-        for (int k = threadIdx.x; k < nz; k += blockDim.x) {
-            const int x = k - INIT_SB;
-            int mx = 0;
-            if (x >= 0 && x <= L + INIT_SB - 2) {
-#pragma unroll
-                for (int d = 0; d < INIT_SB; ++d) mx = max(mx, qs[INIT_QPAD + x - d]);
-            }
-            Mz[k] = mx;
-        }
-    }
-    __syncthreads();
-    int qmax = 0;
-    if (QL) {
-        for (int k = lane; k < L; k += 64) qmax = max(qmax, qs[INIT_QPAD + k]);
-        qmax = (int)wave_max_u32((unsigned)qmax);
-    }
-    return qmax;
-}
-
-// Entry index of pooled photon k: window row r's photons (one CSR range,
-// starting at rs of lane r) take pooled indices from rend - rlen of lane r.
-__device__ __forceinline__ uint32_t pooled_src(uint32_t k, int side, uint32_t rend, uint32_t rlen, uint32_t rs)
-{
-    uint32_t src = 0;
-    for (int r = 0; r < side; ++r) {
-        const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)(rend - rlen), r);
-        const uint32_t rb = (uint32_t)__builtin_amdgcn_readlane((int)rs, r);
-        if (k >= r0) src = rb + (k - r0);
-    }
-    return src;
-}
-
-// One wavefront's initialisation of pixel pix, with the wavefront's LDS area
-// at wbase.  QL: the weights are staged in LDS (qs, M; qmax their largest).
-// WIDE: the pool may hold up to INIT_WIDE_ELDS photons, staged in passes over
-// HBM; otherwise pools of INIT_ELDS to INIT_WIDE_ELDS photons that the LDS
-// path could score are appended to the list `wide` (count first) when it is
-// given, and left for the wide kernel.
-template <bool QL, bool WIDE>
-__device__ __forceinline__ void init_pixel(const DevModel& m, const DevParams& p, const Shape& sh,
-                                           const uint32_t* __restrict__ off, const uint32_t* __restrict__ ent,
-                                           const float* __restrict__ gain, DevState& s, long long pix,
-                                           unsigned long long* wbase, const int* qs, const int* Mz, int qmax,
-                                           uint32_t* wide)
+// The search from global memory: an exact branch and bound over blocks of 64
+// tau (one tau per lane) with 64-bit sums.  An upper bound of every block's
+// best score, sum over pooled photons of z x the largest weight over the lags
+// the block can see, is added up in LDS; blocks are scored exactly in
+// decreasing bound order until no remaining bound can beat (or tie at a
+// smaller tau) the best score.  The bounds count every photon, so they stay
+// valid after photons are claimed.
+__device__ __forceinline__ void lists_search(const DevModel& m, const DevParams& p, const Shape& sh,
+                                          const uint32_t* __restrict__ off, const uint32_t* __restrict__ ent,
+                                          long long fr, int i, int j, unsigned long long* wbase, Peaks& pk)
 {
     const int lane = threadIdx.x & 63;
     const int T = m.T, L = m.L, o = m.o;
     const int R = p.r_init, side = 2 * R + 1;
-    const int* qt = QL ? qs + INIT_QPAD : m.q;
     const int* qstt = m.qst;
-    const long long S = sh.S;
     const int nb = (T + 63) >> 6;
     uint2* lists = reinterpret_cast<uint2*>(wbase);
-    unsigned long long* ub = wbase + side * side;                    // the HBM path's block bounds
-    unsigned long long* lb = wbase;                                  // the LDS path's area
-    (void)qt;
-
-    if (lane < KM) {
-        s.t[lane * S + pix] = 0.0;
-        s.r[lane * S + pix] = 0.f;
-        s.n[(0 * KM + lane) * S + pix] = 0.f;
-        s.n[(1 * KM + lane) * S + pix] = 0.f;
-        s.n[(2 * KM + lane) * S + pix] = -1.f;
-    }
-    const int per_frame = sh.rows * sh.cols;
-    const long long fr = pix / per_frame;
-    const int i = (int)((pix / sh.cols) % sh.rows), j = (int)(pix % sh.cols);
-
-    // pooled photons: lane r < side holds the CSR range of window row i - R + r
-    // (the row's pixels are consecutive, so their photons are one range)
-    uint32_t rs = 0, re = 0;
+    unsigned long long* ub = wbase + side * side;                    // the block bounds
+    long long ntot;
     {
-        const int i2 = i - R + lane;
-        if (lane < side && i2 >= 0 && i2 < sh.rows) {
-            const long long base = (fr * sh.rows + i2) * sh.cols;
-            rs = off[base + max(0, j - R)];
-            re = off[base + min(sh.cols - 1, j + R) + 1];
-        }
-    }
-    const float G = gain_at(gain, pix);
-    if (!(G > 0.f)) {
-        if (lane == 0) {
-            s.cnt[pix] = 0;
-            s.b[pix] = (float)p.b_min;
-        }
-        return;
-    }
-    const uint32_t rlen = re - rs;
-    const uint32_t rend = wave_incl_scan(rlen);                 // pooled index just past row lane
-    const int total = (int)__builtin_amdgcn_readlane((int)rend, 63);
-
-    Peaks pk;
-    pk.n = 0;
-#pragma unroll
-    for (int j = 0; j < KM; ++j) pk.t[j] = pk.a[j] = pk.c[j] = pk.w[j] = 0;
-
-    // Branch and bound from LDS when the pool fits, the weights are staged,
-    // and every score fits 32 bits (checked once the photons are read).
-    const int nbs = (T + INIT_SB - 1) / INIT_SB;
-    const bool ldsok = QL && nbs <= INIT_NB_LDS && qmax < (1 << 24);
-    if (!WIDE && wide && ldsok && total > INIT_ELDS && total <= INIT_WIDE_ELDS) {
-        if (lane == 0) {
-            const unsigned sg = blockIdx.x % INIT_LIST_SEGS;
-            wide[INIT_LIST_HDR + sg * init_list_cap(sh.P) + atomicAdd(&wide[sg * INIT_LIST_STRIDE], 1u)] =
-                (uint32_t)pix;
-        }
-        return;
-    }
-    constexpr int ELDS = WIDE ? INIT_WIDE_ELDS : INIT_ELDS;
-    bool lds = ldsok && total <= ELDS;
-    uint32_t pe[INIT_EPL];
-    long long ntot = 0;
-    const int nk = (T + (1 << INIT_BWS) - 1) >> INIT_BWS;
-    const int np = init_np(L);
-    const int bw2 = (int)init_bound_words(T, L, o);
-    uint32_t* bnd = reinterpret_cast<uint32_t*>(lb) + 2 * np - 2;    // [nbs] sub-block bounds, after their guards
-    uint32_t* E = reinterpret_cast<uint32_t*>(lb + bw2);             // [ELDS] bucketed photons
-    const Bend16 bend{E + ELDS};                                    // [nk] bucket ends, 16 bits each
-    const int nkw = (nk + 1) >> 1;                                  // their words
-    if (lds && WIDE) {
-        // count the photons per bucket while totalling them (a first pass over HBM)
-        for (int b = lane; b < bw2; b += 64) lb[b] = 0ull;
-        for (int b = lane; b < nkw; b += 64) bend.w[b] = 0u;
-        wave_sync();
-        uint32_t nt = 0;                        // at most INIT_WIDE_ELDS x 65535
-        // four 64-entry chunks per round, their loads in flight together
-        for (int c0 = 0; c0 < total; c0 += 256) {
-            uint32_t v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = c0 + 64 * u + lane;
-                const uint32_t x = pooled_src((uint32_t)k, side, rend, rlen, rs);
-                v[u] = k < total ? ent[x] : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (c0 + 64 * u + lane < total) {
-                    if (ent_bin(v[u]) < T) nt += ent_cnt(v[u]);
-                    bend.add1(min(ent_bin(v[u]) >> INIT_BWS, nk - 1));
-                }
-        }
-        ntot = wave_sum_u32(nt);
-        lds = (unsigned long long)ntot * (unsigned long long)qmax <= 0xfffffffeull;
-    }
-    if (lds && !WIDE) {
-        // read the pooled photons once: entry k of the pool is lane k % 64's
-        // pe[k / 64]
-        uint32_t src[INIT_EPL];
-#pragma unroll
-        for (int u = 0; u < INIT_EPL; ++u) src[u] = 0;
-        for (int r = 0; r < side; ++r) {
-            const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)(rend - rlen), r);
-            const uint32_t rb = (uint32_t)__builtin_amdgcn_readlane((int)rs, r);
-#pragma unroll
-            for (int u = 0; u < INIT_EPL; ++u) {
-                const uint32_t k = (uint32_t)(lane + 64 * u);
-                if (k >= r0) src[u] = rb + (k - r0);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < INIT_EPL; ++u) pe[u] = lane + 64 * u < total ? ent[src[u]] : 0u;
-        uint32_t nt = 0;                        // at most INIT_ELDS x 65535
-#pragma unroll
-        for (int u = 0; u < INIT_EPL; ++u)
-            if (lane + 64 * u < total && ent_bin(pe[u]) < T) nt += ent_cnt(pe[u]);
-        ntot = wave_sum_u32(nt);
-        lds = (unsigned long long)ntot * (unsigned long long)qmax <= 0xfffffffeull;
-    }
-    if (lds) {
-        // Count the photons per 2^INIT_BWS-bin bucket, scan the counts into
-        // bucket starts, then stage, bound and search them.
-        if (!WIDE) {
-            for (int b = lane; b < bw2; b += 64) lb[b] = 0ull;
-            for (int b = lane; b < nkw; b += 64) bend.w[b] = 0u;
-            wave_sync();
-#pragma unroll
-            for (int u = 0; u < INIT_EPL; ++u) {
-                if (lane + 64 * u >= total) break;
-                bend.add1(min(ent_bin(pe[u]) >> INIT_BWS, nk - 1));
-            }
-        }
-        wave_sync();
-        // bucket starts (exclusive prefix of the counts); each bucket's cursor
-        // ends at the bucket's end once the photons are staged
-        // (a word's two buckets at a time; a padding bucket past nk counts 0)
-        uint32_t carry = 0;
-        for (int c0 = 0; c0 < nkw; c0 += 64) {
-            const int b = c0 + lane;
-            const uint32_t wd = b < nkw ? bend.w[b] : 0u;
-            const uint32_t lo = wd & 0xffffu, cnt = lo + (wd >> 16);
-            const uint32_t inc = wave_incl_scan(cnt);
-            const uint32_t s0 = carry + inc - cnt;
-            if (b < nkw) bend.w[b] = s0 | ((s0 + lo) << 16);
-            carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-        }
-        wave_sync();
-        if (WIDE) {
-            // second pass over HBM: stage each photon in its bucket (bins >= T
-            // become zero counts at the last bucket's last bin) and add it to
-            // the bounds of the sub-blocks whose tau can see it
-            for (int c0 = 0; c0 < total; c0 += 256) {
-                uint32_t vv[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int k = c0 + 64 * u + lane;
-                    const uint32_t x = pooled_src((uint32_t)k, side, rend, rlen, rs);
-                    vv[u] = k < total ? ent[x] : 0u;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (c0 + 64 * u + lane >= total) continue;
-                    const uint32_t v = vv[u];
-                    const int t = ent_bin(v), z = ent_cnt(v);
-                    const int pos = bend.fetch_inc(min(t >> INIT_BWS, nk - 1));
-                    E[pos] = t < T ? v : ((uint32_t)((nk << INIT_BWS) - 1) << 16);
-                    if (t < T) bound_photon<false>(lb, Mz, np, t + o, (uint32_t)z);
-                }
-            }
-            wave_sync();
-        }
-        lds_search<WIDE>(m, p, T, L, o, nb, nbs, nk, pe, total, ntot, qs, Mz, lb, np, bnd, E, bend, pk);
-    } else {
         // the window's pixels' photon lists (each ascending in t)
         const int npl = side * side;
         for (int w = lane; w < npl; w += 64) {
@@ -854,7 +794,7 @@ __device__ __forceinline__ void init_pixel(const DevModel& m, const DevParams& p
                     for (uint32_t x = rg.x + c0; x < rg.x + c1; ++x) {
                         const uint32_t v = ent[x];
                         const int tb = ent_bin(v);
-                        if (pk.owner(tb) >= 0) continue;
+                        if (pk.claimed(m, tb)) continue;
                         const int lag = tb - tau + o;
                         if ((unsigned)lag < (unsigned)L) sc += (long long)ent_cnt(v) * (long long)m.q[lag];
                     }
@@ -879,7 +819,7 @@ __device__ __forceinline__ void init_pixel(const DevModel& m, const DevParams& p
             if (bestt == 0x7fffffff) break;          // every tau suppressed
             const int a = max(0, bestt - m.wl), c = min(T - 1, bestt + m.wr);
             int win = 0;
-            for (int tb = a + lane; tb <= c; tb += 64) win += pk.owner(tb) < 0;
+            for (int tb = a + lane; tb <= c; tb += 64) win += !pk.claimed(m, tb);
             win = wave_sum(win);
             long long nwin = 0;
             for (int l = 0; l < npl; ++l) {
@@ -887,7 +827,7 @@ __device__ __forceinline__ void init_pixel(const DevModel& m, const DevParams& p
                 for (uint32_t e = rg.x + lane; e < rg.y; e += 64) {
                     const uint32_t v = ent[e];
                     const int tb = ent_bin(v);
-                    if (tb >= a && tb <= c && pk.owner(tb) < 0) nwin += ent_cnt(v);
+                    if (tb >= a && tb <= c && !pk.claimed(m, tb)) nwin += ent_cnt(v);
                 }
             }
             nwin = wave_sum(nwin);
@@ -895,143 +835,326 @@ __device__ __forceinline__ void init_pixel(const DevModel& m, const DevParams& p
             const double d = (double)nwin - bw;
             const bool accept = win > 0 && nwin >= p.n_min && d >= 0.0 && d * d >= k2 * bw;
             if (!accept) break;
-            pk.push(bestt, a, c, win);
+            pk.push(bestt, win);
         }
     }
-    const int npk = pk.n;
+}
 
-    // own photons: total and per claimed window
-    // (a pixel holds at most 65535 entries, each count below 65536: the sums
-    // fit 32 bits)
-    const uint32_t e0 = off[pix], e1 = off[pix + 1];
-    uint32_t zp = 0;
-    uint32_t nown[KM] = {0, 0, 0, 0};
-    for (uint32_t e = e0 + lane; e < e1; e += 64) {
-        const uint32_t v = ent[e];
-        const uint32_t z = (uint32_t)ent_cnt(v);
-        zp += z;
-        const int ow = pk.owner(ent_bin(v));
+// The peaks of the wavefront's pixels, pixel x's peak k in lane 4 x + k, from
+// which finish() makes the initial states of all of them at once (the sixteen
+// FP64 divisions and the scattered stores of one pixel would otherwise keep
+// four lanes busy).
+constexpr int INIT_PPW_MAX = 16;
+enum : int { PIX_NONE = 0, PIX_LIVE = 1, PIX_DEAD = 2, PIX_LEFT = 3 };
+constexpr uint8_t INIT_LEFT = 255;   // the count of a pixel k_init leaves to k_init_rest
+
+struct InitRecords {
+    int t, w, mode;         // tau and window of the lane's peak; the pixel's mode
+    uint32_t nown, zp;      // own photons in the peak's window; all own photons
+    float G;
+    double H;               // IRF mass in the window
+
+    __device__ __forceinline__ void clear()
+    {
+        t = w = mode = 0;
+        nown = zp = 0;
+        G = 1.f;
+        H = 0.0;
+    }
+
+    __device__ __forceinline__ void set_mode(int x, int md)
+    {
+        if ((int)((threadIdx.x & 63) >> 2) == x) mode = md;
+    }
+
+    // pixel x's accepted peaks: v0 the first 64 of its own entries e0 .. e1 - 1
+    __device__ __forceinline__ void set(int x, const Peaks& pk, float g, uint32_t v0, uint32_t e0, uint32_t e1,
+                                        double hfull)
+    {
+        const InitArgs& A = init_args();
+        const DevModel& m = A.m;
+        const int lane = threadIdx.x & 63;
+        // own photons: total and per claimed window
+        // (a pixel holds at most 65535 entries, each count below 65536: the
+        // sums fit 32 bits)
+        uint32_t z = 0, n[KM] = {0, 0, 0, 0};
+        uint32_t v = e0 + lane < e1 ? v0 : 0u;
+        for (uint32_t e = e0;;) {
+            const uint32_t zv = (uint32_t)ent_cnt(v);
+            z += zv;
+            if (pk.n > 0) {
+                const int ow = pk.owner(m, ent_bin(v));
+#pragma unroll
+                for (int k = 0; k < KM; ++k)
+                    if (k < pk.n) n[k] += ow == k ? zv : 0u;
+            }
+            e += 64;
+            if (e >= e1) break;
+            v = e + lane < e1 ? A.ent[e + lane] : 0u;
+        }
+        if (__ballot(z >= 1024u) == 0ull) {                    // sums below 65536: two per word
+            const uint32_t s0 = wave_reduce<OpAdd>(z | (n[0] << 16));
+            z = s0 & 0xffffu;
+            n[0] = s0 >> 16;
+            if (pk.n > 1) {
+                const uint32_t s1 = wave_reduce<OpAdd>(n[1] | (n[2] << 16));
+                n[1] = s1 & 0xffffu;
+                n[2] = s1 >> 16;
+            }
+            if (pk.n > 3) n[3] = wave_reduce<OpAdd>(n[3]);
+        } else {
+            z = wave_reduce<OpAdd>(z);
+#pragma unroll
+            for (int k = 0; k < KM; ++k)
+                if (k < pk.n) n[k] = wave_reduce<OpAdd>(n[k]);
+        }
+        const bool here = (lane >> 2) == x;
+        mode = here ? PIX_LIVE : mode;
+        zp = here ? z : zp;
+        G = here ? g : G;
 #pragma unroll
         for (int k = 0; k < KM; ++k)
-            if (ow == k) nown[k] += z;
-    }
-    zp = wave_sum_u32(zp);
-    double H[KM] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        if (k < npk) {
-            nown[k] = wave_sum_u32(nown[k]);
-            double hs = 0.0;
-            for (int tb = pk.a[k] + lane; tb <= pk.c[k]; tb += 64) {
-                const int idx = tb - pk.t[k] + o;
-                if (pk.owner(tb) == k && idx >= 0 && idx < L) hs += m.hbar[idx];
+            if (k < pk.n) {
+                double h = hfull;
+                if (pk.w[k] != m.wl + m.wr + 1) {     // clipped, or bins claimed before it
+                    const int a = max(0, pk.t[k] - m.wl), c = min(m.T - 1, pk.t[k] + m.wr);
+                    double hs = 0.0;
+                    for (int tb = a + lane; tb <= c; tb += 64) {
+                        const int idx = tb - pk.t[k] + m.o;
+                        if (pk.owner(m, tb) == k && idx >= 0 && idx < m.L) hs += m.hbar[idx];
+                    }
+                    h = wave_sum(hs);
+                }
+                const bool me = lane == 4 * x + k;
+                t = me ? pk.t[k] : t;
+                w = me ? pk.w[k] : w;
+                nown = me ? n[k] : nown;
+                H = me ? h : H;
             }
-            H[k] = wave_sum(hs);
+    }
+
+    // writes the states of pixels first .. first + 15 as far as they are set
+    __device__ __forceinline__ void finish(uint32_t first) const
+    {
+        const InitArgs& A = init_args();
+        const long long S = A.sh.S;
+        const int lane = threadIdx.x & 63, k = lane & 3;
+        const long long pix = (long long)first + (lane >> 2);
+        const long long num = max((long long)zp - (long long)quad_sum_u32(nown), 0ll);
+        const int den = A.m.T - (int)quad_sum_u32((uint32_t)w);
+        // (all below 2^32: exact as doubles, and so are their products)
+        const double fnum = (double)num, fden = (double)den, fw = (double)w, nwk = (double)nown;
+        // the kept peaks take the slots in ascending depth (depths are
+        // distinct): a peak's slot is the number of kept peaks above it; the
+        // other lanes clear the slots past the kept ones
+        bool keep = w > 0 && (den > 0 ? (nwk * fden > fnum * fw) : (nwk > 0.0)) && H > 0.0;
+        const int kt = keep ? t : 0x7fffffff;
+        const uint32_t kept = (uint32_t)(__ballot(keep) >> (lane & ~3)) & 15u;
+        int rank = 0;
+        rank += __builtin_amdgcn_update_dpp(0, kt, 0x00, 0xF, 0xF, true) < kt ? 1 : 0;
+        rank += __builtin_amdgcn_update_dpp(0, kt, 0x55, 0xF, 0xF, true) < kt ? 1 : 0;
+        rank += __builtin_amdgcn_update_dpp(0, kt, 0xAA, 0xF, 0xF, true) < kt ? 1 : 0;
+        rank += __builtin_amdgcn_update_dpp(0, kt, 0xFF, 0xF, 0xF, true) < kt ? 1 : 0;
+        int nkeep = __builtin_popcount(kept);
+        if (!keep) rank = nkeep + __builtin_popcount(~kept & ((1u << k) - 1u));
+        nkeep = min(nkeep, A.p.k_max);
+        keep = keep && rank < nkeep;
+        if (mode == PIX_NONE) return;
+        if (mode == PIX_LEFT) {
+            if (k == 0) A.s.cnt[pix] = INIT_LEFT;
+            return;
+        }
+        const double excess = den > 0 ? nwk - fnum * fw / fden : nwk;
+        A.s.t[rank * S + pix] = keep ? (double)kt : 0.0;
+        A.s.r[rank * S + pix] = keep ? (float)(excess / ((double)G * H)) : 0.f;
+        A.s.n[(0 * KM + rank) * S + pix] = 0.f;
+        A.s.n[(1 * KM + rank) * S + pix] = 0.f;
+        A.s.n[(2 * KM + rank) * S + pix] = -1.f;
+        if (k != 0) return;
+        A.s.cnt[pix] = (uint8_t)nkeep;
+        const double bown = den > 0 && mode == PIX_LIVE ? fnum / fden : 0.0;
+        const double b0 = bown / (double)G;
+        A.s.b[pix] = (float)(b0 > A.p.b_min ? b0 : A.p.b_min);
+    }
+};
+
+// The wavefront's pixel: its place in the frame (32-bit arithmetic: a batch
+// holds below 2^31 pixels).
+struct InitPixel {
+    uint32_t pix;
+    int i, j;
+
+    __device__ __forceinline__ void at(uint32_t p, const Shape& sh)
+    {
+        pix = p;
+        const uint32_t row = p / (uint32_t)sh.cols;
+        j = (int)(p - row * (uint32_t)sh.cols);
+        i = (int)(row % (uint32_t)sh.rows);
+    }
+
+    __device__ __forceinline__ void next(const Shape& sh)
+    {
+        ++pix;
+        if (++j == sh.cols) {
+            j = 0;
+            if (++i == sh.rows) i = 0;
         }
     }
-    long long sum_n = 0, sum_w = 0;                          // (wave-uniform)
-#pragma unroll
-    for (int k = 0; k < KM; ++k)
-        if (k < npk) {
-            sum_n += nown[k];
-            sum_w += pk.w[k];
+
+    // lane r < side holds the CSR range of window row i - R + r (the row's
+    // pixels are consecutive, so their photons are one range)
+    __device__ __forceinline__ PoolRows rows(const Shape& sh, int R, const uint32_t* off, const uint32_t* ent) const
+    {
+        const int lane = threadIdx.x & 63;
+        PoolRows W{0, 0, 2 * R + 1, ent};
+        const int i2 = i - R + lane;
+        if (lane < W.side && i2 >= 0 && i2 < sh.rows) {
+            const long long base = (long long)pix - j + (long long)(i2 - i) * sh.cols;
+            W.rs = off[base + max(0, j - R)];
+            W.re = off[base + min(sh.cols - 1, j + R) + 1];
         }
-    long long num = (long long)zp - sum_n;
-    if (num < 0) num = 0;
-    const long long den = (long long)T - sum_w;
-    // lane k < KM decides peak k (keep, depth, intensity); the kept peaks
-    // take the slots in ascending depth (depths are distinct): a peak's slot
-    // is the number of kept peaks above it
-    long long w = 0;
-    long long nwk = 0;
-    double hk = 0.0;
-    int tk = 0;
+        return W;
+    }
+};
+
+template <int KS, bool WIDE>
+__device__ __forceinline__ InitPool<KS, WIDE> init_pool(const DevModel& m, v4i* area)
+{
+    InitPool<KS, WIDE> P;
+    P.Z = area;
+    P.ks = KS ? KS : m.ks;
+    P.NS = init_stride(m.T);
+    P.plane = init_chunks(P.NS, P.ks);
+    P.B = reinterpret_cast<uint32_t*>(P.Z + (WIDE ? 2 : 1) * P.plane);
+    P.lane = threadIdx.x & 63;
+    P.j = P.lane & 15;
+    P.g = P.lane >> 4;
+    P.qa = reinterpret_cast<const v4i*>(m.qa);
+    P.e = nullptr;
+    return P;
+}
+
+// The IRF mass of a whole peak window (summed as InitRecords::set sums one).
+__device__ __forceinline__ double window_mass(const DevModel& m)
+{
+    double hs = 0.0;
+    for (int x = threadIdx.x & 63; x <= m.wl + m.wr; x += 64) {
+        const int idx = x - m.wl + m.o;
+        if (idx >= 0 && idx < m.L) hs += m.hbar[idx];
+    }
+    return wave_sum(hs);
+}
+
+// Wavefront wv of workgroup b takes the ppw <= 16 consecutive pixels from
+// (b W + wv) ppw on.
+template <int KS>
+__global__ __launch_bounds__(64 * INIT_WAVES, INIT_OCC) void k_init(InitArgs args)
+{
+    extern __shared__ v4i smem[];
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    InitPool<KS, false> P = init_pool<KS, false>(args.m, smem + (size_t)wv * (args.area / 16));
+    if constexpr (KS > 0) {
+        v4i* e = smem + (size_t)nw * (args.area / 16);
+        P.e = e;
+        for (int x = threadIdx.x; x < 2 * KS * 64; x += blockDim.x) e[x] = P.qa[KS * 64 + x];
 #pragma unroll
-    for (int k = 0; k < KM; ++k)
-        if (lane == k) {
-            w = pk.w[k];
-            nwk = nown[k];
-            hk = H[k];
-            tk = pk.t[k];
+        for (int k = 0; k < KS; ++k) P.A[k] = P.qa[k * 64 + lane];
+        __syncthreads();
+    }
+    const double hfull = window_mass(args.m);
+    const int ppw = args.ppw;
+    const uint32_t first = (xcd_block(blockIdx.x, gridDim.x) * nw + wv) * ppw;
+    InitRecords rec;
+    rec.clear();
+    InitPixel q;
+    q.at(first, args.sh);
+    for (int x = 0; x < ppw; ++x) {
+        const InitArgs& A = init_args();
+        // whole wavefront (pixels of other IRF classes: their own launch); no workgroup barriers here
+        if (q.pix >= (uint32_t)A.sh.P) break;
+        if (in_class(A.m, q.pix)) {
+            const PoolRows W = q.rows(A.sh, A.p.r_init, A.off, A.ent);
+            const uint32_t e0 = A.off[q.pix], e1 = A.off[q.pix + 1];
+            const float G = gain_at(A.gain, q.pix);
+            if (!(G > 0.f)) {
+                rec.set_mode(x, PIX_DEAD);
+            } else {
+                const uint32_t v0 = e0 + lane < e1 ? A.ent[e0 + lane] : 0u;
+                // 65536 entries of at most 65535 photons: their sum fits 32 bits
+                bool ok = wave_reduce<OpAdd>(W.re - W.rs) <= 65536u;
+                uint32_t ntot = 0;
+                if (ok) {
+                    uint32_t nt = 0;
+                    ok = !fill_pool(P, W, A.m.T, A.m.o, nt);
+                    ntot = wave_reduce<OpAdd>(nt);
+                    ok = ok && (unsigned long long)ntot * (unsigned long long)A.m.qmax <= 0xfffffffeull;
+                }
+                if (!ok) {
+                    rec.set_mode(x, PIX_LEFT);
+                } else {
+                    Peaks pk;
+                    pk.clear();
+                    if (ntot > 0 || A.p.n_min < 1) dense_search(P, ntot, pk);
+                    rec.set(x, pk, G, v0, e0, e1, hfull);
+                }
+            }
         }
-    const bool keep = lane < npk && (den > 0 ? (nwk * den > num * w) : (nwk > 0)) && hk > 0.0;
-    const int kt = keep ? tk : 0x7fffffff;
-    const uint32_t kept = (uint32_t)__ballot(keep) & ((1u << KM) - 1u);
-    int rank = 0;
-#pragma unroll
-    for (int j = 0; j < KM; ++j) rank += __builtin_amdgcn_readlane(kt, j) < kt ? 1 : 0;
-    int nkeep = __builtin_popcount(kept);
-    if (nkeep > p.k_max) nkeep = p.k_max;
-    if (keep && rank < nkeep) {
-        const double excess = den > 0 ? (double)nwk - (double)num * (double)w / (double)den : (double)nwk;
-        s.t[rank * S + pix] = (double)kt;
-        s.r[rank * S + pix] = (float)(excess / ((double)G * hk));
+        q.next(init_args().sh);
     }
-    if (lane != 0) return;
-    s.cnt[pix] = (uint8_t)nkeep;
-    const double bown = den > 0 ? (double)num / (double)den : 0.0;
-    const double b0 = bown / (double)G;
-    s.b[pix] = (float)(b0 > p.b_min ? b0 : p.b_min);
+    rec.finish(first);
 }
 
-// QL: the IRF weight tables are staged in LDS (they fit INIT_QLDS ints).
-// wide: list of pixels left for k_init_wide (segment counters first), or null.
-template <bool QL>
-__global__ __launch_bounds__(64 * INIT_WAVES, 7) void k_init(DevModel m, DevParams p, Shape sh,
-                                                          const uint32_t* __restrict__ off,
-                                                          const uint32_t* __restrict__ ent,
-                                                          const float* __restrict__ gain, DevState s,
-                                                          uint32_t* wide)
+// The pixels k_init left (args.all: every pixel of the launch), a wavefront
+// looking through args.ppw <= 64 consecutive pixels: pools with over 127
+// photons in a bin from two planes of bytes (args.wide: they fit), the rest
+// from the lists.
+__global__ __launch_bounds__(64 * INIT_WAVES) void k_init_rest(InitArgs args)
 {
-    extern __shared__ unsigned long long smem64[];
-    const int wv = threadIdx.x >> 6;
-    const size_t ww = init_wave_words(m.T, m.L, m.o, p.r_init);
-    int* qs = reinterpret_cast<int*>(smem64 + INIT_WAVES * ww);
-    int* Mz = qs + q_staged_ints(m.L);
-    const int qmax = stage_weights<QL>(m, qs, Mz);
-    const long long pix = (long long)xcd_block(blockIdx.x, gridDim.x) * INIT_WAVES + wv;
-    // whole wavefront (pixels of other IRF classes: their own launch); no workgroup barriers below
-    if (pix >= sh.P || !in_class(m, pix)) return;
-    init_pixel<QL, false>(m, p, sh, off, ent, gain, s, pix, smem64 + (size_t)wv * ww, qs, Mz, qmax, wide);
-}
-
-// The pixels k_init listed (pools of INIT_ELDS to INIT_WIDE_ELDS photons),
-// a wavefront each, strided over a fixed grid.
-__global__ __launch_bounds__(64 * INIT_WAVES) void k_init_wide(DevModel m, DevParams p, Shape sh,
-                                                               const uint32_t* __restrict__ off,
-                                                               const uint32_t* __restrict__ ent,
-                                                               const float* __restrict__ gain, DevState s,
-                                                               const uint32_t* __restrict__ wide)
-{
-    extern __shared__ unsigned long long smem64[];
-    // listed pixel k lies in the segment whose inclusive count prefix (lane
-    // s: segment s) first exceeds k
-    const int lane = threadIdx.x & 63;
-    const uint32_t cs = wide[lane * INIT_LIST_STRIDE];
-    const uint32_t incl = wave_incl_scan(cs);
-    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-    if ((size_t)blockIdx.x * INIT_WAVES >= n) return;                 // whole workgroup
-    const size_t cap = init_list_cap(sh.P);
-    const int wv = threadIdx.x >> 6;
-    const size_t ww = init_wave_words(m.T, m.L, m.o, p.r_init, INIT_WIDE_ELDS);
-    int* qs = reinterpret_cast<int*>(smem64 + INIT_WAVES * ww);
-    int* Mz = qs + q_staged_ints(m.L);
-    const int qmax = stage_weights<true>(m, qs, Mz);
-    for (uint32_t k = blockIdx.x * INIT_WAVES + wv; k < n; k += gridDim.x * INIT_WAVES) {
-        const int sg = __popcll(__builtin_amdgcn_ballot_w64(incl <= k));
-        const uint32_t at = k - (uint32_t)__builtin_amdgcn_readlane((int)(incl - cs), sg);
-        init_pixel<true, true>(m, p, sh, off, ent, gain, s, (long long)wide[INIT_LIST_HDR + sg * cap + at],
-                               smem64 + (size_t)wv * ww, qs, Mz, qmax, nullptr);
+    extern __shared__ v4i smem[];
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int chunk = args.ppw;
+    const long long first = ((long long)blockIdx.x * nw + wv) * chunk;
+    bool mine = lane < chunk && first + lane < args.sh.P && in_class(args.m, first + lane);
+    if (mine) mine = args.all || args.s.cnt[first + lane] == INIT_LEFT;
+    unsigned long long todo = __ballot(mine);
+    if (!todo) return;                      // (no workgroup barriers here)
+    const InitPool<0, true> P = init_pool<0, true>(args.m, smem + (size_t)wv * (args.area / 16));
+    const double hfull = window_mass(args.m);
+    for (; todo; todo &= todo - 1ull) {
+        const InitArgs& A = init_args();
+        const DevModel& m = A.m;
+        InitPixel q;
+        q.at((uint32_t)(first + __builtin_ctzll(todo)), A.sh);
+        const PoolRows W = q.rows(A.sh, A.p.r_init, A.off, A.ent);
+        const uint32_t e0 = A.off[q.pix], e1 = A.off[q.pix + 1];
+        const float G = gain_at(A.gain, q.pix);
+        InitRecords rec;
+        rec.clear();
+        if (!(G > 0.f)) {
+            rec.set_mode(0, PIX_DEAD);
+        } else {
+            Peaks pk;
+            pk.clear();
+            bool dense = args.wide && wave_reduce<OpAdd>(W.re - W.rs) <= 65536u;
+            if (dense) {
+                uint32_t nt = 0;
+                dense = !fill_planes(P, W, A.off, q.pix, A.sh.cols, q.i, q.j, A.sh.rows, m.T, m.o, nt);
+                const uint32_t ntot = wave_reduce<OpAdd>(nt);
+                dense = dense && ntot <= 1u << 24;       // the products' sums stay below 2^31
+                if (dense) dense_search(P, ntot, pk);
+            }
+            if (!dense) {
+                const long long fr = q.pix / ((long long)A.sh.rows * A.sh.cols);
+                lists_search(m, A.p, A.sh, A.off, A.ent, fr, q.i, q.j, reinterpret_cast<unsigned long long*>(P.Z), pk);
+            }
+            wave_sync();
+            rec.set(0, pk, G, e0 + lane < e1 ? A.ent[e0 + lane] : 0u, e0, e1, hfull);
+        }
+        rec.finish(q.pix);
     }
 }
-
-__global__ void k_init_reset(uint32_t* wide)
-{
-    if (threadIdx.x < INIT_LIST_SEGS) wide[threadIdx.x * INIT_LIST_STRIDE] = 0u;
-}
-
-// Words of the list for P pixels.
-size_t init_list_words(long long P) { return INIT_LIST_HDR + INIT_LIST_SEGS * init_list_cap(P); }
 
 // Initial normals (reading): weighted least-squares plane Z = a + c1 X + c2 Y
 // over the APSS neighbourhood in FP64, local coordinates; n = (c1, c2, -1)/|.|,
@@ -1125,34 +1248,57 @@ __global__ __launch_bounds__(256) void k_init_normals(DevParams p, Shape sh, Dev
     }
 }
 
-// LDS bytes of one init workgroup (wide: of the wide kernel): the
-// wavefronts' areas and the IRF weights (o: the IRF's origin, 0 <= o < L).
-size_t init_lds_bytes(int T, int L, int o, int r_init, bool wide)
+// Wavefronts per workgroup, as many as 64 KB of LDS hold.
+static int init_waves(size_t area, size_t tables)
 {
-    const size_t nq = q_staged_ints(L);
-    const size_t qwords = nq <= INIT_QLDS ? (nq + q_window_ints(L) + 1) / 2 : 0;
-    return (INIT_WAVES * init_wave_words(T, L, o, r_init, wide ? INIT_WIDE_ELDS : INIT_ELDS) + qwords) *
-           sizeof(unsigned long long);
+    int nw = INIT_WAVES;
+    while (nw > 1 && nw * area + tables > 65536) nw >>= 1;
+    return nw;
+}
+
+// Consecutive pixels per wavefront (at most INIT_PPW_MAX): the workgroup's
+// tables (a few loads and a barrier) and the wavefront's output serve all of
+// them, but a grid needs enough wavefronts to fill the chip (1024 SIMDs with
+// five each).  Measured with 4, 8 and 16 pixels: 2.48, 2.47 and 2.49 ms at 636 k
+// pixels, 0.183, 0.192 and 0.213 ms at 65 k (an earlier state of the kernel).
+static int pixels_per_wave(long long P) { return P >= 131072 ? 8 : P >= 32768 ? 4 : P >= 16384 ? 2 : 1; }
+static_assert(INIT_PPW_MAX >= 8, "a wavefront's pixels have a lane per peak");
+
+template <int KS>
+static hipError_t launch_ks(InitArgs a, hipStream_t st)
+{
+    const size_t tables = (size_t)2 * KS * 64 * 16;
+    const int nw = init_waves(a.area, tables);
+    a.ppw = pixels_per_wave(a.sh.P);
+    const long long per = (long long)nw * a.ppw;
+    hipLaunchKernelGGL(k_init<KS>, dim3((unsigned)((a.sh.P + per - 1) / per)), dim3(64 * nw), nw * a.area + tables, st,
+                       a);
+    return hipGetLastError();
 }
 
 hipError_t launch_init(const DevModel& m, const DevParams& p, const Shape& sh, const uint32_t* off,
-                       const uint32_t* ent, const float* gain, DevState s, uint32_t* wide, hipStream_t st)
+                       const uint32_t* ent, const float* gain, DevState s, hipStream_t st)
 {
     if (sh.P == 0) return hipSuccess;
-    const size_t lds = init_lds_bytes(m.T, m.L, m.o, p.r_init, false);
-    const unsigned nblk = (unsigned)((sh.P + INIT_WAVES - 1) / INIT_WAVES);
-    if (q_staged_ints(m.L) > (size_t)INIT_QLDS) {
-        hipLaunchKernelGGL(k_init<false>, dim3(nblk), dim3(64 * INIT_WAVES), lds, st, m, p, sh, off, ent, gain, s,
-                           nullptr);
-        return hipGetLastError();
+    InitArgs a{m, p, sh, off, ent, gain, s, 1, (int)init_area(m.T, m.qa ? m.ks : 0, p.r_init, 1), m.qa ? 0 : 1, 0};
+    hipError_t e = hipSuccess;
+    switch (!m.qa ? -1 : m.T > 1024 * PICK_REGS ? 0 : m.ks) {
+    case -1: break;
+    case 1: e = launch_ks<1>(a, st); break;
+    case 2: e = launch_ks<2>(a, st); break;
+    case 3: e = launch_ks<3>(a, st); break;
+    case 4: e = launch_ks<4>(a, st); break;
+    default: e = launch_ks<0>(a, st); break;
     }
-    const size_t wlds = init_lds_bytes(m.T, m.L, m.o, p.r_init, true);
-    if (wlds > 65536 || sh.P >= (1ll << 32)) wide = nullptr;
-    if (wide) hipLaunchKernelGGL(k_init_reset, dim3(1), dim3(64), 0, st, wide);
-    hipLaunchKernelGGL(k_init<true>, dim3(nblk), dim3(64 * INIT_WAVES), lds, st, m, p, sh, off, ent, gain, s, wide);
-    if (wide)
-        hipLaunchKernelGGL(k_init_wide, dim3(std::min(nblk, INIT_WIDE_GRID)), dim3(64 * INIT_WAVES), wlds, st, m, p,
-                           sh, off, ent, gain, s, wide);
+    if (e != hipSuccess) return e;
+    // the pixels left over: enough wavefronts to fill the chip if that is all
+    // of them, at most 64 pixels each (one count per lane)
+    a.wide = m.qa && init_area(m.T, m.ks, p.r_init, 2) <= 65536;
+    a.area = (int)init_area(m.T, a.wide ? m.ks : 0, p.r_init, 2);
+    const int nw = init_waves(a.area, 0);
+    a.ppw = (int)std::max(1ll, std::min(64ll, sh.P / 8192));
+    const long long per = (long long)nw * a.ppw;
+    hipLaunchKernelGGL(k_init_rest, dim3((unsigned)((sh.P + per - 1) / per)), dim3(64 * nw), nw * a.area, st, a);
     return hipGetLastError();
 }
 

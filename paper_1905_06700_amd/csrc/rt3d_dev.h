@@ -16,6 +16,12 @@ struct DevModel {
     const float4*  cr;    // Catmull-Rom segment k-1 (samples k..k+1): cubic coefficients (c0, c1, c2, c3)
     const int32_t* q;     // log-matched-filter weights, 16 fractional bits
     const int32_t* qst;   // range-maximum table of q: qst[l * L + k] = max q[k .. k + 2^l - 1]
+    // q as digits for the integer matrix cores, q = 2^qshift qc - 64 e1 - e0:
+    // [qc, e1, e0][ks steps of 64 lags][64 lanes][16 bytes], lane i + 16 g,
+    // byte b of step s holding row i's value of lag 64 s + 16 g + b - i
+    // (nullptr: the dense search does not apply); qmax the largest weight
+    const int8_t*  qa;
+    int   ks, qshift, qmax;
     const double*  hbar;  // normalised IRF samples
     int   T, L, o;
     int   wl, wr;         // peak window half widths
@@ -610,11 +616,8 @@ hipError_t launch_compact_events(const uint32_t* pix, const uint16_t* bin, uint6
                                  uint32_t* evoff, uint32_t* scratch, uint32_t* off, uint32_t* ent, uint64_t cap,
                                  uint32_t* counts, uint32_t* partial, int32_t* err, hipStream_t st);
 
-// wide: P + 1 words of workspace (a count and a pixel list) for pools too
-// large for the first kernel's registers, or null (they take the HBM path).
 hipError_t launch_init(const DevModel& m, const DevParams& p, const Shape& sh, const uint32_t* off,
-                       const uint32_t* ent, const float* gain, DevState s, uint32_t* wide,
-                       hipStream_t st);
+                       const uint32_t* ent, const float* gain, DevState s, hipStream_t st);
 hipError_t launch_init_normals(const DevParams& p, const Shape& sh, DevState s, hipStream_t st);
 
 hipError_t launch_depth_step(const DevModel& m, const DevParams& p, const Shape& sh,

@@ -15,10 +15,9 @@
 
 #include "rt3d_dev.h"
 #include "rt3d_cnn.h"
+#include "rt3d_init.h"
 
 namespace rt3d {
-size_t init_lds_bytes(int T, int L, int o, int r_init, bool wide = false);
-size_t init_list_words(long long P);
 }
 
 using namespace rt3d;
@@ -38,6 +37,8 @@ struct IrfTables {
     double* d_stab = nullptr;
     int32_t* d_q = nullptr;
     int32_t* d_qst = nullptr;
+    int8_t* d_qa = nullptr;            // q as matrix-core digits (nullptr: the dense search does not apply)
+    int qshift = 0, qmax = 0;
     double* d_hbar = nullptr;
 };
 
@@ -94,7 +95,6 @@ struct Workspace {
     uint32_t* stage;
     uint32_t* cls_list;                // per-class pixel lists (per-pixel IRFs)
     uint32_t* cls_meta;
-    uint32_t* wide;                    // the init's list of pixels with large pools (segment counters first)
     DevState A, B;
     float* btmp;
     CnnBuffers cnn;
@@ -123,7 +123,6 @@ Workspace carve(uint8_t* base, long long P, long long Ps, uint64_t E, bool with_
     w.stage = (uint32_t*)take(sizeof(uint32_t) * CP_STAGE * std::max<long long>(P, 1));
     w.cls_list = (uint32_t*)take(sizeof(uint32_t) * std::max<long long>(P, 1));
     w.cls_meta = (uint32_t*)take(sizeof(uint32_t) * CLASS_META);
-    w.wide = (uint32_t*)take(sizeof(uint32_t) * init_list_words(P));
     for (DevState* s : {&w.A, &w.B}) {
         s->t = (double*)take(sizeof(double) * KM * Ps);
         s->r = (float*)take(sizeof(float) * KM * Ps);
@@ -168,7 +167,7 @@ rt3d_status check_irf(const double* irf, uint32_t irf_len, int32_t irf_origin, i
     if (!(sum > 0.0)) return RT3D_E_INVALID;
     if (irf_origin >= (int32_t)irf_len) return RT3D_E_INVALID;
     // the origin is not known before the IRF is normalised: its largest value
-    if (init_lds_bytes(T, (int)irf_len, (int)irf_len - 1, p->r_init) > 65536) return RT3D_E_UNSUPPORTED;
+    if (!init_admits(T, (int)irf_len, p->r_init)) return RT3D_E_UNSUPPORTED;
     return RT3D_OK;
 }
 
@@ -343,7 +342,31 @@ rt3d_status build_irf(const double* irf, uint32_t irf_len, int32_t irf_origin, i
             const int b = k2 < L ? qst[(size_t)(l - 1) * L + k2] : a;
             qst[(size_t)l * L + k] = std::max(a, b);
         }
+    // the weights as digits for the integer matrix cores (DevModel::qa): qc =
+    // ceil(q / 2^qshift) up to 127, the rest e = 2^qshift qc - q in two
+    // digits, the upper one up to 127
+    t.qmax = *std::max_element(q.begin(), q.end());
+    t.qshift = 0;
+    while (t.qshift < 30 && t.qmax > 127ll << t.qshift) ++t.qshift;
+    std::vector<int8_t> qa;
+    if (L <= INIT_L_MAX && T <= INIT_T_MAX && t.qshift <= 7 + INIT_E_BITS) {
+        const int ks = init_ks(L);
+        qa.assign((size_t)3 * ks * 1024, 0);
+        for (int s = 0; s < ks; ++s)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int b = 0; b < 16; ++b) {
+                    const int lag = 64 * s + 16 * (lane >> 4) + b - (lane & 15);
+                    if (lag < 0 || lag >= L) continue;
+                    const int qc = (q[lag] + (1 << t.qshift) - 1) >> t.qshift, rest = (qc << t.qshift) - q[lag];
+                    const size_t at = (size_t)s * 1024 + lane * 16 + b, plane = (size_t)ks * 1024;
+                    qa[at] = (int8_t)qc;
+                    qa[plane + at] = (int8_t)(rest >> INIT_E_BITS);
+                    qa[2 * plane + at] = (int8_t)(rest & ((1 << INIT_E_BITS) - 1));
+                }
+    }
     hipError_t e = hipMalloc(&t.d_cr, sizeof(float4) * cr.size());
+    if (e == hipSuccess && !qa.empty()) e = hipMalloc(&t.d_qa, qa.size());
+    if (e == hipSuccess && !qa.empty()) e = hipMemcpy(t.d_qa, qa.data(), qa.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&t.d_q, sizeof(int32_t) * q.size());
     if (e == hipSuccess) e = hipMalloc(&t.d_qst, sizeof(int32_t) * qst.size());
     if (e == hipSuccess) e = hipMalloc(&t.d_hbar, sizeof(double) * L);
@@ -359,12 +382,13 @@ rt3d_status build_irf(const double* irf, uint32_t irf_len, int32_t irf_origin, i
 
 void free_irf(IrfTables& t)
 {
-    for (void* ptr : {(void*)t.d_cr, (void*)t.d_stab, (void*)t.d_q, (void*)t.d_qst, (void*)t.d_hbar})
+    for (void* ptr : {(void*)t.d_cr, (void*)t.d_stab, (void*)t.d_q, (void*)t.d_qst, (void*)t.d_qa, (void*)t.d_hbar})
         if (ptr) (void)hipFree(ptr);
     t.d_cr = nullptr;
     t.d_stab = nullptr;
     t.d_q = nullptr;
     t.d_qst = nullptr;
+    t.d_qa = nullptr;
     t.d_hbar = nullptr;
 }
 
@@ -421,6 +445,10 @@ DevModel dev_model(const rt3d_ctx* c, int k = 0, const uint8_t* cls = nullptr, c
     m.cr = t.d_cr;
     m.q = t.d_q;
     m.qst = t.d_qst;
+    m.qa = t.d_qa;
+    m.ks = init_ks(t.L);
+    m.qshift = t.qshift;
+    m.qmax = t.qmax;
     m.hbar = t.d_hbar;
     m.T = c->T;
     m.L = t.L;
@@ -751,12 +779,12 @@ rt3d_status iterate_sr(rt3d_ctx* c, const Shape& lid, const uint32_t* off, const
 // Initialisation under super-resolution: the lidar-grid initialisation into
 // B (slot stride lid.P), spread over the point grid into A, normals there.
 rt3d_status init_sr(rt3d_ctx* c, const Shape& lid, const uint32_t* off, const uint32_t* ent, const float* gain,
-                    DevState A, DevState B, uint32_t* wide, hipStream_t st)
+                    DevState A, DevState B, hipStream_t st)
 {
     const DevModel m = dev_model(c);
     const DevParams p = dev_params(c);
     const Shape fsh = point_grid(lid, c->p.sr);
-    RT3D_LAUNCH(c, RT3D_KERNEL_INIT, st, launch_init(m, p, lid, off, ent, gain, B, wide, st));
+    RT3D_LAUNCH(c, RT3D_KERNEL_INIT, st, launch_init(m, p, lid, off, ent, gain, B, st));
     RT3D_HIP(c, launch_sr_expand(lid, c->p.sr, fsh.P, B, A, st));
     RT3D_LAUNCH(c, RT3D_KERNEL_NORMALS, st, launch_init_normals(p, fsh, A, st));
     return RT3D_OK;
@@ -1060,7 +1088,7 @@ rt3d_status rt3d_reconstruct(rt3d_ctx* c, const rt3d_input* in, rt3d_output* out
         if (layout != prev_layout)
             return fail(c, RT3D_E_STATE, "warm start: no final state of a batch of these frames in the workspace");
     } else if (c->p.sr > 1) {
-        s = init_sr(c, sh, off, ent, in->gain, w.A, w.B, w.wide, st);
+        s = init_sr(c, sh, off, ent, in->gain, w.A, w.B, st);
         if (s != RT3D_OK) return s;
     } else {
         for (const Group& g : groups)
@@ -1068,7 +1096,7 @@ rt3d_status rt3d_reconstruct(rt3d_ctx* c, const rt3d_input* in, rt3d_output* out
                 RT3D_LAUNCH(c, RT3D_KERNEL_INIT, st,
                             launch_init(dev_model(c, k, cls ? cls + g.base : nullptr), dev_params(c, k), g.sh,
                                         off + g.base, ent, in->gain ? in->gain + g.base : nullptr,
-                                        state_at(w.A, g.base), w.wide, st));
+                                        state_at(w.A, g.base), st));
         for (const Group& g : groups)
             RT3D_LAUNCH(c, RT3D_KERNEL_NORMALS, st, launch_init_normals(p, g.sh, state_at(w.A, g.base), st));
     }
@@ -1344,7 +1372,7 @@ static rt3d_status debug_step_sr(rt3d_ctx* c, int32_t step, const uint32_t* off,
     }
     switch (step) {
     case RT3D_STEP_INIT:
-        return init_sr(c, lid, off, ent, gain, O, w.B, w.wide, st);
+        return init_sr(c, lid, off, ent, gain, O, w.B, st);
     case RT3D_STEP_APSS:
         RT3D_HIP(c, launch_apss(m, p, fsh, dev_state(in), O, -1, st));
         return RT3D_OK;
@@ -1404,12 +1432,8 @@ rt3d_status rt3d_debug_step(rt3d_ctx* c, int32_t step, const uint32_t* off, cons
     }
     switch (step) {
     case RT3D_STEP_INIT: {
-        // the pixel list of large pools lives in the bound workspace; without
-        // one that covers the frames those pools take the HBM path
-        uint32_t* wide = nullptr;
-        if (c->ws && c->ws_P >= sh.P) wide = carve_ctx(c, c->ws, c->ws_P, c->ws_E, c->ws_rows, c->ws_cols).wide;
         for (int k = 0; k < nc; ++k)
-            RT3D_HIP(c, launch_init(dev_model(c, k, cls), dev_params(c, k), sh, off, ent, gain, O, wide, st));
+            RT3D_HIP(c, launch_init(dev_model(c, k, cls), dev_params(c, k), sh, off, ent, gain, O, st));
         RT3D_HIP(c, launch_init_normals(p, sh, O, st));
         return RT3D_OK;
     }
