@@ -9,243 +9,39 @@
 // with four points keep APSS.
 //
 // Every convolution is an implicit GEMM on the matrix cores:
-// v_mfma_f32_16x16x16_f16 (FP16 inputs, FP32 accumulation).  Activations are
-// FP16 NHWC with 16 or 32 channels (64 B per pixel at 32), weights FP16.
+// v_mfma_f32_16x16x32_f16 (FP16 inputs, FP32 accumulation).  Activations are
+// FP16 NHWC with 16 or 32 channels, weights FP16.
 //   forward:         Y[p][co]   = b[co] + sum_{tap, ci} X[p + tap][ci] W[tap][ci][co]
 //   backward data:   dX[p][ci]  = sum_{tap, co} dY[p + tap][co] W'[tap][co][ci],
 //                    W' the tap-flipped transpose, gated by the ReLU of X
 //   backward weight: dW[tap][ci][co] = sum_p X[p + tap][ci] dY[p][co],
 //                    per-workgroup partials reduced in a fixed order
-// A forward / backward-data workgroup owns 64 consecutive pixels of CR = 4
-// image rows (one row per wavefront, four 16-pixel MFMA row tiles each) and
-// stages the CR + 2 halo rows and the layer's weights in LDS, rows padded so
-// that a fragment read meets no bank conflict: every weight fragment read
-// from LDS feeds four row tiles, and the staged weights serve 256 pixels.
-// The weight-gradient workgroup owns 64 pixels of one row at a time.
+// Forward and backward data each run as one kernel on 16 x 16 tiles, the
+// intermediate maps of a tile (grown by the receptive field of the layers that
+// follow) in LDS; a training step stores the hidden activations and gradient
+// maps for the weight gradients, which are one launch over all layers, and one
+// more kernel reduces them and updates the weights.
 #include "rt3d_dev.h"
 #include "rt3d_cnn.h"
 
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 namespace rt3d {
 
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
-constexpr int CT = 64;   // output pixels per workgroup row (one row segment)
-constexpr int CR = 4;    // image rows per forward / backward-data workgroup (one per wavefront)
-// LDS row padding (halves) of the forward / backward-data halo pixels and
-// weight rows: strides of 4 mod 32 words put the 16 lanes of a fragment read
-// on distinct banks
-constexpr int CPAD = 4;
-
-__device__ __forceinline__ float4_t mfma16(half4_t a, half4_t b, float4_t c)
+__device__ __forceinline__ float4_t mfma32(half8_t a, half8_t b, float4_t c)
 {
-    return __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-// Stages rows y-1..y+NR-2, columns x0-1..x0+CT of one frame (zero outside
-// the image) into LDS as [NR][CT+2][C + PAD] halves.
-template <int C, int NR = 3, int PAD = 0>
-__device__ __forceinline__ void stage_halo(const __half* __restrict__ X, int F, int H, int W, int f, int y,
-                                           int x0, __half* __restrict__ halo)
+__device__ __forceinline__ half4_t to_half4(float4_t v)
 {
-    constexpr int VPP = C / 8;                       // 16-byte vectors per pixel
-    const int nvec = NR * (CT + 2) * VPP;
-    for (int v = threadIdx.x; v < nvec; v += blockDim.x) {
-        const int c8 = v % VPP;
-        const int px = (v / VPP) % (CT + 2);
-        const int ry = v / (VPP * (CT + 2));
-        const int yy = y + ry - 1, xx = x0 + px - 1;
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-            val = reinterpret_cast<const uint4*>(X + (((long long)f * H + yy) * W + xx) * C)[c8];
-        if (PAD == 0) {
-            reinterpret_cast<uint4*>(halo)[v] = val;
-        } else {   // 8-byte aligned rows
-            uint2* d = reinterpret_cast<uint2*>(halo + (ry * (CT + 2) + px) * (C + PAD) + 8 * c8);
-            d[0] = make_uint2(val.x, val.y);
-            d[1] = make_uint2(val.z, val.w);
-        }
-    }
-    (void)F;
-}
-
-// Forward / backward-data convolution.  Wt: FP16 [COUT][9 * CIN] (k = tap * CIN + ci,
-// tap = ky * 3 + kx).  MODE 0: + bias, ReLU; 1: + bias (last layer); 2: gate by
-// (G > 0) (backward data, G = the layer input's activation), no bias.
-template <int CIN, int COUT, int MODE>
-__global__ __launch_bounds__(64 * CR) void k_conv3x3(const __half* __restrict__ X, const __half* __restrict__ Wt,
-                                                 const float* __restrict__ bias, const __half* __restrict__ Gate,
-                                                 __half* __restrict__ Y, int F, int H, int W)
-{
-    constexpr int K = 9 * CIN;
-    constexpr int NT = COUT / 16;
-    constexpr int MT = CT / 16;                      // row tiles per wavefront
-    constexpr int HS = CIN + CPAD, WS = K + CPAD;    // LDS strides (halves) of a halo pixel, a weight row
-    __shared__ __align__(16) __half halo[(CR + 2) * (CT + 2) * HS];
-    __shared__ __align__(16) __half wsh[COUT * WS];
-    const int segs = (W + CT - 1) / CT;
-    const int bands = (H + CR - 1) / CR;
-    const int seg = blockIdx.x % segs;
-    const int y0 = ((blockIdx.x / segs) % bands) * CR;
-    const int f = blockIdx.x / (segs * bands);
-    const int x0 = seg * CT;
-    stage_halo<CIN, CR + 2, CPAD>(X, F, H, W, f, y0, x0, halo);
-    for (int v = threadIdx.x; v < COUT * K / 8; v += blockDim.x) {
-        const uint4 val = reinterpret_cast<const uint4*>(Wt)[v];
-        const int row = v / (K / 8), c8 = v % (K / 8);
-        uint2* d = reinterpret_cast<uint2*>(wsh + row * WS + 8 * c8);
-        d[0] = make_uint2(val.x, val.y);
-        d[1] = make_uint2(val.z, val.w);
-    }
-    __syncthreads();
-
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;   // wavefront wv: image row y0 + wv
-    const int i = lane & 15, g = lane >> 4;
-    float4_t acc[MT][NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) acc[mt][n] = (float4_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-        const int ky = tap / 3, kx = tap % 3;
-        const __half* arow = halo + (((wv + ky) * (CT + 2)) + i + kx) * HS;
-#pragma unroll
-        for (int cc = 0; cc < CIN / 16; ++cc) {
-            const int k = tap * CIN + cc * 16 + 4 * g;
-            half4_t b[NT];
-#pragma unroll
-            for (int n = 0; n < NT; ++n) b[n] = *reinterpret_cast<const half4_t*>(wsh + (n * 16 + i) * WS + k);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const half4_t a = *reinterpret_cast<const half4_t*>(arow + mt * 16 * HS + cc * 16 + 4 * g);
-#pragma unroll
-                for (int n = 0; n < NT; ++n) acc[mt][n] = mfma16(a, b[n], acc[mt][n]);
-            }
-        }
-    }
-    // D[row = 4 g + r][col = i] of row tile mt: pixel x0 + 16 mt + 4 g + r of row y, channel 16 n + i
-    const int y = y0 + wv;
-    if (y >= H) return;
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-        const int co = n * 16 + i;
-        const float bco = (MODE != 2) ? bias[co] : 0.f;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int x = x0 + mt * 16 + 4 * g + r;
-                if (x >= W) continue;
-                const long long pix = ((long long)f * H + y) * W + x;
-                float v = acc[mt][n][r] + bco;
-                if (MODE == 0) v = fmaxf(v, 0.f);
-                if (MODE == 2 && !(__half2float(Gate[pix * COUT + co]) > 0.f)) v = 0.f;
-                Y[pix * COUT + co] = __float2half(v);
-            }
-    }
-}
-
-// Weight gradient partials: each workgroup reduces its row segment over
-// ROWS_PER_WG consecutive rows (same frame) into part[wg][9 * CIN][COUT] and
-// bias partials bpart[wg][COUT].
-constexpr int WG_ROWS = 8;
-
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_conv3x3_wgrad(const __half* __restrict__ X, const __half* __restrict__ dY,
-                                                       float* __restrict__ part, float* __restrict__ bpart,
-                                                       int F, int H, int W)
-{
-    constexpr int K9 = 9 * CIN;
-    constexpr int MT = K9 / 16;                  // row tiles of (tap, ci)
-    constexpr int NT = COUT / 16;
-    constexpr int TILES = MT * NT;
-    constexpr int TPW = (TILES + 3) / 4;         // tiles per wavefront
-    __shared__ __align__(16) __half halo[3 * (CT + 2) * CIN];
-    __shared__ __align__(16) __half dys[CT * COUT];
-    const int segs = (W + CT - 1) / CT;
-    const int rblocks = (H + WG_ROWS - 1) / WG_ROWS;
-    const int seg = blockIdx.x % segs;
-    const int rb = (blockIdx.x / segs) % rblocks;
-    const int f = blockIdx.x / (segs * rblocks);
-    const int x0 = seg * CT;
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int i = lane & 15, g = lane >> 4;
-    float4_t acc[TPW];
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) acc[t] = (float4_t){0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-    for (int yr = 0; yr < WG_ROWS; ++yr) {
-        const int y = rb * WG_ROWS + yr;
-        if (y >= H) break;
-        __syncthreads();
-        stage_halo<CIN>(X, F, H, W, f, y, x0, halo);
-        for (int v = threadIdx.x; v < CT * COUT / 8; v += blockDim.x) {
-            const int px = v / (COUT / 8), c8 = v % (COUT / 8);
-            const int x = x0 + px;
-            uint4 val = make_uint4(0, 0, 0, 0);
-            if (x < W) val = reinterpret_cast<const uint4*>(dY + (((long long)f * H + y) * W + x) * COUT)[c8];
-            reinterpret_cast<uint4*>(dys)[v] = val;
-        }
-        __syncthreads();
-        if (threadIdx.x < COUT)
-            for (int px = 0; px < CT; ++px) bsum += __half2float(dys[px * COUT + threadIdx.x]);
-        // K dimension: the segment's 64 pixels in 4 steps of 16
-#pragma unroll
-        for (int ks = 0; ks < CT / 16; ++ks) {
-#pragma unroll
-            for (int t = 0; t < TPW; ++t) {
-                const int tile = wv * TPW + t;
-                if (tile >= TILES) continue;
-                const int mt = tile / NT, nt = tile % NT;
-                const int row = mt * 16 + i;                  // (tap, ci) of this lane's A row
-                const int tap = row / CIN, ci = row % CIN;
-                const int ky = tap / 3, kx = tap % 3;
-                half4_t a, b;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int px = ks * 16 + 4 * g + r;        // reduction index = pixel
-                    a[r] = (_Float16)halo[((ky * (CT + 2)) + px + kx) * CIN + ci];
-                    b[r] = (_Float16)dys[px * COUT + nt * 16 + i];
-                }
-                acc[t] = mfma16(a, b, acc[t]);
-            }
-        }
-    }
-    float* out = part + (size_t)blockIdx.x * K9 * COUT;
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-        const int tile = wv * TPW + t;
-        if (tile >= TILES) continue;
-        const int mt = tile / NT, nt = tile % NT;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) out[(mt * 16 + 4 * g + r) * COUT + nt * 16 + i] = acc[t][r];
-    }
-    if (threadIdx.x < COUT) bpart[(size_t)blockIdx.x * COUT + threadIdx.x] = bsum;
-}
-
-// Sums weight-gradient partials over workgroups in a fixed order and writes
-// the FP32 gradient of the flat master-weight layout (scaled by 1/count).
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, const float* __restrict__ bpart,
-                                                      int nwg, int cin_store, int cout_store, int cin, int cout,
-                                                      const float* __restrict__ count, float* __restrict__ grad)
-{
-    const int n_w = 9 * cin * cout;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_w + cout) return;
-    const float inv = 1.f / fmaxf(count[0], 1.f);
-    float s = 0.f;
-    if (idx < n_w) {
-        const int co = idx % cout, ci = (idx / cout) % cin, tap = idx / (cout * cin);
-        const int row = tap * cin_store + ci;
-        for (int wg = 0; wg < nwg; ++wg) s += part[((size_t)wg * 9 * cin_store + row) * cout_store + co];
-    } else {
-        const int co = idx - n_w;
-        for (int wg = 0; wg < nwg; ++wg) s += bpart[(size_t)wg * cout_store + co];
-    }
-    grad[idx] = s * inv;
+    return (half4_t){(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
 }
 
 // Features of the first three slots, FP16 [P][16].
@@ -331,374 +127,754 @@ __global__ __launch_bounds__(PKT * PKT) void k_cnn_pack(Shape sh, DevState s, fl
     reinterpret_cast<uint4*>(x + pix * 16)[1] = o[1];
 }
 
-// Slot k < 3 of a pixel with at most three points moves by sigma_h * y_k.
-__global__ __launch_bounds__(256) void k_cnn_apply(Shape sh, const __half* __restrict__ y, float sigma_h,
-                                                   double tmax, DevState s)
+// Adam on one FP32 master weight.
+__device__ __forceinline__ float adam_step(float* w, float* m, float* v, int idx, float gi, const CnnAdam& o, float c1,
+                                           float c2)
 {
-    const long long S = sh.S;
-    const long long pix = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pix >= sh.P) return;
-    const int c = load_cnt(s.cnt, pix);
-    if (c > 3) return;
-    for (int k = 0; k < c; ++k) {
-        double t = s.t[k * S + pix] + (double)(sigma_h * __half2float(y[pix * 16 + k]));
-        t = t < 0.0 ? 0.0 : (t > tmax ? tmax : t);
-        s.t[k * S + pix] = t;
-    }
-}
-
-// Network outputs of the first three channels as float [3][P].
-__global__ __launch_bounds__(256) void k_cnn_unpack(long long P, const __half* __restrict__ y, float* __restrict__ out)
-{
-    const long long pix = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pix >= P) return;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) out[k * P + pix] = __half2float(y[pix * 16 + k]);
-}
-
-// Training targets: slot k < min(cnt, 3) takes the nearest true depth of its
-// pixel within 3 sigma_h (first surface on ties); truth [S][P], NaN = absent.
-__global__ __launch_bounds__(256) void k_cnn_targets(Shape sh, DevState s, const float* __restrict__ truth, int S,
-                                                     float sigma_h, float* __restrict__ tgt, uint8_t* __restrict__ msk)
-{
-    const long long P = sh.P;
-    const long long pix = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pix >= P) return;
-    const int c = min(load_cnt(s.cnt, pix), 3);
-    for (int k = 0; k < 3; ++k) {
-        float tv = 0.f;
-        uint8_t mv = 0;
-        if (k < c) {
-            const double t = s.t[k * P + pix];
-            double bd = 0.0;
-            int bs = -1;
-            for (int q = 0; q < S; ++q) {
-                const float tr = truth[(long long)q * P + pix];
-                if (!(tr == tr)) continue;               // NaN: no such surface
-                const double d = fabs((double)tr - t);
-                if (bs < 0 || d < bd) {
-                    bs = q;
-                    bd = d;
-                }
-            }
-            if (bs >= 0 && bd <= 3.0 * (double)sigma_h) {
-                tv = fminf(fmaxf((float)(((double)truth[(long long)bs * P + pix] - t) / (double)sigma_h), -8.f), 8.f);
-                mv = 1;
-            }
-        }
-        tgt[k * P + pix] = tv;
-        msk[k * P + pix] = mv;
-    }
-}
-
-// Masked squared error: per-block partial sums, and dY = 2 (y - y*) m in FP16
-// (the gradient of the sum; 1/count is applied to the weight gradients).
-__global__ __launch_bounds__(256) void k_cnn_loss(long long P, const __half* __restrict__ y,
-                                                  const float* __restrict__ tgt, const uint8_t* __restrict__ msk,
-                                                  __half* __restrict__ dy, float* __restrict__ lpart)
-{
-    __shared__ float red[2][256];
-    const long long pix = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    float se = 0.f, n = 0.f;
-    if (pix < P) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            float g = 0.f;
-            if (k < 3 && msk[k * P + pix]) {
-                const float d = __half2float(y[pix * 16 + k]) - tgt[k * P + pix];
-                se += d * d;
-                n += 1.f;
-                g = 2.f * d;
-            }
-            dy[pix * 16 + k] = __float2half(g);
-        }
-    }
-    red[0][threadIdx.x] = se;
-    red[1][threadIdx.x] = n;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if (threadIdx.x < w) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + w];
-            red[1][threadIdx.x] += red[1][threadIdx.x + w];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        lpart[2 * blockIdx.x] = red[0][0];
-        lpart[2 * blockIdx.x + 1] = red[1][0];
-    }
-}
-
-__global__ __launch_bounds__(64) void k_cnn_loss_final(const float* __restrict__ lpart, int nb, float* __restrict__ out)
-{
-    if (threadIdx.x != 0) return;
-    double se = 0.0, n = 0.0;
-    for (int b = 0; b < nb; ++b) {
-        se += lpart[2 * b];
-        n += lpart[2 * b + 1];
-    }
-    out[0] = (float)(se / (n > 1.0 ? n : 1.0));
-    out[1] = (float)n;
-}
-
-// Adam on the FP32 master weights.
-__global__ __launch_bounds__(256) void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                                              const float* __restrict__ g, int n, float lr, float b1, float b2,
-                                              float eps, float c1, float c2)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n) return;
-    const float gi = g[idx];
-    const float mi = b1 * m[idx] + (1.f - b1) * gi;
-    const float vi = b2 * v[idx] + (1.f - b2) * gi * gi;
+    const float mi = o.beta1 * m[idx] + (1.f - o.beta1) * gi;
+    const float vi = o.beta2 * v[idx] + (1.f - o.beta2) * gi * gi;
     m[idx] = mi;
     v[idx] = vi;
-    w[idx] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    const float wn = w[idx] - o.lr * (mi / c1) / (sqrtf(vi / c2) + o.eps);
+    w[idx] = wn;
+    return wn;
 }
 
-// FP16 kernel layouts from the FP32 master weights of one layer (flat
-// [3][3][cin][cout] then bias[cout]): forward Wt[co][tap * CIS + ci] and
-// backward-data Wb[ci][tap' * COS + co] with tap' = 8 - tap; padded
-// channels are zero.
-__global__ __launch_bounds__(256) void k_cnn_prepare(const float* __restrict__ mw, int cin, int cout, int cis, int cos_,
-                                                     __half* __restrict__ wt, __half* __restrict__ wb,
-                                                     float* __restrict__ bias)
+// The FP16 kernel layouts of master weight idx (flat: per layer [3][3][cin]
+// [cout], then bias[cout]) with value v: forward wt[co][tap cis + ci];
+// backward data wb[ci][tap' cos + co], tap' = 8 - tap, of layers 1 and 2, and
+// wb[ci][4 tap' + co] (rows of 64) of layer 3, whose output gradient has four
+// stored channels.  The padding (zero) is the allocation's.
+__device__ __forceinline__ void store_weight(const CnnWeights& W, int idx, float v)
+{
+    int l = 0;
+#pragma unroll
+    for (int k = 1; k < CNN_LAYERS; ++k) l = idx >= CNN_OFF[k] ? k : l;
+    const int off = l == 0 ? CNN_OFF[0] : l == 1 ? CNN_OFF[1] : l == 2 ? CNN_OFF[2] : CNN_OFF[3];
+    const int cin = l == 0 ? 16 : 32, cout = l == 3 ? 3 : 32;
+    const int p = idx - off;
+    __half* wt = l == 0 ? W.wt[0] : l == 1 ? W.wt[1] : l == 2 ? W.wt[2] : W.wt[3];
+    float* bias = l == 0 ? W.bias[0] : l == 1 ? W.bias[1] : l == 2 ? W.bias[2] : W.bias[3];
+    if (p >= 9 * cin * cout) {
+        bias[p - 9 * cin * cout] = v;
+        return;
+    }
+    const int co = p % cout, row = p / cout, ci = row % cin, tap = row / cin;
+    const __half h = __float2half(v);
+    wt[co * 9 * cin + row] = h;
+    if (l == 3) W.wb[3][ci * 64 + (8 - tap) * 4 + co] = h;
+    else if (l > 0) (l == 1 ? W.wb[1] : W.wb[2])[ci * 288 + (8 - tap) * 32 + co] = h;
+}
+
+__global__ __launch_bounds__(256) void k_cnn_prepare(CnnWeights W)
 {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nf = cos_ * 9 * cis;
-    if (idx < nf) {
-        const int co = idx / (9 * cis), k = idx % (9 * cis), tap = k / cis, ci = k % cis;
-        const float v = (co < cout && ci < cin) ? mw[(tap * cin + ci) * cout + co] : 0.f;
-        wt[idx] = __float2half(v);
-        // the same weight in the backward-data layout
-        if (wb) wb[ci * 9 * cos_ + (8 - tap) * cos_ + co] = __float2half(v);
-    }
-    if (idx < cos_) bias[idx] = idx < cout ? mw[9 * cin * cout + idx] : 0.f;
+    if (idx < CNN_PARAMS) store_weight(W, idx, W.master[idx]);
 }
 
 // ---------------------------------------------------------------------------
-// Fused inference: the four convolutions of one FT x FT output tile in one
-// workgroup, every intermediate activation kept in LDS (FP16, the rounding
-// the per-layer kernels apply when they store it).  Layer l computes its
-// output over the tile grown by 4 - l pixels on every side (the receptive
-// field of the layers after it); outputs at positions outside the image are
-// set to zero, which is the next layer's zero padding.  Matrix cores:
-// v_mfma_f32_16x16x32_f16 (lane i + 16 g holds row i, k = 8 g .. 8 g + 7 of A
-// and column i, the same k of B; D rows 4 g .. 4 g + 3 of column i).  The
-// B operand (the layer's weights) stays in registers for the whole layer; A
-// rows are output pixels, gathered from LDS per lane (one 16-byte chunk of 8
-// channels of the input pixel under the tap).
+// Forward and backward data, fused over the layers: one FT x FT output tile in
+// one workgroup of eight wavefronts, every intermediate map kept in LDS as
+// FP16 (the rounding of a stored activation).  Layer l computes its output
+// over the tile grown by the receptive field of the layers after it; outputs
+// at positions outside the image are set to zero, which is the next layer's
+// zero padding.  The weights are the matrix product's A operand (rows: output
+// channels; lane i + 16 g holds row i, k = 8 g .. 8 g + 7) and stay in
+// registers for the whole layer; B's columns are 16 pixels, gathered from LDS
+// per lane (16-byte chunks of 8 channels of the pixel under the tap), so that
+// a lane ends with four consecutive channels (4 g .. 4 g + 3) of pixel i: one
+// 8-byte store.  262 k pixels' forward pass: 37.0 us, 65 us with the pixels as
+// rows, two-byte LDS stores and a swizzled layout (its matrix products take 9
+// us, its LDS reads about as long); bound by the layers' serial chains at two
+// wavefronts per SIMD (four of 128 registers, with spilled or single tiles in
+// flight: 45 to 63 us).  A training step's forward pass on 131 k pixels: 32 us,
+// backward data 19 us (47 and 46 us as a launch per layer).
 constexpr int FT = 16;                   // output tile side
 constexpr int FR0 = FT + 8;              // side of the staged input features (4-pixel halo)
+constexpr int FW = 4;                    // wavefronts
+constexpr int FU = 2;                    // 16-pixel tiles a wavefront works on at once
+constexpr int FA = 3;                    // chunks read ahead of their products
 
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ float4_t mfma32(half8_t a, half8_t b, float4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-
-// LDS offset (halves) of 16-byte chunk q of pixel p in a region of C-channel
-// pixels, the chunks of a pixel permuted by its index so that the same chunk
-// of 8 consecutive pixels lies in 8 distinct bank groups.
+// Halves from one pixel to the next in LDS: padded by 16 bytes, so that the
+// same 16-byte chunk of 8 consecutive pixels lies in 8 distinct bank groups
+// and every tap is a constant offset (an instruction's immediate).
 template <int C>
-__device__ __forceinline__ int chunk_at(int p, int q)
-{
-    if (C == 32) return p * 32 + 8 * (q ^ ((p >> 1) & 3));
-    return p * 16 + 8 * (q ^ ((p >> 2) & 1));
-}
+constexpr int px_stride() { return C == 4 ? 4 : C + 8; }
 
-// One layer over the RO x RO output region whose input region (RO + 2 wide)
-// sits in `in`.  NT output tiles of 16 channels; LAST: bias only, the FT x FT
-// result goes to y (FP16 [P][16]); else bias, ReLU, zero outside the image,
-// into `out` (32 channels).  (gy0, gx0): image position of the output
-// region's first pixel.
-template <int CIN, int NT, bool LAST>
-__device__ __forceinline__ void fused_layer(const __half* __restrict__ in, __half* __restrict__ out, int RO,
-                                            const __half* __restrict__ Wt, const float* __restrict__ bias, int gy0,
-                                            int gx0, int H, int W, long long fbase, __half* __restrict__ y)
-{
-    constexpr int K = 9 * CIN;
-    constexpr int KC = (K + 31) / 32;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int i = lane & 15, g = lane >> 4;
-    half8_t wf[KC][NT];
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc)
+// The tile's place.
+struct TilePos {
+    int Y0, X0, H, W;
+    long long fbase;      // first pixel of the frame
+
+    __device__ __forceinline__ TilePos(int tile, int H_, int W_) : H(H_), W(W_)
+    {
+        const int tx_n = (W + FT - 1) / FT, ty_n = (H + FT - 1) / FT;
+        const int f = tile / (tx_n * ty_n), tr = tile % (tx_n * ty_n);
+        Y0 = (tr / tx_n) * FT;
+        X0 = (tr % tx_n) * FT;
+        fbase = (long long)f * H * W;
+    }
+};
+
+// A layer's weights [16 NT][K] as A operands, and its bias (nullptr: zero),
+// loaded where this is written (the pointer is one the compiler cannot see
+// through: all layers' weights together do not fit the registers; loading them
+// a layer ahead cost more registers than the wait, 42.5 against 37.0 us).
+template <int CIN, int NT>
+struct LayerWeights {
+    static constexpr int K = CIN == 4 ? 64 : 9 * CIN;      // weights per output channel, stored
+    static constexpr int KC = (K + 31) / 32;
+    half8_t w[KC][NT];
+    float4_t b[NT];
+
+    __device__ __forceinline__ LayerWeights(const __half* src, const float* bias)
+    {
+        auto Wt = (const __attribute__((address_space(1))) _Float16*)src;
+        asm volatile("" : "+s"(Wt));
+        const int i = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
-            const int k0 = kc * 32 + 8 * g;
-            half8_t v = {};
-            if (k0 < K) v = *reinterpret_cast<const half8_t*>(Wt + (n * 16 + i) * K + k0);
-            wf[kc][n] = v;
-        }
-    float bco[NT];
+            b[n] = (float4_t){0.f, 0.f, 0.f, 0.f};
+            if (bias) b[n] = *reinterpret_cast<const float4_t*>(bias + n * 16 + 4 * g);
 #pragma unroll
-    for (int n = 0; n < NT; ++n) bco[n] = bias[n * 16 + i];
-    const int RI = RO + 2, npx = RO * RO, nmt = (npx + 15) / 16;
-    for (int mt0 = wv; mt0 < nmt; mt0 += 8) {
-        int abase[2];
-        bool aval[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int m = (mt0 + 4 * u) * 16 + i;
-            aval[u] = (mt0 + 4 * u) < nmt && m < npx;
-            const int mm = aval[u] ? m : 0;
-            abase[u] = (mm / RO) * RI + mm % RO;          // input pixel under tap (0, 0)
-        }
-        float4_t acc[2][NT];
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int n = 0; n < NT; ++n) acc[u][n] = (float4_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kc = 0; kc < KC; ++kc) {
-            int tap, q;
-            if (CIN == 32) {
-                tap = kc;
-                q = g;
-            } else {
-                tap = 2 * kc + (g >> 1);
-                q = g & 1;
-            }
-            const int dp = (tap / 3) * RI + tap % 3;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                half8_t a = {};
-                if (aval[u] && tap < 9) a = *reinterpret_cast<const half8_t*>(in + chunk_at<CIN>(abase[u] + dp, q));
-#pragma unroll
-                for (int n = 0; n < NT; ++n) acc[u][n] = mfma32(a, wf[kc][n], acc[u][n]);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (mt0 + 4 * u >= nmt) continue;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = (mt0 + 4 * u) * 16 + 4 * g + r;
-                if (m >= npx) continue;
-                const int oy = m / RO, ox = m % RO;
-                const int gy = gy0 + oy, gx = gx0 + ox;
-                const bool inside = gy >= 0 && gy < H && gx >= 0 && gx < W;
-#pragma unroll
-                for (int n = 0; n < NT; ++n) {
-                    const float v = acc[u][n][r] + bco[n];
-                    if (LAST) {
-                        if (inside) y[(fbase + (long long)gy * W + gx) * 16 + n * 16 + i] = __float2half(v);
-                    } else {
-                        const int ch = n * 16 + i;
-                        out[chunk_at<32>(m, ch >> 3) + (ch & 7)] = __float2half(inside ? fmaxf(v, 0.f) : 0.f);
-                    }
-                }
+            for (int kc = 0; kc < KC; ++kc) {
+                const int k0 = kc * 32 + 8 * g;
+                half8_t v = {};
+                if (K % 32 == 0 || k0 < K) v = *(const __attribute__((address_space(1))) half8_t*)(Wt + (n * 16 + i) * K + k0);
+                w[kc][n] = v;
             }
         }
     }
+};
+
+// One layer over the RO x RO output region (the tile grown by HALO = (RO -
+// FT) / 2 pixels) whose input region (RO + 2 wide) sits in `in`: CIN channels
+// per pixel (4: 8 bytes each, two taps per 16-byte chunk), NT output tiles of 16
+// channels, the bias added to the sums.  pre(inside, pix, n) runs before the products of a 16-pixel
+// tile and gives what epi(m, oy, ox, inside, pix, n, sums, pre's value) takes
+// after them, per tile n of output channels; pix: the pixel's number in the
+// batch (where inside the image).  A lane of a region's last, partial tile
+// past its end works on pixel 0 and stores nothing; a chunk past the ninth tap
+// (zero weights) reads the ninth.
+template <int CIN, int NT, int RO, class PRE, class EPI>
+__device__ __forceinline__ void fused_layer(const __half* __restrict__ in, const LayerWeights<CIN, NT>& lw,
+                                            const TilePos& tp, PRE pre, EPI epi)
+{
+    constexpr int KC = LayerWeights<CIN, NT>::KC, PS = px_stride<CIN>();
+    constexpr int RI = RO + 2, NPX = RO * RO, NMT = (NPX + 15) / 16, HALO = (RO - FT) / 2;
+    // (opaque: one layer's addresses in registers at a time)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, g = lane >> 4;
+    auto tap_at = [](int tap) { return tap < 9 ? (tap / 3) * RI + tap % 3 : 2 * RI + 2; };
+    for (int mt0 = wv; mt0 < NMT; mt0 += FU * FW) {
+        const __half* at[FU];
+        int m[FU];
+        bool aval[FU], inside[FU];
+        long long pix[FU];
+        decltype(pre(true, 0ll, 0)) held[FU][NT];
+#pragma unroll
+        for (int u = 0; u < FU; ++u) {
+            m[u] = (mt0 + FW * u) * 16 + i;
+            aval[u] = m[u] < NPX;
+            const int mm = aval[u] ? m[u] : 0;
+            at[u] = in + ((mm / RO) * RI + mm % RO) * PS + (CIN == 32 ? 8 * g : CIN == 16 ? 8 * (g & 1) : 0);
+            const int gy = tp.Y0 - HALO + mm / RO, gx = tp.X0 - HALO + mm % RO;
+            inside[u] = aval[u] && gy >= 0 && gy < tp.H && gx >= 0 && gx < tp.W;
+            pix[u] = tp.fbase + (long long)gy * tp.W + gx;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) held[u][n] = pre(inside[u], pix[u], n);
+        }
+        float4_t acc[FU][NT];
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) {
+#pragma unroll
+            for (int u = 0; u < FU; ++u) {
+                half8_t b;
+                if constexpr (CIN == 4) {
+                    // the chunk's two taps, 8 kc + 2 g and the next
+                    const int t0 = 8 * kc + 2 * g, c0 = min(t0, 8), c1 = min(t0 + 1, 8);
+                    const half4_t lo = *reinterpret_cast<const half4_t*>(at[u] + 4 * ((c0 / 3) * RI + c0 % 3));
+                    const half4_t hi = *reinterpret_cast<const half4_t*>(at[u] + 4 * ((c1 / 3) * RI + c1 % 3));
+                    b = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                } else if constexpr (CIN == 16) {
+                    b = *reinterpret_cast<const half8_t*>(at[u] + PS * (g >> 1 ? tap_at(2 * kc + 1) : tap_at(2 * kc)));
+                } else {
+                    b = *reinterpret_cast<const half8_t*>(at[u] + PS * tap_at(kc));
+                }
+#pragma unroll
+                for (int n = 0; n < NT; ++n) acc[u][n] = mfma32(lw.w[kc][n], b, kc == 0 ? (float4_t){0.f, 0.f, 0.f, 0.f} : acc[u][n]);
+            }
+        }
+        if constexpr (CIN == 32) {
+            // the next chunks' reads in flight under the products
+            __builtin_amdgcn_sched_group_barrier(0x100, FA * FU, 0);
+#pragma unroll
+            for (int kc = 0; kc < KC - FA; ++kc) {
+                __builtin_amdgcn_sched_group_barrier(0x008, FU * NT, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, FU, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, FA * FU * NT, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < FU; ++u)
+            if (aval[u])
+#pragma unroll
+                for (int n = 0; n < NT; ++n) epi(m[u], m[u] / RO, m[u] % RO, inside[u], pix[u], n, acc[u][n] + lw.b[n],
+                        held[u][n]);
+    }
 }
 
-__global__ __launch_bounds__(256) void k_cnn_fused(const __half* __restrict__ x, const __half* __restrict__ w0,
-                                                   const __half* __restrict__ w1, const __half* __restrict__ w2,
-                                                   const __half* __restrict__ w3, const float* __restrict__ b0,
-                                                   const float* __restrict__ b1, const float* __restrict__ b2,
-                                                   const float* __restrict__ b3, __half* __restrict__ y, int H, int W)
+// Whether position (oy, ox) of a region grown by HALO lies in the tile itself.
+template <int HALO>
+__device__ __forceinline__ bool in_tile(int oy, int ox)
+{
+    return (unsigned)(oy - HALO) < (unsigned)FT && (unsigned)(ox - HALO) < (unsigned)FT;
+}
+
+// What the network's output is for.
+enum class CnnUse { OUTPUT, APPLY, TRAIN };
+
+struct CnnForward {
+    CnnWeights w;
+    CnnBuffers b;
+    int F, H, W;
+    // OUTPUT: y [3][P], the corrections in sigma_h units
+    float* y;
+    // APPLY: slot k < 3 of a pixel with at most three points moves by sigma_h y_k
+    DevState s;
+    long long S;              // the state's slot stride
+    float sigma_h;
+    double tmax;
+    // TRAIN: true depths [n_surf][P]
+    const float* truth;
+    int n_surf;
+};
+
+// A pixel's points and true depths as the last layer's results meet them.
+constexpr int TRUTH_HELD = 4;
+struct OutputInputs {
+    int c;
+    double t[3];
+    float tr[TRUTH_HELD];
+};
+
+template <CnnUse USE>
+__global__ __launch_bounds__(64 * FW, 2) void k_cnn_forward(CnnForward a)
 {
     // buf0: the input features (FR0^2 x 16 channels), later layer 2's output
     // ((FT + 4)^2 x 32); buf1: layer 1's output ((FT + 6)^2 x 32), later layer 3's
-    __shared__ __align__(16) __half buf0[(FT + 4) * (FT + 4) * 32];
-    __shared__ __align__(16) __half buf1[(FT + 6) * (FT + 6) * 32];
-    static_assert(FR0 * FR0 * 16 <= (FT + 4) * (FT + 4) * 32, "the features fit buf0");
-    const int tx_n = (W + FT - 1) / FT, ty_n = (H + FT - 1) / FT;
-    const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
-    const int f = tile / (tx_n * ty_n), tr = tile % (tx_n * ty_n);
-    const int Y0 = (tr / tx_n) * FT, X0 = (tr % tx_n) * FT;
-    const long long fbase = (long long)f * H * W;
-    for (int v = threadIdx.x; v < FR0 * FR0 * 2; v += blockDim.x) {
-        const int p = v >> 1, q = v & 1;
-        const int gy = Y0 - 4 + p / FR0, gx = X0 - 4 + p % FR0;
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (gy >= 0 && gy < H && gx >= 0 && gx < W)
-            val = reinterpret_cast<const uint4*>(x + (fbase + (long long)gy * W + gx) * 16)[q];
-        *reinterpret_cast<uint4*>(buf0 + chunk_at<16>(p, q)) = val;
+    __shared__ __align__(16) __half buf0[(FT + 4) * (FT + 4) * px_stride<32>()];
+    __shared__ __align__(16) __half buf1[(FT + 6) * (FT + 6) * px_stride<32>()];
+    static_assert(FR0 * FR0 * px_stride<16>() <= (FT + 4) * (FT + 4) * px_stride<32>(), "the features fit buf0");
+    const int tiles = a.F * ((a.W + FT - 1) / FT) * ((a.H + FT - 1) / FT);
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    const long long P = (long long)a.F * a.H * a.W;
+    float se = 0.f, num = 0.f;
+    // (one tile per workgroup, or a stride of the grid over them in training,
+    // where each workgroup leaves one pair of loss sums)
+    for (int t = (int)xcd_block(blockIdx.x, gridDim.x); t < tiles; t += gridDim.x) {
+        const TilePos tp(t, a.H, a.W);
+        if (t >= (int)gridDim.x) __syncthreads();
+        for (int v = threadIdx.x; v < FR0 * FR0 * 2; v += blockDim.x) {
+            const int p = v >> 1, q = v & 1;
+            const int gy = tp.Y0 - 4 + p / FR0, gx = tp.X0 - 4 + p % FR0;
+            uint4 val = make_uint4(0, 0, 0, 0);
+            if (gy >= 0 && gy < a.H && gx >= 0 && gx < a.W)
+                val = reinterpret_cast<const uint4*>(a.b.act[0] + (tp.fbase + (long long)gy * a.W + gx) * 16)[q];
+            *reinterpret_cast<uint4*>(buf0 + p * px_stride<16>() + 8 * q) = val;
+        }
+        __syncthreads();
+        auto none = [](bool, long long, int) { return 0; };
+        // a hidden layer: bias, ReLU, zero outside the image; into LDS and, in
+        // training, the tile's own part to memory
+        auto hidden = [&](auto halo, __half* out, __half* act) {
+            return [=](int m, int oy, int ox, bool inside, long long pix, int n, float4_t v, int) {
+                float4_t r;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) r[c] = inside ? fmaxf(v[c], 0.f) : 0.f;
+                const half4_t h = to_half4(r);
+                const int ch = n * 16 + 4 * g;
+                *reinterpret_cast<half4_t*>(out + m * px_stride<32>() + ch) = h;
+                if (USE == CnnUse::TRAIN && inside && in_tile<decltype(halo)::value>(oy, ox))
+                    *reinterpret_cast<half4_t*>(act + pix * 32 + ch) = h;
+            };
+        };
+        const LayerWeights<16, 2> w0(a.w.wt[0], a.w.bias[0]);
+        fused_layer<16, 2, FT + 6>(buf0, w0, tp, none,
+                                   hidden(std::integral_constant<int, 3>(), buf1, a.b.act[1]));
+        __syncthreads();
+        const LayerWeights<32, 2> w1(a.w.wt[1], a.w.bias[1]);
+        fused_layer<32, 2, FT + 4>(buf1, w1, tp, none,
+                                   hidden(std::integral_constant<int, 2>(), buf0, a.b.act[2]));
+        __syncthreads();
+        const LayerWeights<32, 2> w2(a.w.wt[2], a.w.bias[2]);
+        fused_layer<32, 2, FT + 2>(buf0, w2, tp, none,
+                                   hidden(std::integral_constant<int, 1>(), buf1, a.b.act[3]));
+        __syncthreads();
+        const LayerWeights<32, 1> w3(a.w.wt[3], a.w.bias[3]);
+        // what the output is used on, loaded ahead of the layer's products
+        auto inputs = [&](bool inside, long long pix, int) {
+            OutputInputs in{};
+            if (USE == CnnUse::OUTPUT || !inside || g != 0) return in;
+            in.c = load_cnt(a.s.cnt, pix);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) in.t[k] = a.s.t[k * a.S + pix];
+            if (USE == CnnUse::TRAIN) {
+                in.c = min(in.c, 3);
+#pragma unroll
+                for (int q = 0; q < TRUTH_HELD; ++q)
+                    if (q < a.n_surf) in.tr[q] = a.truth[(long long)q * P + pix];
+            }
+            return in;
+        };
+        fused_layer<32, 1, FT>(buf1, w3, tp, inputs,
+                               [&](int, int, int, bool inside, long long pix, int, float4_t v, const OutputInputs& in) {
+            if (!inside || g != 0) return;                 // channels 0 .. 3: slots 0 .. 2
+            const half4_t y = to_half4(v);
+            if (USE == CnnUse::OUTPUT) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) a.y[k * P + pix] = (float)y[k];
+            } else if (USE == CnnUse::APPLY) {
+                if (in.c > 3) return;
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (k < in.c) {
+                        double t = in.t[k] + (double)(a.sigma_h * (float)y[k]);
+                        t = t < 0.0 ? 0.0 : (t > a.tmax ? a.tmax : t);
+                        a.s.t[k * a.S + pix] = t;
+                    }
+            } else {
+                // targets: slot k < min(cnt, 3) takes the nearest true depth of
+                // its pixel within 3 sigma_h (first surface on ties; NaN:
+                // absent); the loss is the masked squared error, dY its gradient
+                // 2 (y - y*) of the sum (1/count is applied to the weight gradients)
+                half4_t dy = {};
+                double bd[3] = {0.0, 0.0, 0.0};
+                float bt[3] = {0.f, 0.f, 0.f};
+                bool any[3] = {false, false, false};
+                for (int q = 0; q < a.n_surf; ++q) {
+                    const float tr = q < TRUTH_HELD ? (q == 0 ? in.tr[0] : q == 1 ? in.tr[1] : q == 2 ? in.tr[2] : in.tr[3])
+                                                    : a.truth[(long long)q * P + pix];
+                    if (!(tr == tr)) continue;
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const double d = fabs((double)tr - in.t[k]);
+                        if (!any[k] || d < bd[k]) {
+                            any[k] = true;
+                            bt[k] = tr;
+                            bd[k] = d;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (k < in.c && any[k] && bd[k] <= 3.0 * (double)a.sigma_h) {
+                        const float ty =
+                            fminf(fmaxf((float)(((double)bt[k] - in.t[k]) / (double)a.sigma_h), -8.f), 8.f);
+                        const float d = (float)y[k] - ty;
+                        se += d * d;
+                        num += 1.f;
+                        dy[k] = (_Float16)(2.f * d);
+                    }
+                *reinterpret_cast<half4_t*>(a.b.dy4 + pix * 4) = dy;
+            }
+        });
+    }
+    if (USE == CnnUse::TRAIN) {
+        // the workgroup's sums, in a fixed order (lanes past i hold zeros)
+        __shared__ float red[2][FW * 16];
+        static_assert(FW * 16 == 64, "a value per lane of the first wavefront");
+        if (g == 0) {
+            red[0][(threadIdx.x >> 6) * 16 + i] = se;
+            red[1][(threadIdx.x >> 6) * 16 + i] = num;
+        }
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            float s0 = red[0][threadIdx.x], s1 = red[1][threadIdx.x];
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) {
+                s0 += __shfl_xor(s0, d, 64);
+                s1 += __shfl_xor(s1, d, 64);
+            }
+            if (threadIdx.x == 0) {
+                a.b.lpart[2 * blockIdx.x] = s0;
+                a.b.lpart[2 * blockIdx.x + 1] = s1;
+            }
+        }
+    }
+}
+
+// Backward data of layers 3, 2 and 1 on a tile: the output gradient (dy4)
+// staged with a 3-pixel halo, each layer's result gated by the ReLU of its
+// input's activation, kept in LDS for the next layer and written to memory
+// (the tile's own part) for the weight gradients.
+struct CnnBackward {
+    CnnWeights w;
+    CnnBuffers b;
+    int F, H, W;
+};
+
+__global__ __launch_bounds__(64 * FW, 2) void k_cnn_backward(CnnBackward a)
+{
+    __shared__ __align__(16) __half dyb[(FT + 6) * (FT + 6) * 4];
+    __shared__ __align__(16) __half d3[(FT + 4) * (FT + 4) * px_stride<32>()];
+    __shared__ __align__(16) __half d2[(FT + 2) * (FT + 2) * px_stride<32>()];
+    const int g = (threadIdx.x & 63) >> 4;
+    const TilePos tp((int)xcd_block(blockIdx.x, gridDim.x), a.H, a.W);
+    const LayerWeights<4, 2> w3(a.w.wb[3], nullptr);
+    for (int p = threadIdx.x; p < (FT + 6) * (FT + 6); p += blockDim.x) {
+        const int gy = tp.Y0 - 3 + p / (FT + 6), gx = tp.X0 - 3 + p % (FT + 6);
+        half4_t v = {};
+        if (gy >= 0 && gy < a.H && gx >= 0 && gx < a.W)
+            v = *reinterpret_cast<const half4_t*>(a.b.dy4 + (tp.fbase + (long long)gy * a.W + gx) * 4);
+        *reinterpret_cast<half4_t*>(dyb + 4 * p) = v;
     }
     __syncthreads();
-    fused_layer<16, 2, false>(buf0, buf1, FT + 6, w0, b0, Y0 - 3, X0 - 3, H, W, fbase, nullptr);
+    // the four activations a lane's results are gated by
+    auto gate = [&](const __half* act) {
+        return [=](bool inside, long long pix, int n) {
+            half4_t v = {};
+            if (inside) v = *reinterpret_cast<const half4_t*>(act + pix * 32 + n * 16 + 4 * g);
+            return v;
+        };
+    };
+    auto result = [&](auto halo, __half* lds, __half* mem) {
+        return [=](int m, int oy, int ox, bool inside, long long pix, int n, float4_t v, half4_t act) {
+            float4_t r;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[c] = (float)act[c] > 0.f ? v[c] : 0.f;     // (zero outside the image)
+            const half4_t h = to_half4(r);
+            const int ch = n * 16 + 4 * g;
+            if (lds) *reinterpret_cast<half4_t*>(lds + m * px_stride<32>() + ch) = h;
+            if (inside && in_tile<decltype(halo)::value>(oy, ox)) *reinterpret_cast<half4_t*>(mem + pix * 32 + ch) = h;
+        };
+    };
+    fused_layer<4, 2, FT + 4>(dyb, w3, tp, gate(a.b.act[3]),
+                              result(std::integral_constant<int, 2>(), d3, a.b.dact[3]));
     __syncthreads();
-    fused_layer<32, 2, false>(buf1, buf0, FT + 4, w1, b1, Y0 - 2, X0 - 2, H, W, fbase, nullptr);
+    const LayerWeights<32, 2> w2(a.w.wb[2], nullptr);
+    fused_layer<32, 2, FT + 2>(d3, w2, tp, gate(a.b.act[2]),
+                               result(std::integral_constant<int, 1>(), d2, a.b.dact[2]));
     __syncthreads();
-    fused_layer<32, 2, false>(buf0, buf1, FT + 2, w2, b2, Y0 - 1, X0 - 1, H, W, fbase, nullptr);
+    const LayerWeights<32, 2> w1(a.w.wb[1], nullptr);
+    fused_layer<32, 2, FT>(d2, w1, tp, gate(a.b.act[1]),
+                           result(std::integral_constant<int, 0>(), (__half*)nullptr, a.b.dact[1]));
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients of all four layers (blockIdx.y) in one launch.  A workgroup
+// takes units of WG_ROWS image rows x 64 columns, strided by the grid, and
+// accumulates dW in registers over all of them: rows (tap, ci), columns co, K
+// = pixels.  Both operands lie in LDS as [pixel][channel]; the transposed LDS
+// read (ds_read_b64_tr_b16: 16 lanes read a 4 x 16 block of halves and each
+// gets a column of four) hands every lane the pixels of its channel.  Input
+// rows live in a ring of four, so each is loaded once per unit, the next row's
+// loads in flight during two rows' products.  The bias gradient is a product
+// with ones.  131 k pixels: 26 us for the four layers (162 us with the operands
+// gathered from LDS two bytes at a time, a launch per layer).
+constexpr int WG_ROWS = 8;
+constexpr int WG_COLS = 64;
+constexpr int WG_WAVES = 6;
+constexpr int WG_GROUPS = 256;     // workgroups per layer (one per CU): partial sums kept
+
+typedef short short4_t __attribute__((__vector_size__(4 * sizeof(short))));
+typedef __attribute__((address_space(3))) short4_t lds_short4;
+
+// Rows p .. p + 7 of LDS [pixel][C] (C halves per pixel, this lane's group of
+// four lanes at pixel p + (i >> 2)), channels 16 cb .. 16 cb + 15: lane i of
+// the group gets channel 16 cb + i of the eight pixels.
+template <int C>
+__device__ __forceinline__ int tr_at(int px, int cb, int i)
+{
+    // (32 channels: the two 32-byte halves of a pixel swap places every four
+    // pixels, so that the 16 rows a wavefront reads cover all banks)
+    return C == 32 ? px * 32 + 16 * (cb ^ ((px >> 2) & 1)) + 4 * (i & 3) : px * 16 + 4 * (i & 3);
+}
+
+template <int C>
+__device__ __forceinline__ half8_t tr_read8(const __half* base, int p, int cb, int i)
+{
+    union {
+        short4_t s[2];
+        half8_t h;
+    } v;
+    const int px = p + (i >> 2);
+    v.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(base + tr_at<C>(px, cb, i)));
+    v.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(base + tr_at<C>(px + 4, cb, i)));
+    return v.h;
+}
+
+// Offset of 16-byte chunk q of pixel px in the same layout.
+template <int C>
+__device__ __forceinline__ int row_chunk(int px, int q)
+{
+    return C == 32 ? px * 32 + 16 * ((q >> 1) ^ ((px >> 2) & 1)) + 8 * (q & 1) : px * 16 + 8 * q;
+}
+
+// CIN channels of X; the output gradient has GC stored channels (32, or 4 that
+// stand for 16).
+template <int CIN, int GC>
+__device__ __forceinline__ void wgrad_layer(const __half* __restrict__ X, const __half* __restrict__ dY,
+                                            float* __restrict__ part, float* __restrict__ bpart, int F, int H, int W,
+                                            __half* xs, __half* ds)
+{
+    constexpr int CO = GC == 4 ? 16 : 32, NT = CO / 16, CB = CIN / 16;
+    constexpr int TILES = 9 * CB * NT, TPW = (TILES + WG_WAVES - 1) / WG_WAVES;
+    constexpr int XR = (WG_COLS + 2) * CIN, DR = WG_COLS * CO;      // halves of a row of X, of dY
+    constexpr int XV = (WG_COLS + 2) * CIN / 8;                     // 16-byte chunks of a row of X
+    static_assert(XV <= 64 * WG_WAVES && WG_COLS * CO / 8 <= 64 * WG_WAVES, "one chunk per thread");
+    static_assert(TILES % WG_WAVES == 0, "whole tiles per wavefront");
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i = lane & 15, g = lane >> 4;
+    const int segs = (W + WG_COLS - 1) / WG_COLS, rblocks = (H + WG_ROWS - 1) / WG_ROWS, units = F * rblocks * segs;
+    float4_t acc[TPW], accb[NT];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) acc[t] = (float4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < NT; ++n) accb[n] = (float4_t){0.f, 0.f, 0.f, 0.f};
+    half8_t ones;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) ones[q] = (_Float16)1.f;
+    for (int unit = blockIdx.x; unit < units; unit += gridDim.x) {
+        const int x0 = (unit % segs) * WG_COLS, y0 = (unit / segs % rblocks) * WG_ROWS, f = unit / (segs * rblocks);
+        const int y1 = min(y0 + WG_ROWS, H);
+        const long long fbase = (long long)f * H * W;
+        auto load_x = [&](int y) {
+            uint4 v = make_uint4(0, 0, 0, 0);
+            const int px = tid / (CIN / 8), x = x0 + px - 1;
+            if (tid < XV && y >= 0 && y < H && x >= 0 && x < W)
+                v = reinterpret_cast<const uint4*>(X + (fbase + (long long)y * W + x) * CIN)[tid % (CIN / 8)];
+            return v;
+        };
+        auto store_x = [&](int y, uint4 v) {
+            if (tid < XV)
+                *reinterpret_cast<uint4*>(xs + ((y + 1) & 3) * XR + row_chunk<CIN>(tid / (CIN / 8), tid % (CIN / 8))) = v;
+        };
+        auto load_d = [&](int y) {
+            uint4 v = make_uint4(0, 0, 0, 0);
+            const int px = tid / (CO / 8), q = tid % (CO / 8), x = x0 + px;
+            if (tid < WG_COLS * CO / 8 && y < y1 && x < W) {
+                const __half* p = dY + (fbase + (long long)y * W + x) * GC;
+                if constexpr (GC == 4) {
+                    if (q == 0) {
+                        const uint2 w = *reinterpret_cast<const uint2*>(p);
+                        v = make_uint4(w.x, w.y, 0, 0);
+                    }
+                } else {
+                    v = reinterpret_cast<const uint4*>(p)[q];
+                }
+            }
+            return v;
+        };
+        auto store_d = [&](int y, uint4 v) {
+            if (tid < WG_COLS * CO / 8)
+                *reinterpret_cast<uint4*>(ds + (y & 1) * DR + row_chunk<CO>(tid / (CO / 8), tid % (CO / 8))) = v;
+        };
+        uint4 nx, nd;            // rows y + 2 of X and y + 1 of dY, in flight for two rows' products
+        {
+            const uint4 a = load_x(y0 - 1), b = load_x(y0), c = load_x(y0 + 1), d = load_d(y0);
+            nx = load_x(y0 + 2);
+            nd = load_d(y0 + 1);
+            store_x(y0 - 1, a);
+            store_x(y0, b);
+            store_x(y0 + 1, c);
+            store_d(y0, d);
+        }
+        __syncthreads();
+        for (int y = y0; y < y1; ++y) {
+            const uint4 fx = load_x(y + 3), fd = load_d(y + 2);     // (past the unit: not read)
+            const __half* dr = ds + (y & 1) * DR;
+#pragma unroll
+            for (int s = 0; s < WG_COLS / 32; ++s) {
+                const int p0 = 32 * s + 8 * g;
+                half8_t b[NT];
+#pragma unroll
+                for (int n = 0; n < NT; ++n) b[n] = tr_read8<CO>(dr, p0, n, i);
+                half8_t a = {};
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    const int tile = wv * TPW + t, mt = tile / NT, nt = tile % NT;
+                    const int tap = mt / CB, cb = mt % CB, ky = tap / 3, kx = tap % 3;
+                    if (t == 0 || nt == 0) a = tr_read8<CIN>(xs + ((y + ky) & 3) * XR, p0 + kx, cb, i);
+                    acc[t] = mfma32(a, NT == 1 || nt == 0 ? b[0] : b[NT - 1], acc[t]);
+                }
+                if (wv == 0)
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) accb[n] = mfma32(ones, b[n], accb[n]);
+            }
+            store_x(y + 2, nx);
+            store_d(y + 1, nd);
+            nx = fx;
+            nd = fd;
+            __syncthreads();
+        }
+    }
+    float* out = part + (size_t)blockIdx.x * CNN_PART;
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        const int tile = wv * TPW + t, mt = tile / NT, nt = tile % NT;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) out[(mt * 16 + 4 * g + r) * CO + nt * 16 + i] = acc[t][r];
+    }
+    if (wv == 0 && g == 0)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) bpart[(size_t)blockIdx.x * CNN_PART + n * 16 + i] = accb[n][0];
+}
+
+__global__ __launch_bounds__(64 * WG_WAVES) void k_cnn_wgrad(CnnBackward a)
+{
+    __shared__ __align__(16) __half xs[4 * (WG_COLS + 2) * 32];
+    __shared__ __align__(16) __half ds[2 * WG_COLS * 32];
+    float* part = a.b.part;
+    switch (blockIdx.y) {
+    case 0:
+        wgrad_layer<16, 32>(a.b.act[0], a.b.dact[1], part + CNN_POFF[0], part + CNN_PBIAS[0], a.F, a.H, a.W, xs, ds);
+        break;
+    case 1:
+        wgrad_layer<32, 32>(a.b.act[1], a.b.dact[2], part + CNN_POFF[1], part + CNN_PBIAS[1], a.F, a.H, a.W, xs, ds);
+        break;
+    case 2:
+        wgrad_layer<32, 32>(a.b.act[2], a.b.dact[3], part + CNN_POFF[2], part + CNN_PBIAS[2], a.F, a.H, a.W, xs, ds);
+        break;
+    default:
+        wgrad_layer<32, 4>(a.b.act[3], a.b.dy4, part + CNN_POFF[3], part + CNN_PBIAS[3], a.F, a.H, a.W, xs, ds);
+        break;
+    }
+}
+
+// The gradient from the partial sums (ng of them), scaled by 1/count, Adam and
+// the FP16 layouts, a thread per parameter and sixteen slices of the partials
+// each, added in a fixed order; the loss (sums of nl pairs) from workgroup 0.
+// 10 us for 28 MB of partials (4 x 76 us as one thread per parameter over all
+// of them, a launch per layer, and 36 us for the loss on one lane).
+constexpr int UPD_PARAMS = 64, UPD_SLICES = 16;
+
+__global__ __launch_bounds__(UPD_PARAMS * UPD_SLICES) void k_cnn_update(CnnWeights W, CnnBuffers b, int ng, int nl,
+                                                                        CnnAdam opt, float c1, float c2, float* loss)
+{
+    __shared__ double lsum[2][UPD_SLICES];
+    __shared__ float red[UPD_SLICES][UPD_PARAMS];
+    const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
+    // loss sums (of whole numbers below 2^31, and of squared errors): slice by slice
+    {
+        double se = 0.0, n = 0.0;
+        for (int k = slice * 64 + lane; k < nl; k += UPD_SLICES * 64) {
+            se += b.lpart[2 * k];
+            n += b.lpart[2 * k + 1];
+        }
+        se = wave_sum(se);
+        n = wave_sum(n);
+        if (lane == 0) {
+            lsum[0][slice] = se;
+            lsum[1][slice] = n;
+        }
+    }
+    const int idx = blockIdx.x * UPD_PARAMS + lane;
+    float s = 0.f;
+    if (idx < CNN_PARAMS) {
+        int l = 0;
+#pragma unroll
+        for (int k = 1; k < CNN_LAYERS; ++k) l = idx >= CNN_OFF[k] ? k : l;
+        const int p = idx - (l == 0 ? CNN_OFF[0] : l == 1 ? CNN_OFF[1] : l == 2 ? CNN_OFF[2] : CNN_OFF[3]);
+        const int nw = l == 0 ? 9 * 16 * 32 : l == 3 ? 9 * 32 * 3 : 9 * 32 * 32;
+        const int po = l == 0 ? CNN_POFF[0] : l == 1 ? CNN_POFF[1] : l == 2 ? CNN_POFF[2] : CNN_POFF[3];
+        const int pb = l == 0 ? CNN_PBIAS[0] : l == 1 ? CNN_PBIAS[1] : l == 2 ? CNN_PBIAS[2] : CNN_PBIAS[3];
+        const int at = p >= nw ? pb + p - nw : l == 3 ? po + (p / 3) * 16 + p % 3 : po + p;
+        const int per = (ng + UPD_SLICES - 1) / UPD_SLICES, g0 = slice * per, g1 = min(g0 + per, ng);
+        const float* src = b.part + at;
+        int k = g0;
+        for (; k + 8 <= g1; k += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(k + u) * CNN_PART];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; k < g1; ++k) s += src[(size_t)k * CNN_PART];
+    }
+    red[slice][lane] = s;
     __syncthreads();
-    fused_layer<32, 1, true>(buf1, nullptr, FT, w3, b3, Y0, X0, H, W, fbase, y);
+    if (slice != 0) return;
+    double se = 0.0, n = 0.0;
+#pragma unroll
+    for (int k = 0; k < UPD_SLICES; ++k) {
+        se += lsum[0][k];
+        n += lsum[1][k];
+    }
+    if (blockIdx.x == 0 && lane == 0) {
+        loss[0] = (float)(se / (n > 1.0 ? n : 1.0));
+        loss[1] = (float)n;
+    }
+    if (idx >= CNN_PARAMS) return;
+    s = 0.f;
+#pragma unroll
+    for (int k = 0; k < UPD_SLICES; ++k) s += red[k][lane];
+    const float gi = s * (1.f / fmaxf((float)n, 1.f));
+    b.grad[idx] = gi;
+    store_weight(W, idx, adam_step(W.master, W.m, W.v, idx, gi, opt, c1, c2));
 }
 
 // ---------------------------------------------------------------------------
 // launchers
 
-static inline unsigned nb256(long long n) { return (unsigned)((n + 255) / 256); }
-
-// Forward / backward-data workgroups: 64 columns x CR rows each.
-static unsigned conv_grid(const Shape& sh)
+static unsigned tiles_of_frames(const Shape& sh, int t)
 {
-    return (unsigned)(sh.F * ((sh.rows + CR - 1) / CR) * ((sh.cols + CT - 1) / CT));
+    return (unsigned)(sh.F * ((sh.rows + t - 1) / t) * ((sh.cols + t - 1) / t));
 }
 
+// Units of the weight gradient (a workspace admits shapes of at most as many
+// as it was sized for); WG_GROUPS workgroups at most share them.
 unsigned cnn_wgrad_groups(const Shape& sh)
 {
-    return (unsigned)(sh.F * ((sh.rows + WG_ROWS - 1) / WG_ROWS) * ((sh.cols + CT - 1) / CT));
+    return (unsigned)(sh.F * ((sh.rows + WG_ROWS - 1) / WG_ROWS) * ((sh.cols + WG_COLS - 1) / WG_COLS));
 }
+
+unsigned cnn_wgrad_partials(unsigned groups) { return groups < (unsigned)WG_GROUPS ? groups : (unsigned)WG_GROUPS; }
 
 hipError_t launch_cnn_prepare(const CnnWeights& w, hipStream_t st)
 {
-    const float* mw = w.master;
-    for (int l = 0; l < CNN_LAYERS; ++l) {
-        const int nf = CNN_COS[l] * 9 * CNN_CIS[l];
-        hipLaunchKernelGGL(k_cnn_prepare, dim3(nb256(nf)), dim3(256), 0, st, mw, CNN_CIN[l], CNN_COUT[l],
-                           CNN_CIS[l], CNN_COS[l], w.wt[l], l > 0 ? w.wb[l] : nullptr, w.bias[l]);
-        mw += 9 * CNN_CIN[l] * CNN_COUT[l] + CNN_COUT[l];
-    }
+    hipLaunchKernelGGL(k_cnn_prepare, dim3((CNN_PARAMS + 255) / 256), dim3(256), 0, st, w);
     return hipGetLastError();
 }
 
-hipError_t launch_cnn_forward(const Shape& sh, DevState s, float sigma_h, const CnnWeights& w, const CnnBuffers& b,
-                              hipStream_t st)
+static void launch_pack(const Shape& sh, DevState s, float sigma_h, const CnnBuffers& b, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_cnn_pack, dim3(tiles_of_frames(sh, PKT)), dim3(PKT * PKT), 0, st, sh, s, sigma_h, b.act[0]);
+}
+
+hipError_t launch_cnn_output(const Shape& sh, DevState s, float sigma_h, const CnnWeights& w, const CnnBuffers& b,
+                             float* y, hipStream_t st)
 {
     if (sh.P == 0) return hipSuccess;
-    const unsigned tiles = (unsigned)(sh.F * ((sh.rows + PKT - 1) / PKT) * ((sh.cols + PKT - 1) / PKT));
-    hipLaunchKernelGGL(k_cnn_pack, dim3(tiles), dim3(PKT * PKT), 0, st, sh, s, sigma_h, b.act[0]);
-    const unsigned g = conv_grid(sh);
-    hipLaunchKernelGGL((k_conv3x3<16, 32, 0>), dim3(g), dim3(64 * CR), 0, st, b.act[0], w.wt[0], w.bias[0], nullptr,
-                       b.act[1], sh.F, sh.rows, sh.cols);
-    hipLaunchKernelGGL((k_conv3x3<32, 32, 0>), dim3(g), dim3(64 * CR), 0, st, b.act[1], w.wt[1], w.bias[1], nullptr,
-                       b.act[2], sh.F, sh.rows, sh.cols);
-    hipLaunchKernelGGL((k_conv3x3<32, 32, 0>), dim3(g), dim3(64 * CR), 0, st, b.act[2], w.wt[2], w.bias[2], nullptr,
-                       b.act[3], sh.F, sh.rows, sh.cols);
-    hipLaunchKernelGGL((k_conv3x3<32, 16, 1>), dim3(g), dim3(64 * CR), 0, st, b.act[3], w.wt[3], w.bias[3], nullptr,
-                       b.act[4], sh.F, sh.rows, sh.cols);
+    launch_pack(sh, s, sigma_h, b, st);
+    CnnForward a{};
+    a.w = w;
+    a.b = b;
+    a.F = sh.F;
+    a.H = sh.rows;
+    a.W = sh.cols;
+    a.y = y;
+    hipLaunchKernelGGL(k_cnn_forward<CnnUse::OUTPUT>, dim3(tiles_of_frames(sh, FT)), dim3(64 * FW), 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_cnn_infer(const Shape& sh, DevState s, float sigma_h, const CnnWeights& w, const CnnBuffers& b,
-                            hipStream_t st)
+hipError_t launch_cnn_apply(const Shape& sh, DevState s, float sigma_h, const CnnWeights& w, const CnnBuffers& b,
+                            double tmax, hipStream_t st)
 {
     if (sh.P == 0) return hipSuccess;
-    const unsigned tiles = (unsigned)(sh.F * ((sh.rows + PKT - 1) / PKT) * ((sh.cols + PKT - 1) / PKT));
-    hipLaunchKernelGGL(k_cnn_pack, dim3(tiles), dim3(PKT * PKT), 0, st, sh, s, sigma_h, b.act[0]);
-    const unsigned ft = (unsigned)(sh.F * ((sh.rows + FT - 1) / FT) * ((sh.cols + FT - 1) / FT));
-    hipLaunchKernelGGL(k_cnn_fused, dim3(ft), dim3(256), 0, st, b.act[0], w.wt[0], w.wt[1], w.wt[2], w.wt[3],
-                       w.bias[0], w.bias[1], w.bias[2], w.bias[3], b.act[4], sh.rows, sh.cols);
-    return hipGetLastError();
-}
-
-hipError_t launch_cnn_apply(const Shape& sh, const CnnBuffers& b, float sigma_h, double tmax, DevState s,
-                            hipStream_t st)
-{
-    if (sh.P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cnn_apply, dim3(nb256(sh.P)), dim3(256), 0, st, sh, b.act[4], sigma_h, tmax, s);
-    return hipGetLastError();
-}
-
-hipError_t launch_cnn_unpack(const Shape& sh, const CnnBuffers& b, float* out, hipStream_t st)
-{
-    if (sh.P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cnn_unpack, dim3(nb256(sh.P)), dim3(256), 0, st, sh.P, b.act[4], out);
+    launch_pack(sh, s, sigma_h, b, st);
+    CnnForward a{};
+    a.w = w;
+    a.b = b;
+    a.F = sh.F;
+    a.H = sh.rows;
+    a.W = sh.cols;
+    a.s = s;
+    a.S = sh.S;
+    a.sigma_h = sigma_h;
+    a.tmax = tmax;
+    hipLaunchKernelGGL(k_cnn_forward<CnnUse::APPLY>, dim3(tiles_of_frames(sh, FT)), dim3(64 * FW), 0, st, a);
     return hipGetLastError();
 }
 
@@ -707,48 +883,30 @@ hipError_t launch_cnn_train_step(const Shape& sh, DevState s, float sigma_h, con
                                  hipStream_t st)
 {
     if (sh.P == 0) return hipSuccess;
-    hipError_t e = launch_cnn_forward(sh, s, sigma_h, w, b, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cnn_targets, dim3(nb256(sh.P)), dim3(256), 0, st, sh, s, truth, S, sigma_h, b.tgt, b.msk);
-    const unsigned nbl = nb256(sh.P);
-    hipLaunchKernelGGL(k_cnn_loss, dim3(nbl), dim3(256), 0, st, sh.P, b.act[4], b.tgt, b.msk, b.dy16, b.lpart);
-    hipLaunchKernelGGL(k_cnn_loss_final, dim3(1), dim3(64), 0, st, b.lpart, (int)nbl, loss);
-    const unsigned g = conv_grid(sh);
-    const unsigned gw = cnn_wgrad_groups(sh);
-    // layer 3 (32 -> 16 stored): weight gradient, then data gradient into layer 2's output
-    float* grad = b.grad;
-    const int off3 = CNN_OFF[3], off2 = CNN_OFF[2], off1 = CNN_OFF[1], off0 = CNN_OFF[0];
-    hipLaunchKernelGGL((k_conv3x3_wgrad<32, 16>), dim3(gw), dim3(256), 0, st, b.act[3], b.dy16, b.part, b.bpart,
-                       sh.F, sh.rows, sh.cols);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(nb256(9 * 32 * 3 + 3)), dim3(256), 0, st, b.part, b.bpart, (int)gw, 32, 16,
-                       32, 3, loss + 1, grad + off3);
-    hipLaunchKernelGGL((k_conv3x3<16, 32, 2>), dim3(g), dim3(64 * CR), 0, st, b.dy16, w.wb[3], nullptr, b.act[3], b.dA,
-                       sh.F, sh.rows, sh.cols);
-    // layer 2
-    hipLaunchKernelGGL((k_conv3x3_wgrad<32, 32>), dim3(gw), dim3(256), 0, st, b.act[2], b.dA, b.part, b.bpart,
-                       sh.F, sh.rows, sh.cols);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(nb256(9 * 32 * 32 + 32)), dim3(256), 0, st, b.part, b.bpart, (int)gw, 32,
-                       32, 32, 32, loss + 1, grad + off2);
-    hipLaunchKernelGGL((k_conv3x3<32, 32, 2>), dim3(g), dim3(64 * CR), 0, st, b.dA, w.wb[2], nullptr, b.act[2], b.dB,
-                       sh.F, sh.rows, sh.cols);
-    // layer 1
-    hipLaunchKernelGGL((k_conv3x3_wgrad<32, 32>), dim3(gw), dim3(256), 0, st, b.act[1], b.dB, b.part, b.bpart,
-                       sh.F, sh.rows, sh.cols);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(nb256(9 * 32 * 32 + 32)), dim3(256), 0, st, b.part, b.bpart, (int)gw, 32,
-                       32, 32, 32, loss + 1, grad + off1);
-    hipLaunchKernelGGL((k_conv3x3<32, 32, 2>), dim3(g), dim3(64 * CR), 0, st, b.dB, w.wb[1], nullptr, b.act[1], b.dA,
-                       sh.F, sh.rows, sh.cols);
-    // layer 0 (16 -> 32): weight gradient only
-    hipLaunchKernelGGL((k_conv3x3_wgrad<16, 32>), dim3(gw), dim3(256), 0, st, b.act[0], b.dA, b.part, b.bpart,
-                       sh.F, sh.rows, sh.cols);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(nb256(9 * 16 * 32 + 32)), dim3(256), 0, st, b.part, b.bpart, (int)gw, 16,
-                       32, 16, 32, loss + 1, grad + off0);
-    // Adam, then the FP16 layouts
+    launch_pack(sh, s, sigma_h, b, st);
+    CnnForward a{};
+    a.w = w;
+    a.b = b;
+    a.F = sh.F;
+    a.H = sh.rows;
+    a.W = sh.cols;
+    a.s = s;
+    a.S = sh.S;
+    a.sigma_h = sigma_h;
+    a.truth = truth;
+    a.n_surf = S;
+    const unsigned ft = tiles_of_frames(sh, FT);
+    const unsigned nl = ft < CNN_LOSS_PARTS ? ft : CNN_LOSS_PARTS;
+    hipLaunchKernelGGL(k_cnn_forward<CnnUse::TRAIN>, dim3(nl), dim3(64 * FW), 0, st, a);
+    const CnnBackward c{w, b, sh.F, sh.rows, sh.cols};
+    hipLaunchKernelGGL(k_cnn_backward, dim3(ft), dim3(64 * FW), 0, st, c);
+    const unsigned ng = cnn_wgrad_partials(cnn_wgrad_groups(sh));
+    hipLaunchKernelGGL(k_cnn_wgrad, dim3(ng, CNN_LAYERS), dim3(64 * WG_WAVES), 0, st, c);
     ++w.step;
     const float c1 = 1.f - powf(opt.beta1, (float)w.step), c2 = 1.f - powf(opt.beta2, (float)w.step);
-    hipLaunchKernelGGL(k_adam, dim3(nb256(CNN_PARAMS)), dim3(256), 0, st, w.master, w.m, w.v, grad, CNN_PARAMS,
-                       opt.lr, opt.beta1, opt.beta2, opt.eps, c1, c2);
-    return launch_cnn_prepare(w, st);
+    hipLaunchKernelGGL(k_cnn_update, dim3((CNN_PARAMS + UPD_PARAMS - 1) / UPD_PARAMS), dim3(UPD_PARAMS * UPD_SLICES),
+                       0, st, w, b, (int)ng, (int)nl, opt, c1, c2, loss);
+    return hipGetLastError();
 }
 
 }  // namespace rt3d

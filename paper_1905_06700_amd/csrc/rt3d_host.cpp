@@ -132,18 +132,12 @@ Workspace carve(uint8_t* base, long long P, long long Ps, uint64_t E, bool with_
     }
     w.btmp = (float*)take(sizeof(float) * P);
     if (with_cnn) {
-        const size_t nb = (size_t)((P + 255) / 256);
         w.cnn.act[0] = (__half*)take(sizeof(__half) * 16 * P);
         for (int l = 1; l <= 3; ++l) w.cnn.act[l] = (__half*)take(sizeof(__half) * 32 * P);
-        w.cnn.act[4] = (__half*)take(sizeof(__half) * 16 * P);
-        w.cnn.dy16 = (__half*)take(sizeof(__half) * 16 * P);
-        w.cnn.dA = (__half*)take(sizeof(__half) * 32 * P);
-        w.cnn.dB = (__half*)take(sizeof(__half) * 32 * P);
-        w.cnn.tgt = (float*)take(sizeof(float) * 3 * P);
-        w.cnn.msk = (uint8_t*)take(3 * P);
-        w.cnn.lpart = (float*)take(sizeof(float) * 2 * nb);
-        w.cnn.part = (float*)take(sizeof(float) * (size_t)cnn_groups * 9 * 32 * 32);
-        w.cnn.bpart = (float*)take(sizeof(float) * (size_t)cnn_groups * 32);
+        for (int l = 1; l <= 3; ++l) w.cnn.dact[l] = (__half*)take(sizeof(__half) * 32 * P);
+        w.cnn.dy4 = (__half*)take(sizeof(__half) * 4 * P);
+        w.cnn.lpart = (float*)take(sizeof(float) * 2 * CNN_LOSS_PARTS);
+        w.cnn.part = (float*)take(sizeof(float) * (size_t)cnn_wgrad_partials(cnn_groups) * CNN_PART);
         w.cnn.grad = (float*)take(sizeof(float) * CNN_PARAMS);
     }
     w.bytes = at;
@@ -647,7 +641,6 @@ CnnBuffers cnn_at(const CnnBuffers& b, long long base)
 {
     CnnBuffers r = b;
     r.act[0] += base * 16;
-    r.act[4] += base * 16;
     return r;
 }
 
@@ -693,8 +686,8 @@ rt3d_status iterate(rt3d_ctx* c, const Shape& sh, const std::vector<Group>& grou
         for (const Group& g : groups) {
             const CnnBuffers b = cnn_at(*cnn, g.base);
             const DevState ga = state_at(alt, g.base);
-            RT3D_LAUNCH(c, RT3D_KERNEL_CNN, st, launch_cnn_infer(g.sh, ga, sig, c->cnn, b, st));
-            RT3D_HIP(c, launch_cnn_apply(g.sh, b, sig, (double)(c->T - 1), ga, st));
+            RT3D_LAUNCH(c, RT3D_KERNEL_CNN, st,
+                        launch_cnn_apply(g.sh, ga, sig, c->cnn, b, (double)(c->T - 1), st));
         }
         std::swap(cur, alt);
     } else {
@@ -1696,8 +1689,7 @@ rt3d_status rt3d_cnn_forward(rt3d_ctx* c, const rt3d_state* st, float* y, void* 
     if (s != RT3D_OK) return s;
     const Shape sh = shape_of(st->frames, st->rows, st->cols);
     hipStream_t hs = (hipStream_t)hip_stream;
-    RT3D_HIP(c, launch_cnn_infer(sh, dev_state(st), (float)std::sqrt(c->irf[0].sigma2), c->cnn, w.cnn, hs));
-    RT3D_HIP(c, launch_cnn_unpack(sh, w.cnn, y, hs));
+    RT3D_HIP(c, launch_cnn_output(sh, dev_state(st), (float)std::sqrt(c->irf[0].sigma2), c->cnn, w.cnn, y, hs));
     return RT3D_OK;
 }
 
