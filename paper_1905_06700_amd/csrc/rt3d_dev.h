@@ -614,7 +614,9 @@ hipError_t launch_compact_noalloc(const uint16_t* Z, long long P, int T, uint32_
 
 hipError_t launch_compact_events(const uint32_t* pix, const uint16_t* bin, uint64_t n, long long P, int T,
                                  uint32_t* evoff, uint32_t* scratch, uint32_t* off, uint32_t* ent, uint64_t cap,
-                                 uint32_t* counts, uint32_t* partial, int32_t* err, hipStream_t st);
+                                 uint32_t* counts, uint32_t* buckets, int32_t* err, hipStream_t st);
+// Words of `buckets` for P pixels.
+long long ev_bucket_words(long long P);
 
 hipError_t launch_init(const DevModel& m, const DevParams& p, const Shape& sh, const uint32_t* off,
                        const uint32_t* ent, const float* gain, DevState s, hipStream_t st);

@@ -92,6 +92,7 @@ struct Workspace {
     uint32_t* counts;
     uint32_t* partial;
     uint32_t* evoff;
+    uint32_t* ev_buckets;              // the event ingest's buckets of pixels
     uint32_t* stage;
     uint32_t* cls_list;                // per-class pixel lists (per-pixel IRFs)
     uint32_t* cls_meta;
@@ -120,6 +121,7 @@ Workspace carve(uint8_t* base, long long P, long long Ps, uint64_t E, bool with_
     w.counts = (uint32_t*)take(sizeof(uint32_t) * std::max<long long>(Ps, 1));
     w.partial = (uint32_t*)take(sizeof(uint32_t) * scan_partial_elems(Ps));
     w.evoff = (uint32_t*)take(sizeof(uint32_t) * (P + 1));
+    w.ev_buckets = (uint32_t*)take(sizeof(uint32_t) * ev_bucket_words(P));
     w.stage = (uint32_t*)take(sizeof(uint32_t) * CP_STAGE * std::max<long long>(P, 1));
     w.cls_list = (uint32_t*)take(sizeof(uint32_t) * std::max<long long>(P, 1));
     w.cls_meta = (uint32_t*)take(sizeof(uint32_t) * CLASS_META);
@@ -1062,7 +1064,7 @@ rt3d_status rt3d_reconstruct(rt3d_ctx* c, const rt3d_input* in, rt3d_output* out
             return fail(c, RT3D_E_INVALID, "ev_pixel/ev_bin/ev_scratch is NULL");
         RT3D_LAUNCH(c, RT3D_KERNEL_COMPACT, st,
                     launch_compact_events(in->ev_pixel, in->ev_bin, in->n_events, sh.P, c->T, w.evoff,
-                                          in->ev_scratch, w.off, w.ent, c->ws_E, w.counts, w.partial, w.err, st));
+                                          in->ev_scratch, w.off, w.ent, c->ws_E, w.counts, w.ev_buckets, w.err, st));
         off = w.off;
         ent = w.ent;
         c->last_compacted = true;
@@ -1340,7 +1342,7 @@ rt3d_status rt3d_debug_compact_events(rt3d_ctx* c, const uint32_t* ev_pixel, con
     rt3d_status s = need_ws(c, npix, w);
     if (s != RT3D_OK) return s;
     RT3D_HIP(c, launch_compact_events(ev_pixel, ev_bin, n_events, npix, c->T, w.evoff, ev_scratch, off, ent,
-                                      capacity, w.counts, w.partial, w.err, (hipStream_t)hip_stream));
+                                      capacity, w.counts, w.ev_buckets, w.err, (hipStream_t)hip_stream));
     return RT3D_OK;
 }
 
