@@ -21,7 +21,8 @@
 // points, accumulating the sphere moments over the window from LDS in FP32,
 // in coordinates local to the query (depth differences formed in FP64); under
 // the orthographic map the halo covers only the pixels whose lateral offset
-// stays below h, and each neighbour is read once for all the pixel's slots.
+// stays below h, and each neighbour is read once for all the pixel's slots;
+// under the pinhole camera a thread takes one point (k_apss_pinhole).
 // Windows whose staged tile does not fit in 64 KB of LDS take a variant with
 // eight lanes per pixel reading the state from global memory, the partial
 // moment sets meeting in a fixed wavefront-shuffle tree.
@@ -37,6 +38,14 @@ inline size_t apss_tile_bytes(int R)
 {
     const size_t SX = ATX + 2 * (size_t)R, SY = ATY + 2 * (size_t)R;
     return SX * SY * (KM * sizeof(double) + 3 * KM * sizeof(float) + sizeof(int));
+}
+
+// The pinhole kernel's: also the inverse ray length per pixel, and the list of
+// the tile's points.
+inline size_t pinhole_tile_bytes(int R)
+{
+    const size_t SX = ATX + 2 * (size_t)R, SY = ATY + 2 * (size_t)R;
+    return apss_tile_bytes(R) + SX * SY * sizeof(double) + KM * ATX * ATY * sizeof(uint16_t);
 }
 
 size_t apss_lds_bytes(int R) { return apss_tile_bytes(R); }
@@ -57,19 +66,15 @@ int apss_staged_halo(double h_apss, double p_xy, int R)
     return r;
 }
 
-// PERSP: positions of the pinhole camera (t dz along each pixel's ray,
-// differences formed in FP64), no lateral pre-test, projection along the
-// query's ray; else the orthographic map, staged halo p.apss_Rs.
-// carry: also copy the count, background and intensities to `out` (else
-// `out` receives only the depths and normals of the live slots).  The
-// orthographic variant runs five workgroups per CU (96 VGPRs; a few values
+// The orthographic map, staged halo p.apss_Rs.  carry: also copy the count,
+// background and intensities to `out` (else `out` receives only the depths and
+// normals of the live slots).  Five workgroups per CU (96 VGPRs; a few values
 // wait in scratch).
-template <bool PERSP>
-__global__ __launch_bounds__(ATX * ATY, PERSP ? 1 : 5) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in,
-                                                       DevState out, int only_above, int carry)
+__global__ __launch_bounds__(ATX * ATY, 5) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in,
+                                                            DevState out, int only_above, int carry)
 {
     extern __shared__ double apss_lds[];
-    const int R = PERSP ? p.apss_R : p.apss_Rs, SX = ATX + 2 * R, NS = SX * (ATY + 2 * R);
+    const int R = p.apss_Rs, SX = ATX + 2 * R, NS = SX * (ATY + 2 * R);
     double* tl = apss_lds;                                      // [KM][NS] depths
     float* nl = reinterpret_cast<float*>(tl + KM * NS);         // [3][KM][NS] normals
     int* cl = reinterpret_cast<int*>(nl + 3 * KM * NS);         // [NS] counts (0 outside the frame)
@@ -121,134 +126,293 @@ __global__ __launch_bounds__(ATX * ATY, PERSP ? 1 : 5) void k_apss_tile(DevModel
     const float pxy = (float)p.p_xy;
     const double dz = p.dz;
     const double tmax = (double)(m.T - 1);
-    if constexpr (!PERSP) {
-        // every live slot of the pixel against each neighbour in turn: the
-        // neighbour's depth and normal are read from LDS once for all slots
-        double tq[KM];
-        float W[KM], Px[KM], Py[KM], Pz[KM], Nx[KM], Ny[KM], Nz[KM], PN[KM], PP[KM], nn[KM];
+    // every live slot of the pixel against each neighbour in turn: the
+    // neighbour's depth and normal are read from LDS once for all slots
+    double tq[KM];
+    float W[KM], Px[KM], Py[KM], Pz[KM], Nx[KM], Ny[KM], Nz[KM], PN[KM], PP[KM], nn[KM];
 #pragma unroll
-        for (int k = 0; k < KM; ++k) {
-            tq[k] = k < c ? tl[k * NS + xc] : 0.0;
-            W[k] = Px[k] = Py[k] = Pz[k] = Nx[k] = Ny[k] = Nz[k] = PN[k] = PP[k] = nn[k] = 0.f;
-        }
-        if (fit) {
-            for (int di = -R; di <= R; ++di) {
-                const float yy = (float)di * pxy;
-                for (int dj = -R; dj <= R; ++dj) {
-                    // pixels whose lateral offset alone reaches h hold no neighbour
-                    const float yx = (float)dj * pxy;
-                    const float dl = fmaf(yx, yx, yy * yy);
-                    if (!(dl < h2)) continue;
-                    const int x = xc + di * SX + dj;
-                    const int cc = cl[x];
+    for (int k = 0; k < KM; ++k) {
+        tq[k] = k < c ? tl[k * NS + xc] : 0.0;
+        W[k] = Px[k] = Py[k] = Pz[k] = Nx[k] = Ny[k] = Nz[k] = PN[k] = PP[k] = nn[k] = 0.f;
+    }
+    if (fit) {
+        for (int di = -R; di <= R; ++di) {
+            const float yy = (float)di * pxy;
+            for (int dj = -R; dj <= R; ++dj) {
+                // pixels whose lateral offset alone reaches h hold no neighbour
+                const float yx = (float)dj * pxy;
+                const float dl = fmaf(yx, yx, yy * yy);
+                if (!(dl < h2)) continue;
+                const int x = xc + di * SX + dj;
+                const int cc = cl[x];
 #pragma unroll
-                    for (int k2 = 0; k2 < KM; ++k2) {
-                        if (k2 >= cc) break;
-                        const double t2 = tl[k2 * NS + x];
-                        const float nx = nl[(0 * KM + k2) * NS + x];
-                        const float ny = nl[(1 * KM + k2) * NS + x];
-                        const float nz = nl[(2 * KM + k2) * NS + x];
-                        const float yn = fmaf(yx, nx, yy * ny);
+                for (int k2 = 0; k2 < KM; ++k2) {
+                    if (k2 >= cc) break;
+                    const double t2 = tl[k2 * NS + x];
+                    const float nx = nl[(0 * KM + k2) * NS + x];
+                    const float ny = nl[(1 * KM + k2) * NS + x];
+                    const float nz = nl[(2 * KM + k2) * NS + x];
+                    const float yn = fmaf(yx, nx, yy * ny);
 #pragma unroll
-                        for (int k = 0; k < KM; ++k) {
-                            if (k >= c) break;
-                            const float yz = (float)((t2 - tq[k]) * dz);
-                            const float d2 = fmaf(yz, yz, dl);
-                            if (!(d2 < h2)) continue;
-                            float a = 1.f - d2 * inv_h2;
-                            a = a * a;
-                            const float w = a * a;
-                            W[k] += w;
-                            Px[k] = fmaf(w, yx, Px[k]);
-                            Py[k] = fmaf(w, yy, Py[k]);
-                            Pz[k] = fmaf(w, yz, Pz[k]);
-                            Nx[k] = fmaf(w, nx, Nx[k]);
-                            Ny[k] = fmaf(w, ny, Ny[k]);
-                            Nz[k] = fmaf(w, nz, Nz[k]);
-                            PN[k] = fmaf(w, fmaf(yz, nz, yn), PN[k]);
-                            PP[k] = fmaf(w, d2, PP[k]);
-                            nn[k] += 1.f;
-                        }
+                    for (int k = 0; k < KM; ++k) {
+                        if (k >= c) break;
+                        const float yz = (float)((t2 - tq[k]) * dz);
+                        const float d2 = fmaf(yz, yz, dl);
+                        if (!(d2 < h2)) continue;
+                        float a = 1.f - d2 * inv_h2;
+                        a = a * a;
+                        const float w = a * a;
+                        W[k] += w;
+                        Px[k] = fmaf(w, yx, Px[k]);
+                        Py[k] = fmaf(w, yy, Py[k]);
+                        Pz[k] = fmaf(w, yz, Pz[k]);
+                        Nx[k] = fmaf(w, nx, Nx[k]);
+                        Ny[k] = fmaf(w, ny, Ny[k]);
+                        Nz[k] = fmaf(w, nz, Nz[k]);
+                        PN[k] = fmaf(w, fmaf(yz, nz, yn), PN[k]);
+                        PP[k] = fmaf(w, d2, PP[k]);
+                        nn[k] += 1.f;
                     }
                 }
             }
         }
+    }
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+        if (k >= c) break;
+        double tn = tq[k];
+        float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
+        apss_project(fit && nn[k] >= (float)p.m_min, W[k], Px[k], Py[k], Pz[k], Nx[k], Ny[k], Nz[k], PN[k],
+                     PP[k], h, h2, dz, tmax, tn, on);
+        out.t[k * S + pix] = tn;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];
+    }
+}
+
+// The pinhole camera: a point at depth t lies t dz along its pixel's ray
+// (ray_dir), differences formed in FP64, the projection along the query's ray.
+// The tile is staged as above with the full halo p.apss_R and each pixel's
+// inverse ray length (the ray is its unnormalised form times that); then one
+// thread per live point of the tile (listed by pixel in LDS), so that neither
+// the pixels without points nor the second and third slots leave lanes idle,
+// and the rays' square roots are taken once per staged pixel.  A thread's
+// window is cut to the pixels whose rays pass closer than h to the point at
+// all: with uq and u2 = uq + a (dj, di, 0) the unnormalised rays, the point at
+// range rho lies at least rho |uq x u2| / (|uq| |u2|) away from the ray u2,
+// |uq x u2|^2 = a^2 (dj^2 + di^2 + (ux di - uy dj)^2): an ellipse of pixels.
+// Points are taken in the order of their ellipses' rows, so that a wavefront's
+// lanes walk windows of one size, and every second round of workgroups hands
+// the large ones to the SIMDs that have the small ones of the round before.
+// Only slots within h in range are looked at closer: mostly one of a pixel's.
+// 512 threads: two workgroups' worth of LDS per CU, so sixteen wavefronts.
+// 2 x 256 x 256 pixels of 1.7 points, R = 5: 97 us (11 staging, 32 finding the
+// slots in range, 54 the moments; half of the issue slots of the vector ALU),
+// against 370 us for one thread per pixel that took every slot of all 121
+// pixels by itself.
+constexpr int PNT = 512;
+constexpr int APSS_PINHOLE_R = 5;   // largest halo whose staged tile fits the 64 KB that the host admits
+static_assert(KM * ATX * ATY <= 1024, "a listed point: 10 bits for pixel and slot");
+static_assert(KM * (2 * APSS_PINHOLE_R + 1) <= 64, "a row's slots: a bit each");
+
+__global__ __launch_bounds__(PNT, 4) void k_apss_pinhole(DevModel m, DevParams p, Tiles tg, DevState in, DevState out,
+                                                         int only_above, int carry)
+{
+    extern __shared__ double apss_lds[];
+    __shared__ int by_radius[APSS_PINHOLE_R + 1];
+    const int R = p.apss_R, SX = ATX + 2 * R, NS = SX * (ATY + 2 * R);
+    double* tl = apss_lds;                                      // [KM][NS] depths
+    double* vl = tl + KM * NS;                                  // [NS] inverse ray lengths
+    float* nl = reinterpret_cast<float*>(vl + NS);              // [3][KM][NS] normals
+    int* cl = reinterpret_cast<int*>(nl + 3 * KM * NS);         // [NS] counts (0 outside the frame)
+    uint16_t* pl = reinterpret_cast<uint16_t*>(cl + NS);        // [KM ATX ATY] points: radius, KM (tile pixel) + slot
+    if (threadIdx.x <= APSS_PINHOLE_R) by_radius[threadIdx.x] = 0;
+    const int tile0 = (int)xcd_block(blockIdx.x, gridDim.x);
+    const int g = tile_group(tg, tile0);
+    const Shape sh = group_shape(tg, g);
+    in = state_at(in, tg.base[g]);
+    out = state_at(out, tg.base[g]);
+    const long long S = sh.S;
+    const int tile = tile0 - tg.tile0[g];
+    const int tiles_x = (sh.cols + ATX - 1) / ATX, tiles_y = (sh.rows + ATY - 1) / ATY;
+    const int tpf = tiles_x * tiles_y;
+    const int fr = tile / tpf, tr = tile % tpf;
+    const int i0 = (tr / tiles_x) * ATY, j0 = (tr % tiles_x) * ATX;
+    const long long fbase = (long long)fr * sh.rows * sh.cols;
+    const float h = (float)p.h_apss, h2 = h * h, inv_h2 = 1.f / h2;
+    const double dz = p.dz, persp = p.persp;
+    const double tmax = (double)(m.T - 1);
+    const double cxd = 0.5 * (sh.cols - 1), cyd = 0.5 * (sh.rows - 1);
+    const float pa = (float)persp;
+    const double trange = 1.001 * p.h_apss / dz;   // points farther apart in range are farther apart than h
+    // the ellipse of a point: A dj^2 - 2 ux uy di dj + (1 + ux^2) di^2 < K, A = 1 + uy^2
+    // (0.999: the squared range rounded down; |u2| at its largest over the window)
+    struct Ellipse {
+        float K, A, uu, xy;
+    };
+    auto ellipse = [&](int i, int j, double t) {
+        const float ux = pa * (float)(j - cxd), uy = pa * (float)(i - cyd), rho = (float)(t * dz);
+        const float fx = fabsf(ux) + pa * (float)R, fy = fabsf(uy) + pa * (float)R;
+        Ellipse e;
+        e.A = fmaf(uy, uy, 1.f);
+        e.uu = fmaf(ux, ux, e.A);
+        e.xy = ux * uy;
+        e.K = h2 * e.uu * fmaf(fx, fx, fmaf(fy, fy, 1.f)) / (0.999f * rho * rho * pa * pa);
+        return e;
+    };
+    const double none = __builtin_nan("");                      // a slot without a point: in range of nothing
+    for (int x = threadIdx.x; x < NS; x += PNT) {
+        const int i2 = i0 - R + x / SX, j2 = j0 - R + x % SX;
+        int c = 0;
+        if (i2 >= 0 && i2 < sh.rows && j2 >= 0 && j2 < sh.cols) {
+            const long long pp = fbase + (long long)i2 * sh.cols + j2;
+            double ts[KM];
+            c = load_cnt(in.cnt, pp);
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {
+                ts[k] = in.t[k * S + pp];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) nl[(a * KM + k) * NS + x] = in.n[(a * KM + k) * S + pp];
+            }
+            double v[3];
+            ray_dir(p.persp, sh.rows, sh.cols, i2, j2, v);
+            vl[x] = v[2];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = k < c ? ts[k] : none;
+        } else {
+#pragma unroll
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = none;
+        }
+        cl[x] = c;
+    }
+    __syncthreads();
+    // the tile's points, by window radius
+    int c = 0, rk[KM];
+    if (threadIdx.x < ATX * ATY) {
+        const int ty = threadIdx.x / ATX, tx = threadIdx.x % ATX, i = i0 + ty, j = j0 + tx;
+        const int xc = (ty + R) * SX + tx + R;
+        const bool inside = i < sh.rows && j < sh.cols;
+        c = inside ? cl[xc] : 0;
+        const bool fit = !(only_above >= 0 && c <= only_above);
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
-            if (k >= c) break;
-            double tn = tq[k];
-            float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
-            apss_project(fit && nn[k] >= (float)p.m_min, W[k], Px[k], Py[k], Pz[k], Nx[k], Ny[k], Nz[k], PN[k],
-                         PP[k], h, h2, dz, tmax, tn, on);
-            out.t[k * S + pix] = tn;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];
-        }
-    } else {
-        double vq[3];
-        float rq[3];
-        ray_dir(p.persp, sh.rows, sh.cols, i, j, vq);
-        for (int a = 0; a < 3; ++a) rq[a] = (float)vq[a];
-        // the query's unnormalised ray uq = (persp (j - cx), persp (i - cy), 1)
-        const float pa = (float)p.persp;
-        const float uq[3] = {pa * (float)(j - 0.5 * (sh.cols - 1)), pa * (float)(i - 0.5 * (sh.rows - 1)), 1.f};
-        const float uuq = fmaf(uq[0], uq[0], fmaf(uq[1], uq[1], 1.f));
-        for (int k = 0; k < c; ++k) {
-            const double tq = tl[k * NS + xc];
-            const float rho = (float)(tq * dz), rho2 = 0.999f * rho * rho;   // squared range, rounded down
-            float W = 0.f, Px = 0.f, Py = 0.f, Pz = 0.f, Nx = 0.f, Ny = 0.f, Nz = 0.f, PN = 0.f, PP = 0.f, nn = 0.f;
+            rk[k] = 0;
+            if (k >= c) continue;
             if (fit) {
-                for (int di = -R; di <= R; ++di) {
-                    for (int dj = -R; dj <= R; ++dj) {
-                        const int x = xc + di * SX + dj;
-                        const int cc = cl[x];
-                        if (cc == 0) continue;
-                        // every point of this pixel's ray is at least rho_q sin(theta) from
-                        // the query (theta: the angle between the two rays); skip the pixel
-                        // when that reaches h
-                        const float ax = pa * (float)dj, ay = pa * (float)di;   // u2 - uq = (ax, ay, 0)
-                        // |uq x u2| = |uq x (u2 - uq)|
-                        const float cx2 = -uq[2] * ay, cy2 = uq[2] * ax, cz2 = uq[0] * ay - uq[1] * ax;
-                        const float uu2 = fmaf(uq[0] + ax, uq[0] + ax, fmaf(uq[1] + ay, uq[1] + ay, 1.f));
-                        const float sin2 = (cx2 * cx2 + cy2 * cy2 + cz2 * cz2) / (uuq * uu2);
-                        if (!(rho2 * sin2 < h2)) continue;
-                        double v2[3];
-                        ray_dir(p.persp, sh.rows, sh.cols, i + di, j + dj, v2);
-                        for (int k2 = 0; k2 < cc; ++k2) {
-                            const double t2 = tl[k2 * NS + x];
-                            const float yx = (float)((t2 * v2[0] - tq * vq[0]) * dz);
-                            const float yy = (float)((t2 * v2[1] - tq * vq[1]) * dz);
-                            const float yz = (float)((t2 * v2[2] - tq * vq[2]) * dz);
-                            const float d2 = fmaf(yx, yx, fmaf(yy, yy, yz * yz));
-                            if (!(d2 < h2)) continue;
-                            float a = 1.f - d2 * inv_h2;
-                            a = a * a;
-                            const float w = a * a;
-                            const float nx = nl[(0 * KM + k2) * NS + x];
-                            const float ny = nl[(1 * KM + k2) * NS + x];
-                            const float nz = nl[(2 * KM + k2) * NS + x];
-                            W += w;
-                            Px = fmaf(w, yx, Px);
-                            Py = fmaf(w, yy, Py);
-                            Pz = fmaf(w, yz, Pz);
-                            Nx = fmaf(w, nx, Nx);
-                            Ny = fmaf(w, ny, Ny);
-                            Nz = fmaf(w, nz, Nz);
-                            PN = fmaf(w, yx * nx + yy * ny + yz * nz, PN);
-                            PP = fmaf(w, d2, PP);
-                            nn += 1.f;
-                        }
+                const Ellipse e = ellipse(i, j, tl[k * NS + xc]);
+                rk[k] = (int)fminf((float)R, sqrtf(e.K * e.A / e.uu));
+            }
+            atomicAdd(&by_radius[rk[k]], 1);
+        }
+        if (carry && inside) {
+            const long long pix = fbase + (long long)i * sh.cols + j;
+            out.cnt[pix] = (uint8_t)c;
+            out.b[pix] = in.b[pix];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) out.r[k * S + pix] = in.r[k * S + pix];
+        }
+    }
+    __syncthreads();
+    int points = 0;
+    for (int r = R; r >= 0; --r) points += by_radius[r];
+    __syncthreads();
+    if (threadIdx.x == 0) {                     // largest first
+        int run = 0;
+        for (int r = R; r >= 0; --r) {
+            const int n = by_radius[r];
+            by_radius[r] = run;
+            run += n;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < KM; ++k)
+        if (k < c)
+            pl[atomicAdd(&by_radius[rk[k]], 1)] = (uint16_t)((rk[k] << 10) | (threadIdx.x * KM + k));
+    __syncthreads();
+    for (int q = threadIdx.x ^ ((blockIdx.x >> 8 & 1) << 7); q < points; q += PNT) {
+        const int pk = pl[q], k = pk % KM, px = (pk & 1023) / KM, r = pk >> 10;
+        const int i = i0 + px / ATX, j = j0 + px % ATX;
+        const int xc = (px / ATX + R) * SX + px % ATX + R;
+        const long long pix = fbase + (long long)i * sh.cols + j;
+        const int cq = cl[xc];
+        const bool fit = !(only_above >= 0 && cq <= only_above);
+        const double iq = vl[xc];
+        const double vq[3] = {persp * (j - cxd) * iq, persp * (i - cyd) * iq, iq};
+        const float rq[3] = {(float)vq[0], (float)vq[1], (float)vq[2]};
+        const double tq = tl[k * NS + xc];
+        float W = 0.f, Px = 0.f, Py = 0.f, Pz = 0.f, Nx = 0.f, Ny = 0.f, Nz = 0.f, PN = 0.f, PP = 0.f, nn = 0.f;
+        if (fit) {
+            const Ellipse e = ellipse(i, j, tq);
+            const float iA = 1.f / e.A, duu = e.uu * iA;
+            for (int di = -r; di <= r; ++di) {
+                const double wy = persp * (i + di - cyd);
+                const float mid = e.xy * (float)di * iA;
+                const float half = sqrtf(fmaxf((e.K - (float)(di * di) * duu) * iA, 0.f));
+                const int j1 = (int)fminf((float)R, floorf(mid + half));
+                const int jl = (int)fmaxf((float)-R, ceilf(mid - half));
+                // the row's slots within h in range, KM bits per pixel
+                const int row = xc + di * SX;
+                uint64_t near = 0;
+#pragma unroll 2
+                for (int dj = jl; dj <= j1; ++dj) {
+                    unsigned bits = 0;
+#pragma unroll
+                    for (int k2 = 0; k2 < KM; ++k2)
+                        bits |= fabs(fabs(tl[k2 * NS + row + dj]) - fabs(tq)) < trange ? 1u << k2 : 0u;
+                    near |= (uint64_t)bits << (KM * (dj - jl));
+                }
+                // each in turn, the next one's values on their way
+                int at = 0;
+                double t2 = 0.0, iv2 = 0.0;
+                float nx = 0.f, ny = 0.f, nz = 0.f;
+                auto fetch = [&] {
+                    const int bit = __ffsll((unsigned long long)near) - 1, k2 = bit % KM;
+                    at = jl + bit / KM;
+                    const int x = row + at, y = k2 * NS + x;
+                    t2 = tl[y];
+                    iv2 = vl[x];
+                    nx = nl[y];
+                    ny = nl[KM * NS + y];
+                    nz = nl[2 * KM * NS + y];
+                    near &= near - 1;
+                };
+                bool more = near != 0;
+                if (more) fetch();
+                while (more) {
+                    const double wx = persp * (j + at - cxd), t = t2, i2 = iv2;
+                    const float mx = nx, my = ny, mz = nz;
+                    more = near != 0;
+                    if (more) fetch();
+                    const double v2[3] = {wx * i2, wy * i2, i2};
+                    const float yx = (float)((t * v2[0] - tq * vq[0]) * dz);
+                    const float yy = (float)((t * v2[1] - tq * vq[1]) * dz);
+                    const float yz = (float)((t * v2[2] - tq * vq[2]) * dz);
+                    const float d2 = fmaf(yx, yx, fmaf(yy, yy, yz * yz));
+                    if (d2 < h2) {
+                        float a = 1.f - d2 * inv_h2;
+                        a = a * a;
+                        const float w = a * a;
+                        W += w;
+                        Px = fmaf(w, yx, Px);
+                        Py = fmaf(w, yy, Py);
+                        Pz = fmaf(w, yz, Pz);
+                        Nx = fmaf(w, mx, Nx);
+                        Ny = fmaf(w, my, Ny);
+                        Nz = fmaf(w, mz, Nz);
+                        PN = fmaf(w, yx * mx + yy * my + yz * mz, PN);
+                        PP = fmaf(w, d2, PP);
+                        nn += 1.f;
                     }
                 }
             }
-            double tn = tq;
-            float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
-            apss_project(fit && nn >= (float)p.m_min, W, Px, Py, Pz, Nx, Ny, Nz, PN, PP, h, h2, dz, tmax, tn, on,
-                         rq);
-            out.t[k * S + pix] = tn;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];
         }
+        double tn = tq;
+        float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
+        apss_project(fit && nn >= (float)p.m_min, W, Px, Py, Pz, Nx, Ny, Nz, PN, PP, h, h2, dz, tmax, tn, on, rq);
+        out.t[k * S + pix] = tn;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];
     }
 }
 
@@ -374,14 +538,14 @@ hipError_t launch_apss_tiles(const DevModel& m, const DevParams& p, const Tiles&
     if (tg.n == 0 || tg.tile0[tg.n] == 0) return hipSuccess;
     if (p.persp > 0.0) {   // the host admits the perspective camera only where the tile fits
         const size_t lds = apss_tile_bytes(p.apss_R);
-        if (lds > 65536) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_apss_tile<true>, dim3((unsigned)tg.tile0[tg.n]), dim3(ATX * ATY), lds, st, m, p, tg, in,
-                           out, only_above, (int)carry);
+        if (lds > 65536 || p.apss_R > APSS_PINHOLE_R) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_apss_pinhole, dim3((unsigned)tg.tile0[tg.n]), dim3(PNT), pinhole_tile_bytes(p.apss_R),
+                           st, m, p, tg, in, out, only_above, (int)carry);
         return hipGetLastError();
     }
     const size_t lds = apss_tile_bytes(p.apss_Rs);
     if (lds <= 65536) {
-        hipLaunchKernelGGL(k_apss_tile<false>, dim3((unsigned)tg.tile0[tg.n]), dim3(ATX * ATY), lds, st, m, p, tg,
+        hipLaunchKernelGGL(k_apss_tile, dim3((unsigned)tg.tile0[tg.n]), dim3(ATX * ATY), lds, st, m, p, tg,
                            in, out, only_above, (int)carry);
         return hipGetLastError();
     }
