@@ -17,16 +17,16 @@
 // Mapping: a workgroup takes a tile of ATY x ATX pixels of one frame; it stages
 // the counts and every slot of the tile with a halo in LDS in one round of
 // loads (depths in FP64, normals; a second round for the live slots only,
-// after the counts, cost more time than the bytes it saved), then one thread per pixel fits and projects the pixel's
-// points, accumulating the sphere moments over the window from LDS in FP32,
-// in coordinates local to the query (depth differences formed in FP64); under
-// the orthographic map the halo covers only the pixels whose lateral offset
-// stays below h, and each neighbour is read once for all the pixel's slots;
-// under the pinhole camera a thread takes one point (k_apss_pinhole).
+// after the counts, cost more time than the bytes it saved), then one thread
+// per live point, listed by pixel, fits and projects it, accumulating the
+// sphere moments over the window from LDS in FP32, in coordinates local to the
+// query (depth differences formed in FP64); under the orthographic map the
+// halo covers only the pixels whose lateral offset stays below h
+// (apss_moments), under the pinhole camera see k_apss_pinhole.
 // Windows whose staged tile does not fit in 64 KB of LDS take a variant with
 // eight lanes per pixel reading the state from global memory, the partial
 // moment sets meeting in a fixed wavefront-shuffle tree.
-#include "rt3d_dev.h"
+#include "rt3d_points.h"
 
 namespace rt3d {
 
@@ -68,10 +68,14 @@ int apss_staged_halo(double h_apss, double p_xy, int R)
 
 // The orthographic map, staged halo p.apss_Rs.  carry: also copy the count,
 // background and intensities to `out` (else `out` receives only the depths and
-// normals of the live slots).  Five workgroups per CU (96 VGPRs; a few values
-// wait in scratch).
-__global__ __launch_bounds__(ATX * ATY, 5) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in,
-                                                            DevState out, int only_above, int carry)
+// normals of the live slots).  A thread per point leaves no lane to a pixel
+// without points and no slot to wait for another: 636 k pixels of 1.4 points
+// take 41 us (the planes read and written at the rate of a copy would take 22),
+// against 49 us for a thread per pixel that kept the moments of all its slots;
+// 20 k points on a point grid of 80 k pixels 12 us against 17.
+constexpr int APT = 512;
+__global__ __launch_bounds__(APT, 4) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in, DevState out,
+                                                      int only_above, int carry)
 {
     extern __shared__ double apss_lds[];
     const int R = p.apss_Rs, SX = ATX + 2 * R, NS = SX * (ATY + 2 * R);
@@ -92,98 +96,58 @@ __global__ __launch_bounds__(ATX * ATY, 5) void k_apss_tile(DevModel m, DevParam
     const long long fbase = (long long)fr * sh.rows * sh.cols;
     // stage the counts and every slot of the tile and its halo (without
     // waiting for the counts)
-    for (int x = threadIdx.x; x < NS; x += ATX * ATY) {
+    __shared__ int wave_points[ATX * ATY / 64];
+    uint16_t* pl = reinterpret_cast<uint16_t*>(cl + NS);        // [KM ATX ATY] points
+    for (int x = threadIdx.x; x < NS; x += APT) {
         const int i2 = i0 - R + x / SX, j2 = j0 - R + x % SX;
         int c = 0;
         if (i2 >= 0 && i2 < sh.rows && j2 >= 0 && j2 < sh.cols) {
             const long long pp = fbase + (long long)i2 * sh.cols + j2;
+            double ts[KM];
             c = load_cnt(in.cnt, pp);
 #pragma unroll
             for (int k = 0; k < KM; ++k) {
-                tl[k * NS + x] = in.t[k * S + pp];
+                ts[k] = in.t[k * S + pp];
 #pragma unroll
                 for (int a = 0; a < 3; ++a) nl[(a * KM + k) * NS + x] = in.n[(a * KM + k) * S + pp];
             }
+#pragma unroll
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = k < c ? ts[k] : apss_none();
+        } else {
+#pragma unroll
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = apss_none();
         }
         cl[x] = c;
     }
     __syncthreads();
-    const int ty = threadIdx.x / ATX, tx = threadIdx.x % ATX;
-    const int i = i0 + ty, j = j0 + tx;
-    if (i >= sh.rows || j >= sh.cols) return;
-    const long long pix = fbase + (long long)i * sh.cols + j;
-    const int xc = (ty + R) * SX + tx + R;
-    const int c = cl[xc];
-    if (carry) {
-        out.cnt[pix] = (uint8_t)c;
-        out.b[pix] = in.b[pix];
+    int c = 0;
+    if (threadIdx.x < ATX * ATY) {
+        const int ty = threadIdx.x / ATX, tx = threadIdx.x % ATX, i = i0 + ty, j = j0 + tx;
+        const bool inside = i < sh.rows && j < sh.cols;
+        c = inside ? cl[(ty + R) * SX + tx + R] : 0;
+        if (carry && inside) {
+            const long long pix = fbase + (long long)i * sh.cols + j;
+            out.cnt[pix] = (uint8_t)c;
+            out.b[pix] = in.b[pix];
 #pragma unroll
-        for (int k = 0; k < KM; ++k) out.r[k * S + pix] = in.r[k * S + pix];
-    }
-    if (c == 0) return;
-    const bool fit = !(only_above >= 0 && c <= only_above);
-    const float h = (float)p.h_apss, h2 = h * h, inv_h2 = 1.f / h2;
-    const float pxy = (float)p.p_xy;
-    const double dz = p.dz;
-    const double tmax = (double)(m.T - 1);
-    // every live slot of the pixel against each neighbour in turn: the
-    // neighbour's depth and normal are read from LDS once for all slots
-    double tq[KM];
-    float W[KM], Px[KM], Py[KM], Pz[KM], Nx[KM], Ny[KM], Nz[KM], PN[KM], PP[KM], nn[KM];
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        tq[k] = k < c ? tl[k * NS + xc] : 0.0;
-        W[k] = Px[k] = Py[k] = Pz[k] = Nx[k] = Ny[k] = Nz[k] = PN[k] = PP[k] = nn[k] = 0.f;
-    }
-    if (fit) {
-        for (int di = -R; di <= R; ++di) {
-            const float yy = (float)di * pxy;
-            for (int dj = -R; dj <= R; ++dj) {
-                // pixels whose lateral offset alone reaches h hold no neighbour
-                const float yx = (float)dj * pxy;
-                const float dl = fmaf(yx, yx, yy * yy);
-                if (!(dl < h2)) continue;
-                const int x = xc + di * SX + dj;
-                const int cc = cl[x];
-#pragma unroll
-                for (int k2 = 0; k2 < KM; ++k2) {
-                    if (k2 >= cc) break;
-                    const double t2 = tl[k2 * NS + x];
-                    const float nx = nl[(0 * KM + k2) * NS + x];
-                    const float ny = nl[(1 * KM + k2) * NS + x];
-                    const float nz = nl[(2 * KM + k2) * NS + x];
-                    const float yn = fmaf(yx, nx, yy * ny);
-#pragma unroll
-                    for (int k = 0; k < KM; ++k) {
-                        if (k >= c) break;
-                        const float yz = (float)((t2 - tq[k]) * dz);
-                        const float d2 = fmaf(yz, yz, dl);
-                        if (!(d2 < h2)) continue;
-                        float a = 1.f - d2 * inv_h2;
-                        a = a * a;
-                        const float w = a * a;
-                        W[k] += w;
-                        Px[k] = fmaf(w, yx, Px[k]);
-                        Py[k] = fmaf(w, yy, Py[k]);
-                        Pz[k] = fmaf(w, yz, Pz[k]);
-                        Nx[k] = fmaf(w, nx, Nx[k]);
-                        Ny[k] = fmaf(w, ny, Ny[k]);
-                        Nz[k] = fmaf(w, nz, Nz[k]);
-                        PN[k] = fmaf(w, fmaf(yz, nz, yn), PN[k]);
-                        PP[k] = fmaf(w, d2, PP[k]);
-                        nn[k] += 1.f;
-                    }
-                }
-            }
+            for (int k = 0; k < KM; ++k) out.r[k * S + pix] = in.r[k * S + pix];
         }
     }
-#pragma unroll
-    for (int k = 0; k < KM; ++k) {
-        if (k >= c) break;
-        double tn = tq[k];
+    const int points = list_points(c, wave_points, pl);
+    const float h = (float)p.h_apss, h2 = h * h;
+    const double dz = p.dz, reach = 1.001 * p.h_apss / dz;
+    for (int q = threadIdx.x; q < points; q += APT) {
+        const int pk = pl[q], k = pk % KM, px = pk / KM, ty = px / ATX, tx = px % ATX;
+        const int xc = (ty + R) * SX + tx + R;
+        const long long pix = fbase + (long long)(i0 + ty) * sh.cols + j0 + tx;
+        const int cq = cl[xc];
+        double tn = tl[k * NS + xc];
         float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
-        apss_project(fit && nn[k] >= (float)p.m_min, W[k], Px[k], Py[k], Pz[k], Nx[k], Ny[k], Nz[k], PN[k],
-                     PP[k], h, h2, dz, tmax, tn, on);
+        if (!(only_above >= 0 && cq <= only_above)) {
+            const Moments v = apss_moments(tl, nl, NS, SX, xc, R, h2, (float)p.p_xy, dz, reach, tn);
+            apss_project(v.nn >= (float)p.m_min, v.W, v.Px, v.Py, v.Pz, v.Nx, v.Ny, v.Nz, v.PN, v.PP, h, h2, dz,
+                         (double)(m.T - 1), tn, on);
+        }
         out.t[k * S + pix] = tn;
 #pragma unroll
         for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];
@@ -543,9 +507,9 @@ hipError_t launch_apss_tiles(const DevModel& m, const DevParams& p, const Tiles&
                            st, m, p, tg, in, out, only_above, (int)carry);
         return hipGetLastError();
     }
-    const size_t lds = apss_tile_bytes(p.apss_Rs);
-    if (lds <= 65536) {
-        hipLaunchKernelGGL(k_apss_tile, dim3((unsigned)tg.tile0[tg.n]), dim3(ATX * ATY), lds, st, m, p, tg,
+    const size_t lds = apss_tile_bytes(p.apss_Rs) + KM * ATX * ATY * sizeof(uint16_t);
+    if (p.apss_Rs <= APSS_ROW && lds <= 65536) {
+        hipLaunchKernelGGL(k_apss_tile, dim3((unsigned)tg.tile0[tg.n]), dim3(APT), lds, st, m, p, tg,
                            in, out, only_above, (int)carry);
         return hipGetLastError();
     }

@@ -204,7 +204,7 @@ __device__ __forceinline__ void apss_1(const DevModel& m, const DevParams& p, co
         }
         double tn = tq;
         float on[3] = {in.n[(0 * KM + k) * S + pix], in.n[(1 * KM + k) * S + pix], in.n[(2 * KM + k) * S + pix]};
-        apss_project(nn >= (float)p.m_min, W, Px, Py, Pz, Nx, Ny, Nz, PN, PP, h, h2, dz, tmax, tn, on);
+        apss_project<true>(nn >= (float)p.m_min, W, Px, Py, Pz, Nx, Ny, Nz, PN, PP, h, h2, dz, tmax, tn, on);
         out.t[k * S + pix] = tn;
 #pragma unroll
         for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];

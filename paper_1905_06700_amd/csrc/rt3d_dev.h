@@ -325,26 +325,29 @@ __device__ __forceinline__ void merge_points(double (&t)[KM], float (&r)[KM], fl
 // Sphere fit from the moments and projection of the query along its line of
 // sight: updates depth t (bins) and normal n when the fit is usable.  ray:
 // the unit line of sight under the pinhole camera (nullptr: +Z, the
-// orthographic map); the normal faces the sensor (against the ray).
+// orthographic map); the normal faces the sensor (against the ray).  The sums
+// are written as fused multiply-adds, so that every kernel rounds them alike
+// (XFIRST: the x products innermost, the order of the one-launch loop).
+template <bool XFIRST = false>
 __device__ __forceinline__ void apss_project(bool ok, float W, float Px, float Py, float Pz, float Nx, float Ny,
                                              float Nz, float PN, float PP, float h, float h2, double dz, double tmax,
                                              double& t, float (&n)[3], const float* ray = nullptr)
 {
     if (!ok) return;
     const float invW = 1.f / W;
-    const float PdP = Px * Px + Py * Py + Pz * Pz;
-    const float PdN = Px * Nx + Py * Ny + Pz * Nz;
+    const float PdP = fmaf(Pz, Pz, XFIRST ? fmaf(Py, Py, Px * Px) : fmaf(Px, Px, Py * Py));
+    const float PdN = fmaf(Pz, Nz, XFIRST ? fmaf(Py, Ny, Px * Nx) : fmaf(Px, Nx, Py * Ny));
     const float D = PP - PdP * invW;
     if (!(D > 1e-12f * W * h2)) return;
     const float u4 = 0.5f * (PN - PdN * invW) / D;
     const float ulx = (Nx - 2.f * u4 * Px) * invW;
     const float uly = (Ny - 2.f * u4 * Py) * invW;
     const float ulz = (Nz - 2.f * u4 * Pz) * invW;
-    const float u0 = -(ulx * Px + uly * Py + ulz * Pz + u4 * PP) * invW;
+    const float u0 = -fmaf(u4, PP, fmaf(ulz, Pz, fmaf(ulx, Px, uly * Py))) * invW;
     const float nul = sqrtf(ulx * ulx + uly * uly + ulz * ulz);
     const float bz = ray ? ulx * ray[0] + uly * ray[1] + ulz * ray[2] : ulz;   // ul along the line of sight
     if (!(fabsf(bz) > 1e-6f * nul)) return;
-    const float disc = bz * bz - 4.f * u4 * u0;
+    const float disc = ray ? fmaf(bz, bz, -4.f * u4 * u0) : fmaf(-4.f * u4, u0, bz * bz);
     float sroot;
     if (disc < 0.f) sroot = -bz / (2.f * u4);
     else sroot = -2.f * u0 / (bz + copysignf(sqrtf(disc), bz));
