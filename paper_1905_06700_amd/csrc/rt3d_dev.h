@@ -213,47 +213,63 @@ __device__ __forceinline__ void irf_eval(const DevModel& m, int tb, int a, float
 
 // S(t) = sum over bins of h(tb - t) and dS/dt = -sum h'(tb - t) (every lag
 // shares the local parameter s).  Inside the domain, for an IRF whose segments
-// never dip below zero, the closed-form cubic of all segments; else by direct
-// summation over the segments that fall inside [0, T).
-// Lane `part` of `parts` sums the segments k0 + part, k0 + part + parts, ...
-// (parts = 1: the whole sum).
-// tab: the piecewise cubic's table (m.s_tab, or a copy of it in LDS).
-__device__ __forceinline__ void s_eval_tab(const DevModel& m, const double* tab, double t, float& S, float& Sp,
-                                           int part = 0, int parts = 1)
+// never dip below zero, the closed-form cubic of all segments (s_cubic); else by
+// direct summation over the segments that fall inside [0, T) (s_direct: lane
+// `part` of `parts` sums the segments k0 + part, k0 + part + parts, ...).
+struct SPlace {
+    int k0, k1;   // segment k holds bin tb = k + a - o + sh; keep 0 <= tb <= T - 1
+    float s;
+};
+
+__device__ __forceinline__ SPlace s_place(const DevModel& m, double t)
 {
     const double fl = floor(t);
     const int a = (int)fl;
     const float f = (float)(t - fl);
     const int sh = f > 0.f ? 1 : 0;
-    const float s = sh ? 1.f - f : 0.f;
-    // segment k holds bin tb = k + a - o + sh; keep 0 <= tb <= T - 1
-    const int k0 = max(-1, m.o - a - sh), k1 = min(m.L - 1, m.T - 1 + m.o - a - sh);
-    if (m.s_np > 0 && k0 == -1 && k1 == m.L - 1) {   // every segment: the piecewise cubic (by part 0)
-        S = 0.f;
-        Sp = 0.f;
-        if (part == 0) {
-            if (s == 0.f) {
-                S = (float)m.s_v0;
-                Sp = (float)(-m.s_d0);
-            } else if (s == 1.f) {
-                S = (float)m.s_v1;
-                Sp = (float)(-m.s_d1);
-            } else {
-                const double sd = (double)s;
-                int i = 0;
-                while (i + 1 < m.s_np && sd >= tab[i + 1]) ++i;
-                const double* c = tab + (m.s_np + 1) + 4 * i;
-                S = (float)(((c[3] * sd + c[2]) * sd + c[1]) * sd + c[0]);
-                Sp = (float)(-((3.0 * c[3] * sd + 2.0 * c[2]) * sd + c[1]));
-            }
-        }
-        return;
+    SPlace v;
+    v.s = sh ? 1.f - f : 0.f;
+    v.k0 = max(-1, m.o - a - sh);
+    v.k1 = min(m.L - 1, m.T - 1 + m.o - a - sh);
+    return v;
+}
+
+// Whether the cubic holds at t.
+__device__ __forceinline__ bool s_whole(const DevModel& m, double t)
+{
+    const SPlace v = s_place(m, t);
+    return m.s_np > 0 && v.k0 == -1 && v.k1 == m.L - 1;
+}
+
+// tab: the piecewise cubic's table (m.s_tab, or a copy of it in LDS).
+__device__ __forceinline__ void s_cubic(const DevModel& m, const double* tab, double t, float& S, float& Sp)
+{
+    const float s = s_place(m, t).s;
+    if (s == 0.f) {
+        S = (float)m.s_v0;
+        Sp = (float)(-m.s_d0);
+    } else if (s == 1.f) {
+        S = (float)m.s_v1;
+        Sp = (float)(-m.s_d1);
+    } else {
+        const double sd = (double)s;
+        int i = 0;                                   // breakpoints at or below s (ascending)
+#pragma unroll 4
+        for (int j = 1; j < m.s_np; ++j) i += sd >= tab[j] ? 1 : 0;
+        const double* c = tab + (m.s_np + 1) + 4 * i;
+        S = (float)(((c[3] * sd + c[2]) * sd + c[1]) * sd + c[0]);
+        Sp = (float)(-((3.0 * c[3] * sd + 2.0 * c[2]) * sd + c[1]));
     }
+}
+
+__device__ __forceinline__ void s_direct(const DevModel& m, double t, float& S, float& Sp, int part, int parts)
+{
+    const SPlace v = s_place(m, t);
     float acc = 0.f, accp = 0.f;
 #pragma unroll 4
-    for (int k = k0 + part; k <= k1; k += parts) {
+    for (int k = v.k0 + part; k <= v.k1; k += parts) {
         float h, hp;
-        cr_segment(m.cr[k + 1], s, h, hp);
+        cr_segment(m.cr[k + 1], v.s, h, hp);
         acc += h;
         accp -= hp;
     }
@@ -261,10 +277,14 @@ __device__ __forceinline__ void s_eval_tab(const DevModel& m, const double* tab,
     Sp = accp;
 }
 
+// Lane `part` of `parts`: the cubic by part 0, the direct sum by its share.
 __device__ __forceinline__ void s_eval(const DevModel& m, double t, float& S, float& Sp, int part = 0,
                                        int parts = 1)
 {
-    s_eval_tab(m, m.s_tab, t, S, Sp, part, parts);
+    S = 0.f;
+    Sp = 0.f;
+    if (!s_whole(m, t)) s_direct(m, t, S, Sp, part, parts);
+    else if (part == 0) s_cubic(m, m.s_tab, t, S, Sp);
 }
 
 __device__ __forceinline__ int ent_bin(uint32_t e) { return (int)(e >> 16); }
