@@ -314,7 +314,10 @@ rt3d_status rt3d_query(rt3d_ctx* ctx, void* hip_stream, rt3d_stats* st);
  * waits for the recorded events, returns the summed milliseconds and the
  * number of timed launches, and clears them.  The events are created once and
  * reused (at most 4096 launches are kept between reads; later ones are not
- * timed).  E_INVALID for an unknown id, E_DEVICE on a HIP failure. */
+ * timed).  Batches that run an iteration in three launches of several steps
+ * each run the steps one by one while a group of the iteration (DEPTH to
+ * BFILTER) is timed; results are the same bit for bit.  E_INVALID for an
+ * unknown id, E_DEVICE on a HIP failure. */
 #define RT3D_KERNEL_COMPACT   0   /* histogram -> active bins (count, scan, fill) */
 #define RT3D_KERNEL_INIT      1   /* log-matched-filter initialisation */
 #define RT3D_KERNEL_NORMALS   2   /* initial normals */

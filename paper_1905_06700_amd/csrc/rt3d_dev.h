@@ -148,8 +148,9 @@ __host__ __device__ inline Shape group_shape(const Tiles& tg, int g)
     return sh;
 }
 
-// Appends group (base, sh) to tg; false when tg is full.
-inline bool tiles_add(Tiles& tg, long long base, const Shape& sh)
+// Appends group (base, sh) to tg, in tiles of tx columns x ty rows; false when tg
+// is full.
+inline bool tiles_add(Tiles& tg, long long base, const Shape& sh, int tx = TILE, int ty = TILE)
 {
     if (tg.n == 0) tg.tile0[0] = 0;
     if (tg.n >= TILE_GROUPS) return false;
@@ -159,7 +160,7 @@ inline bool tiles_add(Tiles& tg, long long base, const Shape& sh)
     tg.rows[g] = sh.rows;
     tg.cols[g] = sh.cols;
     tg.S = sh.S;
-    const long long nt = (long long)sh.F * ((sh.rows + TILE - 1) / TILE) * ((sh.cols + TILE - 1) / TILE);
+    const long long nt = (long long)sh.F * ((sh.rows + ty - 1) / ty) * ((sh.cols + tx - 1) / tx);
     tg.tile0[g + 1] = tg.tile0[g] + (int)nt;
     return true;
 }
@@ -679,6 +680,26 @@ hipError_t launch_ifilter_tiles(const DevParams& p, const Tiles& tg, DevState in
 // dst = the filtered src floored at b_min, per group (src, dst, tmp: the batch's arrays)
 hipError_t launch_bfilter_tiles(const float* w, int rb, const Tiles& tg, float b_min, const float* src, float* dst,
                                 float* tmp, hipStream_t st);
+// An iteration in three launches (k_iter.hip): part 0 the background filter of
+// the iteration before (filter) and the depth step on `in`; 1 APSS, merge and
+// intensity step; 2 intensity filter and background step (into btmp).  out: `in`
+// with the other buffers of the planes that part 1 (t, n, cnt) and part 2 (t, r,
+// cnt) write.  Tiles of iter_tiles_add; one IRF class, orthographic map.
+struct IterArgs {
+    DevModel m;
+    DevParams p;
+    const uint32_t *off, *ent;
+    const float* gain;
+    DevState in, out;
+    float* btmp;
+    const float* w;       // background filter: 2 rb + 1 taps
+    int rb;
+    long long P;
+    bool filter;
+};
+bool iter_fits(const DevParams& p, int rb);
+bool iter_tiles_add(Tiles& tg, long long base, const Shape& sh);
+hipError_t launch_iter(const IterArgs& a, const Tiles& tg, int part, hipStream_t st);
 hipError_t launch_apss(const DevModel& m, const DevParams& p, const Shape& sh, DevState in,
                        DevState out, int only_above, hipStream_t st);
 hipError_t launch_merge(const DevModel& m, const DevParams& p, const Shape& sh, DevState s, hipStream_t st);

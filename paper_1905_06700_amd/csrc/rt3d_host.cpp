@@ -646,6 +646,69 @@ CnnBuffers cnn_at(const CnnBuffers& b, long long base)
     return r;
 }
 
+// Whether the iterations run as three launches on tiles (k_iter.hip): APSS on
+// the orthographic map, one IRF, no step of the iteration timed by itself, and
+// at most ITER_PIXELS pixels.  Whole calls, three launches against six, us:
+// 20 k pixels 791 / 990, 40 k 965 / 1056, 80 k 1452 / 1447 at 42 entries per
+// pixel; 57 k 1276 / 1339, 80 k 1582 / 1614, 159 k 1881 / 1920 at 4; 262 k
+// pixels, one iteration, 138 / 126: above, the steps' own kernels with more
+// workgroups per CU are the faster ones.
+constexpr long long ITER_PIXELS = LANES8_PIXELS;
+
+bool iter_eligible(const rt3d_ctx* c, const Shape& sh, const uint8_t* cls)
+{
+    const bool timed = c->prof_id == RT3D_KERNEL_DEPTH || c->prof_id == RT3D_KERNEL_APSS ||
+                       c->prof_id == RT3D_KERNEL_INTENSITY || c->prof_id == RT3D_KERNEL_IFILTER ||
+                       c->prof_id == RT3D_KERNEL_BKG || c->prof_id == RT3D_KERNEL_BFILTER;
+    return c->p.denoiser == RT3D_DENOISE_APSS && !cls && !(c->p.persp > 0) && !timed && sh.P <= ITER_PIXELS &&
+           iter_fits(dev_params(c), c->rb);
+}
+
+// n_iter such iterations, `cur` and `alt` as in iterate(); the last background
+// filter by its own kernel.
+rt3d_status iterate_tiles(rt3d_ctx* c, const Shape& sh, const std::vector<Group>& groups, const uint32_t* off,
+                          const uint32_t* ent, const float* gain, DevState& cur, DevState& alt, float* btmp,
+                          int n_iter, hipStream_t st)
+{
+    std::vector<Tiles> small(1, Tiles{}), tiles(1, Tiles{});
+    for (const Group& g : groups) {
+        if (!iter_tiles_add(small.back(), g.base, g.sh)) {
+            small.push_back(Tiles{});
+            iter_tiles_add(small.back(), g.base, g.sh);
+        }
+        if (!tiles_add(tiles.back(), g.base, g.sh)) {
+            tiles.push_back(Tiles{});
+            tiles_add(tiles.back(), g.base, g.sh);
+        }
+    }
+    IterArgs a{dev_model(c), dev_params(c), off, ent, gain, cur, cur, btmp, c->d_bw, c->rb, sh.P, false};
+    for (int it = 0; it < n_iter; ++it) {
+        a.in = cur;
+        a.filter = it > 0;
+        for (const Tiles& tg : small) RT3D_HIP(c, launch_iter(a, tg, 0, st));
+        a.out = cur;
+        a.out.t = alt.t;
+        a.out.n = alt.n;
+        a.out.cnt = alt.cnt;
+        for (const Tiles& tg : small) RT3D_HIP(c, launch_iter(a, tg, 1, st));
+        std::swap(cur.t, alt.t);
+        std::swap(cur.n, alt.n);
+        std::swap(cur.cnt, alt.cnt);
+        a.in = a.out = cur;
+        a.out.t = alt.t;
+        a.out.r = alt.r;
+        a.out.cnt = alt.cnt;
+        for (const Tiles& tg : small) RT3D_HIP(c, launch_iter(a, tg, 2, st));
+        std::swap(cur.t, alt.t);
+        std::swap(cur.r, alt.r);
+        std::swap(cur.cnt, alt.cnt);
+    }
+    if (n_iter > 0)
+        for (const Tiles& tg : tiles)
+            RT3D_HIP(c, launch_bfilter_tiles(c->d_bw, c->rb, tg, (float)c->p.b_min, btmp, cur.b, alt.b, st));
+    return RT3D_OK;
+}
+
 // One iteration on the state whose planes `cur` points at; `alt` holds the
 // other buffer of each plane.  Kernels that read neighbours' values write the
 // planes they change to the other buffer (APSS: depths and normals; the
@@ -1107,10 +1170,15 @@ rt3d_status rt3d_reconstruct(rt3d_ctx* c, const rt3d_input* in, rt3d_output* out
                     launch_loop(m, p, sh, off, ent, in->gain, w.A, w.B, w.btmp, c->d_bw, c->rb, c->p.n_iter, st));
     } else {
         DevState cur = w.A, alt = w.B;
-        for (int it = 0; it < c->p.n_iter; ++it) {
-            s = iterate(c, sh, groups, off, ent, in->gain, cur, alt, w.btmp, &w.cnn, cls, st, w.cls_list,
-                        w.cls_meta);
+        if (iter_eligible(c, sh, cls)) {
+            s = iterate_tiles(c, sh, groups, off, ent, in->gain, cur, alt, w.btmp, c->p.n_iter, st);
             if (s != RT3D_OK) return s;
+        } else {
+            for (int it = 0; it < c->p.n_iter; ++it) {
+                s = iterate(c, sh, groups, off, ent, in->gain, cur, alt, w.btmp, &w.cnn, cls, st, w.cls_list,
+                            w.cls_meta);
+                if (s != RT3D_OK) return s;
+            }
         }
         s = settle(c, sh, cur, w.A, st);
         if (s != RT3D_OK) return s;
@@ -1442,6 +1510,26 @@ rt3d_status rt3d_debug_step(rt3d_ctx* c, int32_t step, const uint32_t* off, cons
         break;
     }
     if (step < 0 || step > RT3D_STEP_ITERATION) return fail(c, RT3D_E_INVALID, "unknown step");
+    if (step == RT3D_STEP_ITERATION) {
+        Workspace w;
+        rt3d_status s = need_ws(c, sh.P, w);
+        if (s != RT3D_OK) return s;
+        const bool small = iter_eligible(c, sh, cls);
+        DevState cur = O, alt = w.B;
+        if (c->p.denoiser == RT3D_DENOISE_APSS) {
+            // the planes that change buffers an odd number of times start in
+            // the workspace, so that the iteration leaves every plane in O
+            std::swap(cur.n, alt.n);
+            std::swap(cur.r, alt.r);
+            if (!small) std::swap(cur.cnt, alt.cnt);
+        }
+        RT3D_HIP(c, launch_copy_state(sh, dev_state(in), cur, st));
+        const std::vector<Group> groups{Group{0, sh}};
+        s = small ? iterate_tiles(c, sh, groups, off, ent, gain, cur, alt, w.btmp, 1, st)
+                  : iterate(c, sh, groups, off, ent, gain, cur, alt, w.btmp, &w.cnn, cls, st);
+        if (s != RT3D_OK) return s;
+        return settle(c, sh, cur, O, st);
+    }
     RT3D_HIP(c, launch_copy_state(sh, dev_state(in), O, st));
     switch (step) {
     case RT3D_STEP_DEPTH:
@@ -1468,15 +1556,6 @@ rt3d_status rt3d_debug_step(rt3d_ctx* c, int32_t step, const uint32_t* off, cons
         RT3D_HIP(c, launch_bfilter(c->d_bw, c->rb, sh, (float)c->p.b_min, O.b, w.btmp, w.B.b, st));
         RT3D_HIP(c, hipMemcpyAsync(O.b, w.btmp, sizeof(float) * sh.P, hipMemcpyDeviceToDevice, st));
         return RT3D_OK;
-    }
-    case RT3D_STEP_ITERATION: {
-        Workspace w;
-        rt3d_status s = need_ws(c, sh.P, w);
-        if (s != RT3D_OK) return s;
-        DevState cur = O, alt = w.B;
-        s = iterate(c, sh, std::vector<Group>{Group{0, sh}}, off, ent, gain, cur, alt, w.btmp, &w.cnn, cls, st);
-        if (s != RT3D_OK) return s;
-        return settle(c, sh, cur, O, st);
     }
     default:
         return fail(c, RT3D_E_INVALID, "unknown step");
