@@ -37,6 +37,21 @@ __device__ __forceinline__ int list_points(int c, int (&wave_points)[4], uint16_
     return points;
 }
 
+// The slots of pixels row - R .. row + R closer in depth than reach: bit
+// KM (dj + R) + slot.
+__device__ __forceinline__ uint64_t near_slots(const double* tl, int NS, int row, int R, double reach, double tq)
+{
+    uint64_t near = 0;
+#pragma unroll 3
+    for (int dj = -R; dj <= R; ++dj) {
+        unsigned bits = 0;
+#pragma unroll
+        for (int k = 0; k < KM; ++k) bits |= fabs(tl[k * NS + row + dj] - tq) < reach ? 1u << k : 0u;
+        near |= (uint64_t)bits << (KM * (dj + R));
+    }
+    return near;
+}
+
 struct Moments {
     float W, Px, Py, Pz, Nx, Ny, Nz, PN, PP, nn;
 };
@@ -55,14 +70,7 @@ __device__ __forceinline__ Moments apss_moments(const double* tl, const float* n
     for (int di = -R; di <= R; ++di) {
         const float yy = (float)di * pxy;
         const int row = xc + di * SX;
-        uint64_t near = 0;
-#pragma unroll 3
-        for (int dj = -R; dj <= R; ++dj) {
-            unsigned bits = 0;
-#pragma unroll
-            for (int k = 0; k < KM; ++k) bits |= fabs(tl[k * NS + row + dj] - tq) < reach ? 1u << k : 0u;
-            near |= (uint64_t)bits << (KM * (dj + R));
-        }
+        uint64_t near = near_slots(tl, NS, row, R, reach, tq);
         int at = 0;
         double t2 = 0.0;
         float nx = 0.f, ny = 0.f, nz = 0.f;
