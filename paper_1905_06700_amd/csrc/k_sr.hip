@@ -19,11 +19,19 @@
 // Lane u holds the points of the block's point-grid pixel u in registers
 // (s <= 4, so s^2 <= 16 lanes); the block's points are also staged in LDS.
 // The pixel's entries go through 16 at a time, one per lane: a lane
-// evaluates lambda of its entry over the staged points and leaves
-// z/(g lambda) and the bin in LDS; then every lane adds the batch's
-// z h'/lambda and z h/lambda to each of its points.  The background's
-// sum z/lambda is a sum over the sixteen lanes.
-#include "rt3d_dev.h"
+// evaluates lambda of its entry over the staged points and, when the entry lies
+// in some point's support, leaves z/(g lambda) and the bin in LDS; then every
+// lane adds the batch's z h'/lambda and z h/lambda to each of its points.  The
+// background's sum z/lambda is a sum over the sixteen lanes.
+// A frame's lidar pixels fill two wavefronts per SIMD, so the time is the chain
+// of reads: segments and the cubic's table in LDS, several points' (entries')
+// segments read at once, the next batch of entries on its way.  8 frames of
+// 32 x 32 lidar pixels, 3 x 3 point-grid pixels each: 11 us a step (8 us the
+// background's) and no launch for the merge, against 15 us (10 us) and 5 us with
+// the segments read from memory one point, one entry after the other.
+#include "rt3d_steps.h"
+
+#include <type_traits>
 
 namespace rt3d {
 
@@ -32,8 +40,9 @@ namespace rt3d {
 constexpr int SR_GROUP = 16;
 constexpr int SR_GROUPS = 16;
 
-// What a launch of k_sr_step computes.
-enum SrWork { SR_DEPTH, SR_INTENSITY, SR_BKG, SR_GRADIENTS };
+// What a launch of k_sr_step computes (SR_MERGE_INTENSITY: the in-pixel merge,
+// then the intensity step).
+enum SrWork { SR_DEPTH, SR_INTENSITY, SR_MERGE_INTENSITY, SR_BKG, SR_GRADIENTS };
 
 // Orders a wavefront's LDS writes before its reads (and reads before the next writes).
 __device__ __forceinline__ void sr_sync()
@@ -47,15 +56,41 @@ __device__ __forceinline__ void sr_sync()
 // pixel p, for frames of rows x cols lidar pixels.
 __device__ __forceinline__ long long sr_fine(long long p, int u, int s, int rows, int cols)
 {
-    const long long npf = (long long)rows * cols;
-    const long long f = p / npf;
-    const long long rem = p - f * npf;
-    const long long i = rem / cols, j = rem - i * cols;
-    const long long fi = i * s + u / s, fj = j * s + u % s;
-    return (f * rows * s + fi) * ((long long)cols * s) + fj;
+    // (32-bit divisions: pixels of both grids total below 2^31)
+    const uint32_t row = (uint32_t)p / (uint32_t)cols, j = (uint32_t)p - row * (uint32_t)cols;   // f rows + i
+    const uint32_t du = (uint32_t)u / (uint32_t)s, dv = (uint32_t)u - du * (uint32_t)s;
+    return (long long)(row * (uint32_t)s + du) * ((long long)cols * s) + j * (uint32_t)s + dv;
 }
 
-template <SrWork WHICH>
+// h and h' at bin tb of a point with anchor a and fraction f, the segment read
+// whether or not the bin lies in the support (any place of the table then), so
+// that the reads of several points or bins are in flight together.  The values
+// of irf_eval_t; returns whether it does.
+__device__ __forceinline__ bool sr_irf(const float4* cr, int L, int o, int tb, int a, float f, float& h, float& hp)
+{
+    const int sh = f > 0.f ? 1 : 0;
+    const float s = sh ? 1.f - f : 0.f;
+    const int lo = 1 - sh;
+    const int idx = tb - a + o + lo;
+    const bool in = (unsigned)(idx - lo) <= (unsigned)(L - lo);
+    cr_segment(cr[in ? idx : 0], s, h, hp);
+    h = in ? h : 0.f;
+    hp = in ? hp : 0.f;
+    return in;
+}
+
+// Inclusive prefix sum over each row of 16 lanes.
+__device__ __forceinline__ int sr_scan(int v)
+{
+    uint32_t x = (uint32_t)v;
+    x += dpp_or_zero<0x111>(x);
+    x += dpp_or_zero<0x112>(x);
+    x += dpp_or_zero<0x114>(x);
+    x += dpp_or_zero<0x118>(x);
+    return (int)x;
+}
+
+template <SrWork WHICH, bool TLDS>
 __global__ __launch_bounds__(SR_GROUP * SR_GROUPS) void k_sr_step(DevModel m, DevParams p, Shape lid, int s,
                                                                  long long Pf, const uint32_t* __restrict__ off,
                                                                  const uint32_t* __restrict__ ent,
@@ -63,11 +98,10 @@ __global__ __launch_bounds__(SR_GROUP * SR_GROUPS) void k_sr_step(DevModel m, De
                                                                  float* __restrict__ bdst, float* __restrict__ gt,
                                                                  float* __restrict__ gr, float* __restrict__ gb)
 {
-    __shared__ int s_a[SR_GROUPS][SR_GROUP * KM];
-    __shared__ float s_f[SR_GROUPS][SR_GROUP * KM];
-    __shared__ float s_r[SR_GROUPS][SR_GROUP * KM];
-    __shared__ float s_w[SR_GROUPS][SR_GROUP];
-    __shared__ int s_tb[SR_GROUPS][SR_GROUP];
+    __shared__ float4 s_pt[SR_GROUPS][SR_GROUP * KM];       // anchor (bits), fraction, intensity
+    __shared__ float2 s_wt[SR_GROUPS][SR_GROUP];            // z / (g lambda), bin (bits)
+    __shared__ float4 crl[TLDS ? STEP_CR_LDS : 1];
+    __shared__ double stl[STEP_STAB_LDS];
     const int g = (int)(threadIdx.x / SR_GROUP), u = (int)(threadIdx.x % SR_GROUP);
     const long long pix = (long long)blockIdx.x * SR_GROUPS + g;
     const bool valid = pix < lid.P;                 // the whole group
@@ -78,23 +112,18 @@ __global__ __launch_bounds__(SR_GROUP * SR_GROUPS) void k_sr_step(DevModel m, De
     PixPoints pts;
     load_points(st, Pf, q, pts);
     if (!in_block) pts.c = 0;
+    if (WHICH == SR_MERGE_INTENSITY && in_block) merge_lane(st, Pf, p, q, 0, pts);
+    const uint32_t o0 = off[pq], o1 = off[pq + 1];
     const float G = valid ? gain_at(gain, pq) : 0.f;
     const float bb = st.b[pq];
+    const float4* cr = stage_segments<TLDS, WHICH != SR_BKG>(m, crl, stl);
     const bool live = G > 0.f;                      // group-uniform
     // the block's points staged in LDS, lane after lane (prefix of the counts in the group)
-    int before = 0, np = 0;
-    for (int v = 0; v < SR_GROUP; ++v) {
-        const int cv = __shfl(pts.c, (int)(threadIdx.x & ~(SR_GROUP - 1)) + v, 64);
-        before += v < u ? cv : 0;
-        np += cv;
-    }
+    const int upto = sr_scan(pts.c), np = __shfl(upto, (int)(threadIdx.x & ~(SR_GROUP - 1)) + SR_GROUP - 1, 64);
 #pragma unroll
     for (int k = 0; k < KM; ++k)
-        if (k < pts.c) {
-            s_a[g][before + k] = pts.a[k];
-            s_f[g][before + k] = pts.f[k];
-            s_r[g][before + k] = pts.r[k];
-        }
+        if (k < pts.c)
+            s_pt[g][upto - pts.c + k] = make_float4(__int_as_float(pts.a[k]), pts.f[k], pts.r[k], 0.f);
     sr_sync();
     float sh[KM], shp[KM], sz = 0.f;
 #pragma unroll
@@ -102,41 +131,61 @@ __global__ __launch_bounds__(SR_GROUP * SR_GROUPS) void k_sr_step(DevModel m, De
         sh[k] = 0.f;
         shp[k] = 0.f;
     }
-    const uint32_t e0 = live ? off[pq] : 0u, e1 = live ? off[pq + 1] : 0u;
+    const uint32_t e0 = live ? o0 : 0u, e1 = live ? o1 : 0u;
     const float invG = live ? 1.f / G : 0.f;
+    const int cmax = wave_max_count(pts.c);
+    uint32_t next = e0 + (uint32_t)u < e1 ? ent[e0 + (uint32_t)u] : 0u;
     for (uint32_t eb = e0; eb < e1; eb += SR_GROUP) {   // the same trip count on the group's lanes
         const uint32_t x = eb + (uint32_t)u;
         const bool on = x < e1;
-        const uint32_t v = on ? ent[x] : 0u;
+        const uint32_t v = next;
+        next = x + SR_GROUP < e1 ? ent[x + SR_GROUP] : 0u;
         const int tb = ent_bin(v);
         float lam = bb;
+        bool hit = false;
+#pragma unroll 4
         for (int n = 0; n < np; ++n) {
+            const float4 pt = s_pt[g][n];
             float h, hp;
-            irf_eval(m, tb, s_a[g][n], s_f[g][n], h, hp);
-            lam = fmaf(s_r[g][n], h, lam);
+            hit |= sr_irf(cr, m.L, m.o, tb, __float_as_int(pt.x), pt.y, h, hp);
+            lam = fmaf(pt.z, h, lam);
         }
         const float w = on ? (float)ent_cnt(v) * invG * __builtin_amdgcn_rcpf(lam) : 0.f;
         sz += w;
         if (WHICH != SR_BKG) {
-            s_w[g][u] = w;
-            s_tb[g][u] = tb;
+            // the entries in some point's support, in order (the others add zeros;
+            // a weight that is not finite is kept, to reach the sums)
+            hit = on && (hit || !(w <= 3.402823466e38f));
+            const unsigned hits = (unsigned)(__builtin_amdgcn_ballot_w64(hit) >> (threadIdx.x & 48)) & 0xffffu;
+            if (hit) s_wt[g][__popc(hits & ((1u << u) - 1u))] = make_float2(w, __int_as_float(tb));
             sr_sync();
-            const int nb = (int)min((uint32_t)SR_GROUP, e1 - eb);
-            for (int y = 0; y < nb; ++y) {
-                const float wy = s_w[g][y];
-                const int ty = s_tb[g][y];
+            const int nb = __popc(hits);
+            // slots past a lane's count have an anchor that no bin reaches: they add zeros
+            auto add = [&](auto slots) {
+#pragma unroll 4
+                for (int y = 0; y < nb; ++y) {
+                    const float2 wt = s_wt[g][y];
 #pragma unroll
-                for (int k = 0; k < KM; ++k)
-                    if (k < pts.c) {
+                    for (int k = 0; k < decltype(slots)::value; ++k) {
                         float h, hp;
-                        irf_eval(m, ty, pts.a[k], pts.f[k], h, hp);
-                        sh[k] = fmaf(wy, h, sh[k]);
-                        shp[k] = fmaf(wy, hp, shp[k]);
+                        sr_irf(cr, m.L, m.o, __float_as_int(wt.y), pts.a[k], pts.f[k], h, hp);
+                        sh[k] = fmaf(wt.x, h, sh[k]);
+                        shp[k] = fmaf(wt.x, hp, shp[k]);
                     }
-            }
+                }
+            };
+            if (cmax == 1) add(std::integral_constant<int, 1>{});
+            else if (cmax == 2) add(std::integral_constant<int, 2>{});
+            else add(std::integral_constant<int, KM>{});
             sr_sync();                              // reads done before the next batch's writes
         }
     }
+    // S and S' of a point (the cubic's table in LDS where it fits)
+    auto s_of = [&](double t, float& S, float& Sp) {
+        if (!s_whole(m, t)) s_direct(m, t, S, Sp, 0, 1);
+        else if (stab_staged(m)) s_cubic(m, stl, t, S, Sp);
+        else s_cubic(m, m.s_tab, t, S, Sp);
+    };
     if (WHICH == SR_BKG || WHICH == SR_GRADIENTS) {
 #pragma unroll
         for (int d = SR_GROUP / 2; d >= 1; d >>= 1) sz += __shfl_xor(sz, d, 64);
@@ -147,16 +196,16 @@ __global__ __launch_bounds__(SR_GROUP * SR_GROUPS) void k_sr_step(DevModel m, De
             for (int k = 0; k < KM; ++k)
                 if (k < pts.c && pts.r[k] > 0.f) {
                     float S, Sp;
-                    s_eval(m, pts.t[k], S, Sp);
+                    s_of(pts.t[k], S, Sp);
                     st.t[(long long)k * Pf + q] = depth_next(m, p, pts.t[k], Sp, shp[k]);
                 }
-    } else if (WHICH == SR_INTENSITY) {
+    } else if (WHICH == SR_INTENSITY || WHICH == SR_MERGE_INTENSITY) {
         if (live)
 #pragma unroll
             for (int k = 0; k < KM; ++k)
                 if (k < pts.c) {
                     float S, Sp;
-                    s_eval(m, pts.t[k], S, Sp);
+                    s_of(pts.t[k], S, Sp);
                     if (S > 0.f) st.r[(long long)k * Pf + q] = intensity_next(p, pts.r[k], S, sh[k]);
                 }
     } else if (WHICH == SR_BKG) {
@@ -168,7 +217,7 @@ __global__ __launch_bounds__(SR_GROUP * SR_GROUPS) void k_sr_step(DevModel m, De
                 float vt = 0.f, vr = 0.f;
                 if (live && k < pts.c) {
                     float S, Sp;
-                    s_eval(m, pts.t[k], S, Sp);
+                    s_of(pts.t[k], S, Sp);
                     vt = G * pts.r[k] * (Sp + shp[k]);
                     vr = G * (S - sh[k]);
                 }
@@ -214,12 +263,17 @@ static hipError_t sr_launch(const DevModel& m, const DevParams& p, const Shape& 
                             float* gt, float* gr, float* gb, hipStream_t stream)
 {
     if (lid.P == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sr_step<WHICH>, dim3((unsigned)((lid.P + SR_GROUPS - 1) / SR_GROUPS)),
-                       dim3(SR_GROUP * SR_GROUPS), 0, stream, m, p, lid, s, Pf, off, ent, gain, st, bdst, gt, gr, gb);
+    const dim3 g((unsigned)((lid.P + SR_GROUPS - 1) / SR_GROUPS)), b(SR_GROUP * SR_GROUPS);
+    if (segments_fit(m))
+        hipLaunchKernelGGL((k_sr_step<WHICH, true>), g, b, 0, stream, m, p, lid, s, Pf, off, ent, gain, st, bdst, gt,
+                           gr, gb);
+    else
+        hipLaunchKernelGGL((k_sr_step<WHICH, false>), g, b, 0, stream, m, p, lid, s, Pf, off, ent, gain, st, bdst, gt,
+                           gr, gb);
     return hipGetLastError();
 }
 
-hipError_t launch_sr_step(int step, const DevModel& m, const DevParams& p, const Shape& lid, int s, long long Pf,
+hipError_t launch_sr_step(int step, bool merge, const DevModel& m, const DevParams& p, const Shape& lid, int s, long long Pf,
                           const uint32_t* off, const uint32_t* ent, const float* gain, DevState st, float* bdst,
                           hipStream_t stream)
 {
@@ -227,6 +281,9 @@ hipError_t launch_sr_step(int step, const DevModel& m, const DevParams& p, const
     case RT3D_STEP_DEPTH:
         return sr_launch<SR_DEPTH>(m, p, lid, s, Pf, off, ent, gain, st, nullptr, nullptr, nullptr, nullptr, stream);
     case RT3D_STEP_INTENSITY:
+        if (merge)
+            return sr_launch<SR_MERGE_INTENSITY>(m, p, lid, s, Pf, off, ent, gain, st, nullptr, nullptr, nullptr,
+                                                 nullptr, stream);
         return sr_launch<SR_INTENSITY>(m, p, lid, s, Pf, off, ent, gain, st, nullptr, nullptr, nullptr, nullptr,
                                        stream);
     case RT3D_STEP_BKG:

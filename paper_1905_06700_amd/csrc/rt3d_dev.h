@@ -735,9 +735,10 @@ hipError_t launch_world_z(const Shape& g, long long base, DevState s, const rt3d
 // its b[0 .. lid.P - 1] is the lidar background.  step: RT3D_STEP_DEPTH,
 // _INTENSITY or _BKG (bdst: where the new background goes, nullptr: st.b).
 constexpr int SR_MAX = 4;
-hipError_t launch_sr_step(int step, const DevModel& m, const DevParams& p, const Shape& lid, int s, long long Pf,
-                          const uint32_t* off, const uint32_t* ent, const float* gain, DevState st, float* bdst,
-                          hipStream_t stream);
+// merge: the in-pixel merge ahead of the intensity step
+hipError_t launch_sr_step(int step, bool merge, const DevModel& m, const DevParams& p, const Shape& lid, int s,
+                          long long Pf, const uint32_t* off, const uint32_t* ent, const float* gain, DevState st,
+                          float* bdst, hipStream_t stream);
 // gt, gr: [KM][Pf], gb: [lid.P]
 hipError_t launch_sr_gradients(const DevModel& m, const DevParams& p, const Shape& lid, int s, long long Pf,
                                const uint32_t* off, const uint32_t* ent, const float* gain, DevState st, float* gt,

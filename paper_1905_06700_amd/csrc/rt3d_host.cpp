@@ -818,17 +818,19 @@ rt3d_status iterate_sr(rt3d_ctx* c, const Shape& lid, const uint32_t* off, const
     const int sr = c->p.sr;
     const Shape fsh = point_grid(lid, sr);
     RT3D_LAUNCH(c, RT3D_KERNEL_DEPTH, st,
-                launch_sr_step(RT3D_STEP_DEPTH, m, p, lid, sr, fsh.P, off, ent, gain, A, nullptr, st));
+                launch_sr_step(RT3D_STEP_DEPTH, false, m, p, lid, sr, fsh.P, off, ent, gain, A, nullptr, st));
     if (c->p.denoiser == RT3D_DENOISE_APSS)
         RT3D_LAUNCH(c, RT3D_KERNEL_APSS, st, launch_apss(m, p, fsh, A, B, -1, st));
     else
         RT3D_HIP(c, launch_copy_state(fsh, A, B, st));
-    RT3D_LAUNCH(c, RT3D_KERNEL_MERGE, st, launch_merge(m, p, fsh, B, st));
+    // the in-pixel merge runs fused ahead of the intensity step (alone when it is timed)
+    const bool merge = c->prof_id != RT3D_KERNEL_MERGE;
+    if (!merge) RT3D_LAUNCH(c, RT3D_KERNEL_MERGE, st, launch_merge(m, p, fsh, B, st));
     RT3D_LAUNCH(c, RT3D_KERNEL_INTENSITY, st,
-                launch_sr_step(RT3D_STEP_INTENSITY, m, p, lid, sr, fsh.P, off, ent, gain, B, nullptr, st));
+                launch_sr_step(RT3D_STEP_INTENSITY, merge, m, p, lid, sr, fsh.P, off, ent, gain, B, nullptr, st));
     RT3D_LAUNCH(c, RT3D_KERNEL_IFILTER, st, launch_ifilter(p, fsh, B, A, st));
     RT3D_LAUNCH(c, RT3D_KERNEL_BKG, st,
-                launch_sr_step(RT3D_STEP_BKG, m, p, lid, sr, fsh.P, off, ent, gain, A, btmp, st));
+                launch_sr_step(RT3D_STEP_BKG, false, m, p, lid, sr, fsh.P, off, ent, gain, A, btmp, st));
     RT3D_LAUNCH(c, RT3D_KERNEL_BFILTER, st,
                 launch_bfilter(c->d_bw, c->rb, lid, (float)c->p.b_min, btmp, A.b, B.b, st));
     return RT3D_OK;
@@ -1451,7 +1453,7 @@ static rt3d_status debug_step_sr(rt3d_ctx* c, int32_t step, const uint32_t* off,
     case RT3D_STEP_DEPTH:
     case RT3D_STEP_INTENSITY:
     case RT3D_STEP_BKG:
-        RT3D_HIP(c, launch_sr_step(step, m, p, lid, sr, fsh.P, off, ent, gain, O, nullptr, st));
+        RT3D_HIP(c, launch_sr_step(step, false, m, p, lid, sr, fsh.P, off, ent, gain, O, nullptr, st));
         return RT3D_OK;
     case RT3D_STEP_MERGE:
         RT3D_HIP(c, launch_merge(m, p, fsh, O, st));
