@@ -112,10 +112,10 @@ __global__ __launch_bounds__(APT, 4) void k_apss_tile(DevModel m, DevParams p, T
                 for (int a = 0; a < 3; ++a) nl[(a * KM + k) * NS + x] = in.n[(a * KM + k) * S + pp];
             }
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k * NS + x] = k < c ? ts[k] : apss_none();
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = k < c ? ts[k] : no_depth();
         } else {
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k * NS + x] = apss_none();
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = no_depth();
         }
         cl[x] = c;
     }
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(APT, 4) void k_apss_tile(DevModel m, DevParams p, T
         double tn = tl[k * NS + xc];
         float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
         if (!(only_above >= 0 && cq <= only_above)) {
-            const Moments v = apss_moments(tl, nl, NS, SX, xc, R, h2, (float)p.p_xy, dz, reach, tn);
+            const Moments v = apss_moments(tl, NS, SX, xc, R, h2, (float)p.p_xy, dz, reach, tn, TileNormals{nl, NS});
             apss_project(v.nn >= (float)p.m_min, v.W, v.Px, v.Py, v.Pz, v.Nx, v.Ny, v.Nz, v.PN, v.PP, h, h2, dz,
                          (double)(m.T - 1), tn, on);
         }

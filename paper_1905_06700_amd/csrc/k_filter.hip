@@ -65,10 +65,10 @@ __global__ __launch_bounds__(IFT * IFT, PERSP ? 1 : 6) void k_ifilter_tile(DevPa
                 rl[k][x] = in.r[k * S + pp];
             }
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k][x] = k < c ? ts[k] : ifilter_none();
+            for (int k = 0; k < KM; ++k) tl[k][x] = k < c ? ts[k] : no_depth();
         } else {
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k][x] = ifilter_none();
+            for (int k = 0; k < KM; ++k) tl[k][x] = no_depth();
         }
         cl[x] = c;
     }

@@ -1250,7 +1250,7 @@ __global__ __launch_bounds__(NT_THREADS, 4) void k_init_normals_tile(DevParams p
 #pragma unroll
         for (int k = 0; k < KM; ++k) t[k] = s.t[k * S + pp];
 #pragma unroll
-        for (int k = 0; k < KM; ++k) tl[k * NS + x] = inside && k < cc ? t[k] : apss_none();
+        for (int k = 0; k < KM; ++k) tl[k * NS + x] = inside && k < cc ? t[k] : no_depth();
     }
     int c = 0;
     if (threadIdx.x < NT_SIDE * NT_SIDE) {

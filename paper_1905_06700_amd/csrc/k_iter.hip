@@ -248,10 +248,10 @@ __global__ __launch_bounds__(IPX * LPP, 5) void k_iter_intensity(DevModel m, Dev
                 for (int a = 0; a < 3; ++a) nl[(a * KM + k) * NS + x] = in.n[(a * KM + k) * P + pp];
             }
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k * NS + x] = k < c ? ts[k] : apss_none();
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = k < c ? ts[k] : no_depth();
         } else {
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k * NS + x] = apss_none();
+            for (int k = 0; k < KM; ++k) tl[k * NS + x] = no_depth();
         }
         cl[x] = c;
     }
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(IPX * LPP, 5) void k_iter_intensity(DevModel m, Dev
             const float h = (float)p.h_apss, h2 = h * h;
             const double dz = p.dz, tq = tl[k * NS + xc];
             const Moments v =
-                apss_moments(tl, nl, NS, SX, xc, R, h2, (float)p.p_xy, dz, 1.001 * p.h_apss / dz, tq);
+                apss_moments(tl, NS, SX, xc, R, h2, (float)p.p_xy, dz, 1.001 * p.h_apss / dz, tq, TileNormals{nl, NS});
             double tn = tq;
             float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
             apss_project(v.nn >= (float)p.m_min, v.W, v.Px, v.Py, v.Pz, v.Nx, v.Ny, v.Nz, v.PN, v.PP, h, h2, dz,
@@ -328,10 +328,10 @@ __global__ __launch_bounds__(IPX * LPP, 5) void k_iter_background(DevModel m, De
                 rl[k][x] = in.r[k * P + pp];
             }
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k][x] = k < c ? ts[k] : ifilter_none();
+            for (int k = 0; k < KM; ++k) tl[k][x] = k < c ? ts[k] : no_depth();
         } else {
 #pragma unroll
-            for (int k = 0; k < KM; ++k) tl[k][x] = ifilter_none();
+            for (int k = 0; k < KM; ++k) tl[k][x] = no_depth();
         }
         cl[x] = c;
     }

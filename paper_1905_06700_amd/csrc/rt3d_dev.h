@@ -305,6 +305,8 @@ __device__ __forceinline__ int ent_cnt(uint32_t e) { return (int)(e & 0xffffu); 
 // the summed intensity and the intensity-weighted normal, normalised (the
 // first point's normal when the weighted sum vanishes); the merged point is
 // compared with the next.  c drops by one per merge.
+// (The weighted sums are written as fused multiply-adds, so that every kernel
+// rounds them alike.)
 __device__ __forceinline__ void merge_points(double (&t)[KM], float (&r)[KM], float (&nx)[KM], float (&ny)[KM],
                                              float (&nz)[KM], int& c, double dm)
 {
@@ -321,9 +323,9 @@ __device__ __forceinline__ void merge_points(double (&t)[KM], float (&r)[KM], fl
         if (t[a + 1] - t[a] < dm) {
             const double ra = r[a], rb = r[a + 1];
             const double tt = (ra + rb > 0.0) ? (ra * t[a] + rb * t[a + 1]) / (ra + rb) : 0.5 * (t[a] + t[a + 1]);
-            const float mx = r[a] * nx[a] + r[a + 1] * nx[a + 1];
-            const float my = r[a] * ny[a] + r[a + 1] * ny[a + 1];
-            const float mz = r[a] * nz[a] + r[a + 1] * nz[a + 1];
+            const float mx = fmaf(r[a + 1], nx[a + 1], r[a] * nx[a]);
+            const float my = fmaf(r[a + 1], ny[a + 1], r[a] * ny[a]);
+            const float mz = fmaf(r[a + 1], nz[a + 1], r[a] * nz[a]);
             const float nrm = sqrtf(mx * mx + my * my + mz * mz);
             if (nrm > 0.f) {
                 nx[a] = mx / nrm;

@@ -3,8 +3,8 @@
 // (k_apss.hip and k_filter.hip have the readings.)
 //
 // A tile's slot arrays are [KM][NS], a pixel's window SX apart by row; slots
-// that hold no point are staged as APSS_NONE / IFILTER_NONE, so that no read
-// waits on a count: the slots in reach are found first, all of a row's reads in
+// that hold no point are staged as no_depth(), so that no read waits on a
+// count: the slots in reach are found first, all of a row's reads in
 // flight together, then the few found are summed one by one in the window's
 // order.
 #pragma once
@@ -56,14 +56,17 @@ struct Moments {
     float W, Px, Py, Pz, Nx, Ny, Nz, PN, PP, nn;
 };
 
-// A depth in reach of nothing.
-__device__ __forceinline__ double apss_none() { return __builtin_nan(""); }
+// A depth in reach of nothing and nearest to nothing.
+__device__ __forceinline__ double no_depth() { return __builtin_nan(""); }
 
 // The sphere moments of the point at depth tq of the pixel at xc: neighbours
 // closer than h (h2 = h^2), R <= APSS_ROW.  (reach: 1.001 h / dz, an upper
 // bound of the depth offset of a neighbour; the exact test follows.)
-__device__ __forceinline__ Moments apss_moments(const double* tl, const float* nl, int NS, int SX, int xc, int R,
-                                                float h2, float pxy, double dz, double reach, double tq)
+// normals(slot, di, dj, at, n): the normal of a slot of the window's pixel (di, dj),
+// its place `at` in the slot's tile.
+template <class Normals>
+__device__ __forceinline__ Moments apss_moments(const double* tl, int NS, int SX, int xc, int R, float h2, float pxy,
+                                                double dz, double reach, double tq, Normals normals)
 {
     Moments s{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const float inv_h2 = 1.f / h2;
@@ -73,21 +76,18 @@ __device__ __forceinline__ Moments apss_moments(const double* tl, const float* n
         uint64_t near = near_slots(tl, NS, row, R, reach, tq);
         int at = 0;
         double t2 = 0.0;
-        float nx = 0.f, ny = 0.f, nz = 0.f;
+        float n[3] = {0.f, 0.f, 0.f};
         auto fetch = [&] {
-            const int bit = __ffsll((unsigned long long)near) - 1;
+            const int bit = __ffsll((unsigned long long)near) - 1, k = bit % KM;
             at = bit / KM - R;
-            const int y = (bit % KM) * NS + row + at;
-            t2 = tl[y];
-            nx = nl[y];
-            ny = nl[KM * NS + y];
-            nz = nl[2 * KM * NS + y];
+            t2 = tl[k * NS + row + at];
+            normals(k, di, at, row + at, n);
             near &= near - 1;
         };
         bool more = near != 0;
         if (more) fetch();
         while (more) {
-            const float yx = (float)at * pxy, mx = nx, my = ny, mz = nz;
+            const float yx = (float)at * pxy, mx = n[0], my = n[1], mz = n[2];
             const float yz = (float)((t2 - tq) * dz);
             more = near != 0;
             if (more) fetch();
@@ -112,8 +112,16 @@ __device__ __forceinline__ Moments apss_moments(const double* tl, const float* n
     return s;
 }
 
-// A depth that is nearest to nothing.
-__device__ __forceinline__ double ifilter_none() { return __builtin_inf(); }
+// Normals staged as [3][KM][NS].
+struct TileNormals {
+    const float* nl;
+    int NS;
+    __device__ __forceinline__ void operator()(int k, int, int, int at, float (&n)[3]) const
+    {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) n[a] = nl[(a * KM + k) * NS + at];
+    }
+};
 
 // The low-passed intensity of the point at depth tq, intensity r of the pixel
 // at xc: the 8 surrounding pixels' nearest points (lowest slot on ties) closer
