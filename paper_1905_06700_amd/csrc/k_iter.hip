@@ -1,5 +1,5 @@
 // k_iter.hip -- one iteration of the reconstruction loop (Results,
-// "Reconstruction algorithm") in three launches on tiles of 16 x 4 pixels:
+// "Reconstruction algorithm") in three launches on tiles of 8 x 4 pixels:
 //   k_iter_depth      the background filter of the iteration before, the depth
 //                     step;
 //   k_iter_intensity  APSS, the in-pixel merge, the intensity step;
@@ -10,23 +10,22 @@
 // of sums as the steps' own kernels (k_steps.hip, k_apss.hip, k_filter.hip), so the
 // result is the same to the bit.
 //
-// Mapping: LPP lanes per pixel, 64 LPP threads.  Steps on points (APSS, the
+// Mapping: LPP lanes per pixel, 32 LPP threads.  Steps on points (APSS, the
 // intensity filter) take a thread per slot, thread 4 q + k slot k of tile pixel
 // q; the gradient steps the pixel's LPP lanes, which load what does not depend
 // on the first part (entries' range, gain, background) ahead of it.
 //
 // What a step's own launch costs a small batch is its start, its first loads
 // and its last wavefronts (about 4 us whatever it does), and its pixels are
-// few for tiles of 16 x 16.  An iteration on 20 k pixels takes 25 us (7 + 11 +
-// 6) against 34 us in six launches, on 90 k pixels 32 us (10 + 14 + 8) against
-// 48 us; on 636 k pixels 270 us against 222 us, where the steps' own kernels
-// keep more workgroups on a CU (the host's rule has the sizes in between).
+// few for tiles of 16 x 16.  An iteration on 20 k pixels takes 24 us (7 + 11 +
+// 6) against 34 us in six launches, on 90 k pixels 31 us (9 + 14 + 8) against
+// 48 us; the host's rule has the sizes where that turns.
 #include "rt3d_points.h"
 #include "rt3d_steps.h"
 
 namespace rt3d {
 
-constexpr int ITX = 16, ITY = 4;        // tile: columns, rows
+constexpr int ITX = 8, ITY = 4;         // tile: columns, rows (16 x 4: the same on 20 k pixels, 3% slower on 90 k)
 constexpr int IPX = ITX * ITY;          // pixels of a tile
 static_assert(KM == 4, "a pixel's slots: a quad of lanes");
 

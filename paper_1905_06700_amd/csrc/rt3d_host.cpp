@@ -648,11 +648,11 @@ CnnBuffers cnn_at(const CnnBuffers& b, long long base)
 
 // Whether the iterations run as three launches on tiles (k_iter.hip): APSS on
 // the orthographic map, one IRF, no step of the iteration timed by itself, and
-// at most ITER_PIXELS pixels.  Whole calls, three launches against six, us:
-// 20 k pixels 791 / 990, 40 k 965 / 1056, 80 k 1452 / 1447 at 42 entries per
-// pixel; 57 k 1276 / 1339, 80 k 1582 / 1614, 159 k 1881 / 1920 at 4; 262 k
-// pixels, one iteration, 138 / 126: above, the steps' own kernels with more
-// workgroups per CU are the faster ones.
+// at most ITER_PIXELS pixels.  Whole calls, three launches against six, us: one
+// frame of 20 k pixels 738 / 965, 40 k 839 / 1021, 80 k 1339 / 1393 (42 entries
+// per pixel), 1467 / 1594 (4 entries); two of 80 k 2225 / 1951 and 2429 / 2350,
+// with four lanes per pixel: above, the steps' own kernels with more workgroups
+// per CU are the faster ones.
 constexpr long long ITER_PIXELS = LANES8_PIXELS;
 
 bool iter_eligible(const rt3d_ctx* c, const Shape& sh, const uint8_t* cls)
