@@ -72,7 +72,7 @@ int apss_staged_halo(double h_apss, double p_xy, int R)
 // without points and no slot to wait for another: 636 k pixels of 1.4 points
 // take 41 us (the planes read and written at the rate of a copy would take 22),
 // against 49 us for a thread per pixel that kept the moments of all its slots;
-// 20 k points on a point grid of 80 k pixels 12 us against 17.
+// a point grid of 74 k pixels 12 us against 17.
 constexpr int APT = 512;
 __global__ __launch_bounds__(APT, 4) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in, DevState out,
                                                       int only_above, int carry)

@@ -1218,7 +1218,7 @@ struct PlaneFit {
 // pixel tile and its halo in LDS, a thread per live point (list_points), the
 // slots in reach of it found a row at a time, then summed one by one.  What
 // took the time was one dependent read after the other: 45 us for 636 k pixels,
-// 7.5 us for 20 k, against 159 and 37 us for a thread per pixel on the state in
+// 7.5 us for 1 k, against 159 and 37 us for a thread per pixel on the state in
 // memory.
 constexpr int NORMALS_R = APSS_ROW, NT_SIDE = TILE, NT_THREADS = 512;
 

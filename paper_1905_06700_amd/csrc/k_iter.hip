@@ -17,15 +17,15 @@
 //
 // What a step's own launch costs a small batch is its start, its first loads
 // and its last wavefronts (about 4 us whatever it does), and its pixels are
-// few for tiles of 16 x 16.  An iteration on 20 k pixels takes 24 us (7 + 11 +
-// 6) against 34 us in six launches, on 90 k pixels 31 us (9 + 14 + 8) against
-// 48 us; the host's rule has the sizes where that turns.
+// few for tiles of 16 x 16.  An iteration on a frame of 32 x 32 takes 24 us (7 +
+// 11 + 6) against 34 us in six launches, on one of 141 x 141 31 us (9 + 14 + 8)
+// against 48 us; the host's rule has the sizes where that turns.
 #include "rt3d_points.h"
 #include "rt3d_steps.h"
 
 namespace rt3d {
 
-constexpr int ITX = 8, ITY = 4;         // tile: columns, rows (16 x 4: the same on 20 k pixels, 3% slower on 90 k)
+constexpr int ITX = 8, ITY = 4;         // tile: columns, rows (16 x 4: the same at 1 k pixels, 3% slower at 20 k)
 constexpr int IPX = ITX * ITY;          // pixels of a tile
 static_assert(KM == 4, "a pixel's slots: a quad of lanes");
 
