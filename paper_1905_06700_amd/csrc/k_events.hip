@@ -10,7 +10,7 @@
 // sees one atomic per workgroup and bucket instead of one per event: bucket
 // totals, their scan, then the scatter of (pixel in the bucket, bin) words, each workgroup's
 // events of a bucket side by side.  One workgroup per bucket then orders its
-// events by pixel in LDS, sorts each pixel's bins (up to 64 of them in the
+// events by pixel in LDS, sorts each pixel's bins (up to 128 of them in the
 // lanes of a wavefront), run-length encodes them and leaves the bucket's
 // entries packed; a scan of the buckets' entry counts, and the entries move to
 // their place.  Buckets with more than EV_CAP events (a few pixels much
@@ -19,11 +19,12 @@
 // pixel sorted by one wavefront (in LDS up to EV_LDS events, in place in the
 // scratch buffer beyond).  The result does not depend on the event order.
 //
-// What bounds it is the events' traffic to memory, one place at a time: 3.9 M
-// events of 79.5 k pixels (24 MB) took 575 us by the direct way alone (284 in
+// What bounds it is the events' traffic to memory, one place at a time: 4.4 M
+// events of 79.5 k pixels (26 MB) took 575 us by the direct way alone (284 in
 // the scatter, 174 in the count: an atomic and a scattered store per event)
-// and take 141 us by buckets (46 in the scatter, 12 in the count, 55 in the
-// sort, 7 in the copy, the rest launches of a few us).
+// and take 122 us by buckets (47 in the scatter, 13 in the count, 39 in the
+// sort, 8 in the copy, the rest launches of a few us; the sort took 54 while
+// pixels of 65 to 128 events, a tenth of them, were sorted in LDS).
 #include "rt3d_dev.h"
 
 #include <algorithm>
@@ -38,6 +39,7 @@ constexpr int EV_EPT = 16;         // events per thread, at most
 constexpr int EV_BUCKETS = 16384;  // buckets, at most (64 KB of counters)
 constexpr int EV_MEAN = 4096;      // events per bucket, at most on average
 constexpr int EV_CAP = 6144;       // events a bucket's workgroup orders in LDS
+constexpr int EV_PER = EV_CAP / (64 * EV_WAVES);   // of them per thread
 constexpr int EV_BMAX = 1024;      // pixels per bucket, at most (else every bucket goes the direct way)
 
 // The buckets' arrays in the workspace (NB of them, B = 2^lg pixels each).
@@ -296,9 +298,29 @@ __device__ __forceinline__ uint32_t ev_move(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
 }
 
+// PAIR: two 16-bit values per lane, two sorts side by side.
+template <bool PAIR>
+__device__ __forceinline__ uint32_t ev_min(uint32_t v, uint32_t o)
+{
+    typedef unsigned short pair __attribute__((ext_vector_type(2)));
+    if (!PAIR) return v < o ? v : o;
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(pair, v),
+                                                                  __builtin_bit_cast(pair, o)));
+}
+
+template <bool PAIR>
+__device__ __forceinline__ uint32_t ev_max(uint32_t v, uint32_t o)
+{
+    typedef unsigned short pair __attribute__((ext_vector_type(2)));
+    if (!PAIR) return v < o ? o : v;
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(pair, v),
+                                                                  __builtin_bit_cast(pair, o)));
+}
+
+template <bool PAIR>
 __device__ __forceinline__ uint32_t ev_keep(uint32_t v, uint32_t o, bool upper)
 {
-    const uint32_t lo = v < o ? v : o, hi = v < o ? o : v;
+    const uint32_t lo = ev_min<PAIR>(v, o), hi = ev_max<PAIR>(v, o);
     return upper ? hi : lo;
 }
 
@@ -314,25 +336,45 @@ __device__ __forceinline__ uint32_t ev_xor32(uint32_t v, bool b32)
     return b32 ? r[0] : r[1];
 }
 
+template <bool PAIR>
 __device__ __forceinline__ uint32_t ev_sort64(uint32_t v, int lane)
 {
     const bool b1 = lane & 1, b2 = lane & 2, b4 = lane & 4, b8 = lane & 8, b16 = lane & 16, b32 = lane & 32;
-    auto x1 = [&] { v = ev_keep(v, ev_move<0xB1>(v), b1); };                       // lane ^ 1
-    auto x2 = [&] { v = ev_keep(v, ev_move<0x4E>(v), b2); };                       // ^ 2
-    auto x4 = [&] { v = ev_keep(v, ev_move<0x1B>(ev_move<0x141>(v)), b4); };       // ^ 7 ^ 3
-    auto x8 = [&] { v = ev_keep(v, ev_move<0x128>(v), b8); };                      // rotated by 8 of 16
+    auto x1 = [&] { v = ev_keep<PAIR>(v, ev_move<0xB1>(v), b1); };                       // lane ^ 1
+    auto x2 = [&] { v = ev_keep<PAIR>(v, ev_move<0x4E>(v), b2); };                       // ^ 2
+    auto x4 = [&] { v = ev_keep<PAIR>(v, ev_move<0x1B>(ev_move<0x141>(v)), b4); };       // ^ 7 ^ 3
+    auto x8 = [&] { v = ev_keep<PAIR>(v, ev_move<0x128>(v), b8); };                      // rotated by 8 of 16
     x1();
-    v = ev_keep(v, ev_move<0x1B>(v), b2);                                          // ^ 3
+    v = ev_keep<PAIR>(v, ev_move<0x1B>(v), b2);                                          // ^ 3
     x1();
-    v = ev_keep(v, ev_move<0x141>(v), b4);                                         // ^ 7
+    v = ev_keep<PAIR>(v, ev_move<0x141>(v), b4);                                         // ^ 7
     x2(), x1();
-    v = ev_keep(v, ev_move<0x140>(v), b8);                                         // ^ 15
+    v = ev_keep<PAIR>(v, ev_move<0x140>(v), b8);                                         // ^ 15
     x4(), x2(), x1();
-    v = ev_keep(v, ev_xor16(ev_move<0x140>(v), b16), b16);                         // ^ 31
+    v = ev_keep<PAIR>(v, ev_xor16(ev_move<0x140>(v), b16), b16);                         // ^ 31
     x8(), x4(), x2(), x1();
-    v = ev_keep(v, ev_xor32(ev_xor16(ev_move<0x140>(v), b16), b32), b32);          // ^ 63
-    v = ev_keep(v, ev_xor16(v, b16), b16);
+    v = ev_keep<PAIR>(v, ev_xor32(ev_xor16(ev_move<0x140>(v), b16), b32), b32);          // ^ 63
+    v = ev_keep<PAIR>(v, ev_xor16(v, b16), b16);
     x8(), x4(), x2(), x1();
+    return v;
+}
+
+// Ascending sort of 128 16-bit values, value i in the low half of lane i, value
+// 64 + i in the high half: both halves sorted side by side, the mirrored pairs
+// between them, then the half-cleaners on both.
+__device__ __forceinline__ uint32_t ev_sort128(uint32_t v, int lane)
+{
+    const bool b1 = lane & 1, b2 = lane & 2, b4 = lane & 4, b8 = lane & 8, b16 = lane & 16, b32 = lane & 32;
+    v = ev_sort64<true>(v, lane);
+    const uint32_t m = ev_xor32(ev_xor16(ev_move<0x140>(v), b16), b32);            // lane ^ 63
+    const uint32_t o = (m >> 16) | (m << 16);
+    v = (ev_min<true>(v, o) & 0xffffu) | (ev_max<true>(v, o) & 0xffff0000u);
+    v = ev_keep<true>(v, ev_xor32(v, b32), b32);
+    v = ev_keep<true>(v, ev_xor16(v, b16), b16);
+    v = ev_keep<true>(v, ev_move<0x128>(v), b8);
+    v = ev_keep<true>(v, ev_move<0x1B>(ev_move<0x141>(v)), b4);
+    v = ev_keep<true>(v, ev_move<0x4E>(v), b2);
+    v = ev_keep<true>(v, ev_move<0xB1>(v), b1);
     return v;
 }
 
@@ -400,7 +442,17 @@ __global__ __launch_bounds__(64 * EV_WAVES) void k_ev_sort(EvBuckets b, long lon
     const int np = (int)min((long long)B, P - p0);
     for (int x = threadIdx.x; x < B; x += 64 * EV_WAVES) cur[x] = 0;
     __syncthreads();
-    for (uint32_t x = threadIdx.x; x < n; x += 64 * EV_WAVES) atomicAdd(&cur[scratch[s0 + x] >> 16], 1u);
+    // the bucket's events in registers, every read in flight at once; an event's
+    // place in its pixel's segment is the counter's value before it
+    uint32_t v[EV_PER], rank[EV_PER];
+#pragma unroll
+    for (int u = 0; u < EV_PER; ++u) {
+        const uint32_t x = threadIdx.x + u * 64 * EV_WAVES;
+        v[u] = x < n ? scratch[s0 + x] : EV_INF;
+    }
+#pragma unroll
+    for (int u = 0; u < EV_PER; ++u)
+        rank[u] = threadIdx.x + u * 64 * EV_WAVES < n ? atomicAdd(&cur[v[u] >> 16], 1u) : 0u;
     __syncthreads();
     auto scan = [&](bool places) {             // wavefront 0: exclusive scan of cur into cur (and seg)
         uint32_t run = 0;
@@ -420,20 +472,29 @@ __global__ __launch_bounds__(64 * EV_WAVES) void k_ev_sort(EvBuckets b, long lon
         if (lane == 0) seg[B] = run;
     }
     __syncthreads();
-    for (uint32_t x = threadIdx.x; x < n; x += 64 * EV_WAVES) {
-        const uint32_t v = scratch[s0 + x];
-        bins[atomicAdd(&cur[v >> 16], 1u)] = (uint16_t)v;
-    }
+#pragma unroll
+    for (int u = 0; u < EV_PER; ++u)
+        if (threadIdx.x + u * 64 * EV_WAVES < n) bins[seg[v[u] >> 16] + rank[u]] = (uint16_t)v[u];
     __syncthreads();
     for (int p = w; p < B; p += EV_WAVES) {
         const uint32_t at = seg[p], m = seg[p + 1] - at;
         uint32_t d;
         if (m <= 64) {
             uint32_t v = (uint32_t)lane < m ? bins[at + lane] : EV_INF;
-            v = ev_sort64(v, lane);
+            v = ev_sort64<false>(v, lane);
             if ((uint32_t)lane < m) bins[at + lane] = (uint16_t)v;
             const uint32_t pv = (uint32_t)__shfl_up((int)v, 1, 64);
             d = (uint32_t)__popcll(__ballot((uint32_t)lane < m && (lane == 0 || v != pv)));
+        } else if (m <= 128) {
+            const bool in = 64u + lane < m;
+            const uint32_t v = ev_sort128(bins[at + lane] | (in ? (uint32_t)bins[at + 64 + lane] << 16 : 0xffff0000u),
+                                          lane);
+            bins[at + lane] = (uint16_t)v;
+            if (in) bins[at + 64 + lane] = (uint16_t)(v >> 16);
+            const uint32_t df = v ^ (uint32_t)__shfl_up((int)v, 1, 64);
+            const uint32_t mid = (uint32_t)__builtin_amdgcn_readlane((int)v, 63) & 0xffffu;   // value 63
+            const bool head = lane == 0 ? (v >> 16) != mid : (df >> 16) != 0;
+            d = (uint32_t)(__popcll(__ballot(lane == 0 || (df & 0xffffu))) + __popcll(__ballot(in && head)));
         } else {
             ev_bitonic(bins + at, m);
             d = ev_distinct(bins + at, m);

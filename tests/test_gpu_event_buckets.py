@@ -2,7 +2,7 @@
 oracle: pixel counts around a bucket and around the number of buckets, events
 per pixel from none to past what a bucket's workgroup orders in LDS (the
 direct way), a few pixels much brighter than the rest (both ways in one call),
-segments of 63 to 65 events, invalid events among them, a capacity that cuts
+segments around 64 and 128 events, invalid events among them, a capacity that cuts
 the lists."""
 import numpy as np
 import pytest
@@ -44,6 +44,8 @@ CASES = {
     "skewed": lambda r: (20000,) + skewed(r, 20000, slice(9000, 9040), 3000),
     "hot_last": lambda r: (1030,) + skewed(r, 1030, slice(1029, 1030), 100000),
     "segments": lambda r: (2500,) + counts(r, r.integers(60, 68, 2500)),
+    "segments_128": lambda r: (700,) + counts(r, r.integers(120, 136, 700)),
+    "few_bins_100": lambda r: (400,) + counts(r, r.integers(66, 129, 400), 3),
 }
 
 
