@@ -207,11 +207,6 @@ __device__ __forceinline__ void irf_eval_t(const float4* __restrict__ cr, int L,
     if ((unsigned)(idx - lo) <= (unsigned)(L - lo)) cr_segment(cr[idx], s, h, hp);
 }
 
-__device__ __forceinline__ void irf_eval(const DevModel& m, int tb, int a, float f, float& h, float& hp)
-{
-    irf_eval_t(m.cr, m.L, m.o, tb, a, f, h, hp);
-}
-
 // S(t) = sum over bins of h(tb - t) and dS/dt = -sum h'(tb - t) (every lag
 // shares the local parameter s).  Inside the domain, for an IRF whose segments
 // never dip below zero, the closed-form cubic of all segments (s_cubic); else by
@@ -493,8 +488,6 @@ __device__ __forceinline__ void store_points(const DevState& s, long long P, lon
 
 
 // Wave-level helpers (wave64).
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
-
 
 // Cross-lane moves inside small aligned lane groups on the VALU (DPP), with
 // no LDS traffic.  Every lane of the wavefront must be active.
