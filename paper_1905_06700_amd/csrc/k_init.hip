@@ -539,7 +539,7 @@ struct PickRegs {
 struct PickLoop {
     const uint32_t* B;
     int nblk, lane;
-    uint32_t done;          // bit u: block lane + 64 u scored
+    uint32_t done;          // bit u: block lane + 64 u scored (u < 32: INIT_T_MAX)
 
     __device__ __forceinline__ void load(const uint32_t* b, int n, int l)
     {
@@ -580,7 +580,8 @@ struct PickLoop {
 
     __device__ __forceinline__ void mark(int d0, int n, int)
     {
-        const int d1 = d0 + n - 1, u = (d1 - lane) >> 6;     // the last block of this lane at or below d1
+        // (a tile's blocks past the last one have no mark: a 33rd with 32768 bins)
+        const int d1 = min(d0 + n, nblk) - 1, u = (d1 - lane) >> 6;   // the last block of this lane at or below d1
         if (d1 >= lane && lane + 64 * u >= d0) done |= 1u << u;
     }
 };

@@ -9,7 +9,8 @@ namespace rt3d {
 
 constexpr int INIT_WAVES = 4;       // wavefronts per workgroup (fewer where their LDS areas are large)
 constexpr int INIT_OCC = 5;         // workgroups per CU the registers allow
-constexpr int INIT_T_MAX = 32768;   // bins the dense pool covers (one bit per 64 blocks of 16 tau)
+constexpr int INIT_T_MAX = 32768;   // bins the dense search covers (2048 blocks of 16 tau: a bit of 32 in each lane)
+static_assert(INIT_T_MAX <= 16 * 64 * 32, "a mark per block");
 constexpr int INIT_L_MAX = 3904;    // IRF bins the weight tables cover
 constexpr int INIT_E_BITS = 6;      // low digit of e = 2^qshift qc - q
 
