@@ -16,7 +16,7 @@ struct DevModel {
     const float4*  cr;    // Catmull-Rom segment k-1 (samples k..k+1): cubic coefficients (c0, c1, c2, c3)
     const int32_t* q;     // log-matched-filter weights, 16 fractional bits
     const int32_t* qst;   // range-maximum table of q: qst[l * L + k] = max q[k .. k + 2^l - 1]
-    // q as digits for the integer matrix cores, q = 2^qshift qc - 64 e1 - e0:
+    // q as digits for the integer matrix cores, q = 2^qshift qc - 128 e1 - e0:
     // [qc, e1, e0][ks steps of 64 lags][64 lanes][16 bytes], lane i + 16 g,
     // byte b of step s holding row i's value of lag 64 s + 16 g + b - i
     // (nullptr: the dense search does not apply); qmax the largest weight

@@ -340,7 +340,9 @@ rt3d_status build_irf(const double* irf, uint32_t irf_len, int32_t irf_origin, i
         }
     // the weights as digits for the integer matrix cores (DevModel::qa): qc =
     // ceil(q / 2^qshift) up to 127, the rest e = 2^qshift qc - q in two
-    // digits, the upper one up to 127
+    // digits up to 127 (six bits in the lower one left weights above 15.9 out,
+    // which sbr_guess x bins above 3e7 reaches with a 19-bin IRF: 0.54 ms from
+    // the lists instead of 0.07, 20 k pixels of 4613 bins)
     t.qmax = *std::max_element(q.begin(), q.end());
     t.qshift = 0;
     while (t.qshift < 30 && t.qmax > 127ll << t.qshift) ++t.qshift;

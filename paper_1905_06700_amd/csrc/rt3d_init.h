@@ -12,7 +12,7 @@ constexpr int INIT_OCC = 5;         // workgroups per CU the registers allow
 constexpr int INIT_T_MAX = 32768;   // bins the dense search covers (2048 blocks of 16 tau: a bit of 32 in each lane)
 static_assert(INIT_T_MAX <= 16 * 64 * 32, "a mark per block");
 constexpr int INIT_L_MAX = 3904;    // IRF bins the weight tables cover
-constexpr int INIT_E_BITS = 6;      // low digit of e = 2^qshift qc - q
+constexpr int INIT_E_BITS = 7;      // low digit of e = 2^qshift qc - q (both digits up to 127: qshift up to 14)
 
 // Steps of 64 bins that hold the L + 15 lags of a block of 16 tau.
 inline __host__ __device__ int init_ks(int L) { return (L + 15 + 63) / 64; }
