@@ -40,10 +40,14 @@
 //
 // Pixels with more than 127 pooled photons in one bin are left to a second
 // kernel, which holds the counts as two 7-bit digits in two planes of bytes
-// and adds both planes' products.  Where the tables do not apply (IRFs over
-// INIT_L_MAX bins, histograms over INIT_T_MAX bins, more than 16383 photons in
-// one bin, scores past 32 bits) an exact branch and bound over blocks of 64
-// tau reads the photons from memory.
+// and adds both planes' products.
+//
+// The dense pool costs the same however few photons it holds.  Sparse pools of
+// long histograms or long IRFs (list_mean), and what the digits do not cover
+// (IRFs over INIT_L_MAX bins, histograms over INIT_T_MAX bins, more than 16383
+// photons in one bin, scores past 32 bits), take the list search: an exact
+// branch and bound over the photon list, most of the time one of a dependent
+// chain (pick a block, add its few entries' weights, compare).
 #include "rt3d_dev.h"
 #include "rt3d_init.h"
 #include "rt3d_points.h"
@@ -135,7 +139,10 @@ struct InitArgs {
     DevState s;
     int ppw;            // pixels per wavefront
     int area;           // LDS bytes of one wavefront
-    int all;            // k_init_rest: every live pixel of the launch
+    uint32_t mean;      // k_init_lists: pooled entries of an average pixel up to which it takes any,
+    uint32_t limit;     // and of the pixels it takes
+    uint32_t cap;       // pooled entries the list search's LDS holds
+    int left;           // only the pixels that the launch before left
     int wide;           // k_init_rest: two planes of bytes fit the wavefront's LDS
 };
 
@@ -152,16 +159,6 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// max q[lo..hi] from the range-maximum table qst (level l: max of 2^l
-// consecutive weights; lo <= hi, both in [0, L)).
-__device__ __forceinline__ int q_range_max(const int* qst, int L, int lo, int hi)
-{
-    const int len = hi - lo + 1;
-    const int l = 31 - __clz(len);
-    const int a = qst[l * L + lo], b = qst[l * L + hi - (1 << l) + 1];
-    return a > b ? a : b;
 }
 
 __device__ __forceinline__ int popc_ballot(bool x) { return __popcll(__ballot(x)); }
@@ -314,15 +311,27 @@ struct InitPool {
                 }
             }
         } else {
-            for (int b = 0; b < NG; ++b) {
-                Acc d[4];
+            // (two groups of four tiles per read of the weights, where the registers allow)
+            constexpr int G = WIDE ? 1 : 2;
+            for (int b0 = 0; b0 < NG; b0 += G) {
+                Acc d[G][4];
+                int at[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u) at[u] = lb + 4 * min(b0 + u, NG - 1);
+#pragma unroll 2
                 for (int k = 0; k < ks; ++k) {
                     const v4i a = qa[k * 64 + lane];
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) add(d[c], a, lb + 4 * (b + k) + c);
+                    for (int u = 0; u < G; ++u)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) add(d[u][c], a, at[u] + 4 * k + c);
                 }
-                const uint32_t v[4] = {max4(d[0].sum()), max4(d[1].sum()), max4(d[2].sum()), max4(d[3].sum())};
-                store4(b, v);
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    const uint32_t v[4] = {max4(d[u][0].sum()), max4(d[u][1].sum()), max4(d[u][2].sum()),
+                                           max4(d[u][3].sum())};
+                    store4(min(b0 + u, NG - 1), v);
+                }
             }
         }
     }
@@ -695,151 +704,221 @@ __device__ __forceinline__ void dense_search(const InitPool<KS, WIDE>& P, uint32
     }
 }
 
-// The search from global memory: an exact branch and bound over blocks of 64
-// tau (one tau per lane) with 64-bit sums.  An upper bound of every block's
-// best score, sum over pooled photons of z x the largest weight over the lags
-// the block can see, is added up in LDS; blocks are scored exactly in
-// decreasing bound order until no remaining bound can beat (or tie at a
-// smaller tau) the best score.  The bounds count every photon, so they stay
-// valid after photons are claimed.
-__device__ __forceinline__ void lists_search(const DevModel& m, const DevParams& p, const Shape& sh,
-                                          const uint32_t* __restrict__ off, const uint32_t* __restrict__ ent,
-                                          long long fr, int i, int j, unsigned long long* wbase, Peaks& pk)
+// The search over the photon list: an exact branch and bound over blocks of 64
+// tau, one per lane.  The bound of a block, sum z x the largest weight of the 64
+// lags a photon's bin can have in it, is added up in LDS; blocks are scored
+// exactly in decreasing bound order until no remaining bound can beat (or tie
+// at a smaller tau) the best score.  A score takes the entries in reach one by
+// one (their lanes from a ballot over 64 entries), each lane's weight one read
+// of the padded table.  STAGED: the entries, n of them, are in LDS, and an
+// accepted peak's photons leave them and the bounds; else they are read from
+// memory, row by row of the window, for every block.  The scores fit the type.
+// LIST_BLOCKS blocks are scored at once, LIST_TAKE entries in flight: 10 k
+// pixels, pools of 200 entries of 8192 bins, a 2001-bin IRF 287 us against 434
+// us for one block and four entries; of 20000 bins, a 19-bin IRF 462 against
+// 393 us.
+constexpr int LIST_BLOCKS = 4, LIST_TAKE = 2;
+static_assert(64 * LIST_BLOCKS - 1 <= LIST_PAD, "the weights' zeros reach over the blocks");
+
+template <class Score, bool STAGED>
+__device__ __forceinline__ void list_search(const PoolRows& W, uint32_t* list, uint32_t n, Score* ub, Peaks& pk)
 {
-    const int lane = threadIdx.x & 63;
-    const int T = m.T, L = m.L, o = m.o;
-    const int R = p.r_init, side = 2 * R + 1;
-    const int* qstt = m.qst;
-    const int nb = (T + 63) >> 6;
-    uint2* lists = reinterpret_cast<uint2*>(wbase);
-    unsigned long long* ub = wbase + side * side;                    // the block bounds
-    long long ntot;
-    {
-        // the window's pixels' photon lists (each ascending in t)
-        const int npl = side * side;
-        for (int w = lane; w < npl; w += 64) {
-            const int i2 = i - R + w / side, j2 = j - R + w % side;
-            uint2 rg = make_uint2(0u, 0u);
-            if (i2 >= 0 && i2 < sh.rows && j2 >= 0 && j2 < sh.cols) {
-                const long long pp = (fr * sh.rows + i2) * sh.cols + j2;
-                rg = make_uint2(off[pp], off[pp + 1]);
-            }
-            lists[w] = rg;
-        }
-        wave_sync();
-        ntot = 0;
-        const double k2 = p.kappa * p.kappa;
-        // Branch and bound over blocks of 64 tau, reading the photons from HBM.
-        for (int b = lane; b < nb; b += 64) ub[b] = 0ull;
-        wave_sync();
-
-        // photon total and per-block score bounds
-        for (int l = 0; l < npl; ++l) {
-            const uint2 rg = lists[l];
-            for (uint32_t e = rg.x + lane; e < rg.y; e += 64) {
-                const uint32_t v = ent[e];
-                const int t = ent_bin(v), z = ent_cnt(v);
-                if (t >= T) continue;
-                ntot += z;
-                const int tlo = max(0, t + o - L + 1), thi = min(T - 1, t + o);
-                for (int b = tlo >> 6; b <= (thi >> 6); ++b) {
-                    const int a0 = max(tlo, b << 6), a1 = min(thi, (b << 6) + 63);
-                    const int qm = q_range_max(qstt, L, t - a1 + o, t - a0 + o);
-                    atomicAdd(&ub[b], (unsigned long long)z * (unsigned long long)qm);
-                }
+    const InitArgs& A = init_args();
+    const DevModel& m = A.m;
+    const int T = m.T, L = m.L, o = m.o, nb = (T + 63) >> 6, lane = threadIdx.x & 63;
+    const int32_t* q = m.q;
+    const int32_t* qwin = m.qwin;
+    // f(entry, its place), 64 at a time; places past the end hold bin 65535
+    auto each = [&](auto f) {
+        if constexpr (STAGED) {
+            for (uint32_t x = lane; x - lane < n; x += 64) f(x < n ? list[x] : 0xffff0000u, x);
+        } else {
+            for (int r = 0; r < W.side; ++r) {
+                const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)W.rs, r);
+                const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)W.re, r);
+#pragma unroll 4
+                for (uint32_t x = a; x < b; x += 64) f(x + lane < b ? W.ent[x + lane] : 0xffff0000u, 0u);
             }
         }
-        ntot = wave_sum(ntot);
-        wave_sync();
-
-        for (int it = 0; it < p.k_init; ++it) {
-            long long best = -1;
-            int bestt = 0x7fffffff;
-            uint32_t done = 0;                      // bit q: block lane + 64 q scored in this round
-            while (true) {
-                // unscored block with the largest bound (smallest index on ties)
-                unsigned long long bu = 0;
-                int bb = 0x7fffffff;
-                for (int q = 0; lane + 64 * q < nb; ++q) {
-                    if ((done >> q) & 1u) continue;
-                    const unsigned long long u = ub[lane + 64 * q];
-                    if (bb == 0x7fffffff || u > bu) {
-                        bu = u;
-                        bb = lane + 64 * q;
-                    }
-                }
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const unsigned long long ou = __shfl_xor(bu, d, 64);
-                    const int ob = __shfl_xor(bb, d, 64);
-                    if (ob != 0x7fffffff && (bb == 0x7fffffff || ou > bu || (ou == bu && ob < bb))) {
-                        bu = ou;
-                        bb = ob;
-                    }
-                }
-                if (bb == 0x7fffffff) break;
-                if ((long long)bu < best || ((long long)bu == best && (bb << 6) > bestt)) break;
-                if (lane == (bb & 63)) done |= 1u << (bb >> 6);
-                // exact scores of the block's 64 tau
-                const int tau = (bb << 6) + lane;
-                const int wlo = (bb << 6) - o, whi = (bb << 6) + 63 - o + L - 1;
-                long long sc = 0;
-                for (int l = 0; l < npl; ++l) {
-                    const uint2 rg = lists[l];
-                    int c0 = 0, c1 = 0;
-                    for (uint32_t e0 = rg.x; e0 < rg.y; e0 += 64) {
-                        const uint32_t e = e0 + lane;
-                        const int t = e < rg.y ? ent_bin(ent[e]) : 0x7fffffff;
-                        c0 += popc_ballot(t < wlo);
-                        c1 += popc_ballot(t <= whi);
-                    }
-                    for (uint32_t x = rg.x + c0; x < rg.x + c1; ++x) {
-                        const uint32_t v = ent[x];
-                        const int tb = ent_bin(v);
-                        if (pk.claimed(m, tb)) continue;
-                        const int lag = tb - tau + o;
-                        if ((unsigned)lag < (unsigned)L) sc += (long long)ent_cnt(v) * (long long)m.q[lag];
-                    }
-                }
-                const bool valid = tau < T && !pk.suppressed(tau, m.wnms);
-                long long sv = valid ? sc : -1;
-                int st = valid ? tau : 0x7fffffff;
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const long long ov = __shfl_xor(sv, d, 64);
-                    const int ot = __shfl_xor(st, d, 64);
-                    if (ov > sv || (ov == sv && ot < st)) {
-                        sv = ov;
-                        st = ot;
-                    }
-                }
-                if (st != 0x7fffffff && (sv > best || (sv == best && st < bestt))) {
-                    best = sv;
-                    bestt = st;
+    };
+    // the bins of the staged entries 64 lane .. 64 lane + 63 (a pixel's are in
+    // order: most of its chunks are out of a block's reach)
+    int first = 0, last = -1;
+    if (STAGED)
+        each([&](uint32_t v, uint32_t x) {
+            const uint32_t t = (uint32_t)ent_bin(v);
+            const uint32_t a = wave_reduce<OpMin>(t), b = wave_reduce<OpMax>(t < (uint32_t)T ? t : 0u);
+            const bool here = (uint32_t)lane == (x - lane) >> 6;
+            first = here ? (int)a : first;
+            last = here ? (int)b : last;
+        });
+    // the same for entries of bins lo .. hi at least
+    auto each_in = [&](int lo, int hi, auto f) {
+        if constexpr (STAGED) {
+            for (unsigned long long c = __ballot(first <= hi && last >= lo); c; c &= c - 1) {
+                const uint32_t x = 64u * (uint32_t)__builtin_ctzll(c) + lane;
+                f(x < n ? list[x] : 0xffff0000u, x);
+            }
+        } else {
+            each(f);
+        }
+    };
+    // adds an entry's terms to the bounds (or takes them away)
+    auto bound = [&](uint32_t v, bool away) {
+        const int t = ent_bin(v);
+        if (t >= T) return;
+        const Score z = (Score)(uint32_t)ent_cnt(v);
+        const int b0 = max(0, t + o - L + 1) >> 6, b1 = min(T - 1, t + o) >> 6;
+        for (int b = b0; b <= b1; ++b) {
+            const Score w = z * (Score)(uint32_t)qwin[t + o - 64 * b];
+            atomicAdd(&ub[b], away ? (Score)0 - w : w);
+        }
+    };
+    unsigned long long nt = 0;
+    for (int b = lane; b < nb; b += 64) ub[b] = 0;
+    wave_sync();
+    each([&](uint32_t v, uint32_t) {
+        bound(v, false);
+        nt += ent_bin(v) < T ? (uint32_t)ent_cnt(v) : 0u;
+    });
+    const long long ntot = wave_sum((long long)nt);
+    wave_sync();
+    for (int it = 0; it < A.p.k_init; ++it) {
+        Score best = 0;
+        int bestt = NO_TAU;
+        uint32_t done = 0;                      // bit u: block lane + 64 u scored in this round
+        while (true) {
+            // the unscored block with the largest bound (the first on ties)
+            Score bu = 0;
+            int bb = NO_TAU;
+            for (int u = 0; lane + 64 * u < nb; ++u) {
+                if ((done >> u) & 1u) continue;
+                const Score x = ub[lane + 64 * u];
+                if (bb == NO_TAU || x > bu) {
+                    bu = x;
+                    bb = lane + 64 * u;
                 }
             }
-            if (bestt == 0x7fffffff) break;          // every tau suppressed
-            const int a = max(0, bestt - m.wl), c = min(T - 1, bestt + m.wr);
-            int win = 0;
-            for (int tb = a + lane; tb <= c; tb += 64) win += !pk.claimed(m, tb);
-            win = wave_sum(win);
-            long long nwin = 0;
-            for (int l = 0; l < npl; ++l) {
-                const uint2 rg = lists[l];
-                for (uint32_t e = rg.x + lane; e < rg.y; e += 64) {
-                    const uint32_t v = ent[e];
-                    const int tb = ent_bin(v);
-                    if (tb >= a && tb <= c && !pk.claimed(m, tb)) nwin += ent_cnt(v);
+            const Score mx = wave_max(bu);
+            bb = (int)wave_reduce<OpMin>((uint32_t)(bu == mx ? bb : NO_TAU));
+            if (bb == NO_TAU) break;
+            if (bestt != NO_TAU && (mx < best || (mx == best && (bb << 6) > bestt))) break;
+            // exact scores of LIST_BLOCKS blocks around it
+            const int s0 = max(0, min(bb - LIST_BLOCKS / 2, nb - LIST_BLOCKS)), lo = 64 * s0 - o;
+            const int hi = lo + 64 * LIST_BLOCKS - 1 + L - 1;
+            const int32_t* ql = q + LIST_PAD - lo - lane;  // lag t - tau + o of this lane's first tau
+            Score sc[LIST_BLOCKS] = {};
+            unsigned long long in;
+            uint32_t v;
+            auto take = [&] {                              // the next few entries' terms
+                constexpr int N = LIST_TAKE;
+                int tt[N], zz[N], w[N][LIST_BLOCKS];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)v, in ? __builtin_ctzll(in) : 0);
+                    tt[u] = in ? ent_bin(e) : lo;
+                    zz[u] = in ? ent_cnt(e) : 0;
+                    in &= in - 1;
                 }
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+#pragma unroll
+                    for (int k = 0; k < LIST_BLOCKS; ++k) w[u][k] = ql[tt[u] - 64 * k];
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+#pragma unroll
+                    for (int k = 0; k < LIST_BLOCKS; ++k)
+                        sc[k] += sizeof(Score) == 4 ? (Score)__umul24(zz[u], w[u][k])
+                                                    : (Score)(uint32_t)zz[u] * (Score)(uint32_t)w[u][k];
+            };
+            each_in(lo, hi, [&](uint32_t e, uint32_t) {
+                const int t = ent_bin(e);
+                v = e;
+                in = __ballot(t >= lo && t <= hi && t < T && (STAGED || !pk.claimed(m, t)));
+                while (in) take();
+            });
+            Score sk = 0, smx;
+            int tk = NO_TAU;
+#pragma unroll
+            for (int k = 0; k < LIST_BLOCKS; ++k) {
+                const int b = s0 + k, tau = 64 * b + lane;
+                if (b < nb && lane == (b & 63)) done |= 1u << (b >> 6);
+                const Score x = tau < T && !pk.suppressed(tau, m.wnms) ? sc[k] + 1 : 0;      // (0: none)
+                tk = x > sk ? tau : tk;
+                sk = max(sk, x);
             }
-            nwin = wave_sum(nwin);
-            const double bw = (double)ntot * (double)win / (double)T;
-            const double d = (double)nwin - bw;
-            const bool accept = win > 0 && nwin >= p.n_min && d >= 0.0 && d * d >= k2 * bw;
-            if (!accept) break;
-            pk.push(bestt, win);
+            smx = wave_max(sk);
+            const int st = (int)wave_reduce<OpMin>((uint32_t)(sk == smx ? tk : NO_TAU));
+            if (smx != 0 && (bestt == NO_TAU || smx - 1 > best || (smx - 1 == best && st < bestt))) {
+                best = smx - 1;
+                bestt = st;
+            }
+        }
+        if (bestt == NO_TAU) break;             // every tau suppressed
+        const int a = max(0, bestt - m.wl), c = min(T - 1, bestt + m.wr);
+        int win = 0;
+        for (int tb = a + lane; tb <= c; tb += 64) win += !pk.claimed(m, tb);
+        win = wave_sum(win);
+        unsigned long long nw = 0;
+        each_in(a, c, [&](uint32_t v, uint32_t) {
+            const int t = ent_bin(v);
+            if (t >= a && t <= c && (STAGED || !pk.claimed(m, t))) nw += (uint32_t)ent_cnt(v);
+        });
+        const long long nwin = wave_sum((long long)nw);
+        const double bw = (double)ntot * (double)win / (double)T;
+        const double d = (double)nwin - bw;
+        const double k2 = A.p.kappa * A.p.kappa;
+        if (!(win > 0 && nwin >= A.p.n_min && d >= 0.0 && d * d >= k2 * bw)) break;
+        pk.push(bestt, win);
+        if (STAGED && it + 1 < A.p.k_init) {
+            each_in(a, c, [&](uint32_t v, uint32_t x) {
+                const int t = ent_bin(v);
+                if (t < a || t > c) return;
+                bound(v, true);
+                list[x] = 0xffff0000u;
+            });
+            wave_sync();
         }
     }
+}
+
+// The same for a window of n entries, area its LDS.
+__device__ __forceinline__ void list_search_any(const PoolRows& W, uint32_t n, v4i* area, Peaks& pk)
+{
+    const InitArgs& A = init_args();
+    unsigned long long* ub = reinterpret_cast<unsigned long long*>(area);
+    uint32_t* list = reinterpret_cast<uint32_t*>(ub + ((A.m.T + 63) >> 6));
+    if (n > A.cap) {
+        list_search<unsigned long long, false>(W, list, n, ub, pk);
+        return;
+    }
+    // the rows side by side, three rows' first entries in flight at a time
+    const int lane = threadIdx.x & 63, T = A.m.T;
+    const uint32_t len = W.re - W.rs, at = wave_incl_scan(len) - len;
+    uint32_t nt = 0;                            // (at most 4096 x 65535)
+    for (int r0 = 0; r0 < W.side; r0 += 3) {
+        uint32_t a[3], k[3], d[3], v[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            a[r] = (uint32_t)__builtin_amdgcn_readlane((int)W.rs, r0 + r);
+            k[r] = (uint32_t)__builtin_amdgcn_readlane((int)len, r0 + r);
+            d[r] = (uint32_t)__builtin_amdgcn_readlane((int)at, r0 + r);
+            v[r] = (uint32_t)lane < k[r] ? W.ent[a[r] + lane] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            for (uint32_t x = lane; x < k[r]; x += 64) {
+                if (x >= 64) v[r] = W.ent[a[r] + x];
+                list[d[r] + x] = v[r];
+                nt += ent_bin(v[r]) < T ? (uint32_t)ent_cnt(v[r]) : 0u;
+            }
+    }
+    wave_sync();
+    const uint32_t ntot = wave_reduce<OpAdd>(nt);
+    if (A.m.qmax < 1 << 24 && (unsigned long long)ntot * (unsigned long long)A.m.qmax <= 0xfffffffeull)
+        list_search<uint32_t, true>(W, list, n, reinterpret_cast<uint32_t*>(ub), pk);
+    else
+        list_search<unsigned long long, true>(W, list, n, ub, pk);
 }
 
 // The peaks of the wavefront's pixels, pixel x's peak k in lane 4 x + k, from
@@ -1075,7 +1154,7 @@ __global__ __launch_bounds__(64 * INIT_WAVES, INIT_OCC) void k_init(InitArgs arg
         const InitArgs& A = init_args();
         // whole wavefront (pixels of other IRF classes: their own launch); no workgroup barriers here
         if (q.pix >= (uint32_t)A.sh.P) break;
-        if (in_class(A.m, q.pix)) {
+        if (in_class(A.m, q.pix) && !(KS == 0 && A.left && A.s.cnt[q.pix] != INIT_LEFT)) {
             const PoolRows W = q.rows(A.sh, A.p.r_init, A.off, A.ent);
             const uint32_t e0 = A.off[q.pix], e1 = A.off[q.pix + 1];
             const float G = gain_at(A.gain, q.pix);
@@ -1107,19 +1186,60 @@ __global__ __launch_bounds__(64 * INIT_WAVES, INIT_OCC) void k_init(InitArgs arg
     rec.finish(first);
 }
 
-// The pixels k_init left (args.all: every pixel of the launch), a wavefront
-// looking through args.ppw <= 64 consecutive pixels: pools with over 127
-// photons in a bin from two planes of bytes (args.wide: they fit), the rest
-// from the lists.
-__global__ __launch_bounds__(64 * INIT_WAVES) void k_init_rest(InitArgs args)
+// The same pixels per wavefront, by the list search: those of at most
+// args.limit pooled entries, if the launch's pixels have at most args.mean on
+// average (the others are left).
+__global__ __launch_bounds__(64 * INIT_WAVES) void k_init_lists(InitArgs args)
+{
+    extern __shared__ v4i smem[];
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    v4i* area = smem + (size_t)wv * (args.area / 16);
+    const double hfull = window_mass(args.m);
+    const int ppw = args.ppw, side = 2 * args.p.r_init + 1;
+    const unsigned long long pooled = (unsigned long long)(args.off[args.sh.P] - args.off[0]) * (unsigned)(side * side);
+    const bool any = pooled <= (unsigned long long)args.mean * (unsigned long long)args.sh.P;
+    const uint32_t first = (xcd_block(blockIdx.x, gridDim.x) * nw + wv) * ppw;
+    InitRecords rec;
+    rec.clear();
+    InitPixel q;
+    q.at(first, args.sh);
+    for (int x = 0; x < ppw; ++x) {
+        const InitArgs& A = init_args();
+        if (q.pix >= (uint32_t)A.sh.P) break;   // (whole wavefront; no workgroup barriers here)
+        if (in_class(A.m, q.pix) && !(A.left && A.s.cnt[q.pix] != INIT_LEFT)) {
+            const PoolRows W = q.rows(A.sh, A.p.r_init, A.off, A.ent);
+            const uint32_t e0 = A.off[q.pix], e1 = A.off[q.pix + 1];
+            const float G = gain_at(A.gain, q.pix);
+            const uint32_t n = wave_reduce<OpAdd>(W.re - W.rs);
+            if (!(G > 0.f)) {
+                rec.set_mode(x, PIX_DEAD);
+            } else if (!any || n > A.limit) {
+                rec.set_mode(x, PIX_LEFT);
+            } else {
+                Peaks pk;
+                pk.clear();
+                list_search_any(W, n, area, pk);
+                rec.set(x, pk, G, e0 + lane < e1 ? A.ent[e0 + lane] : 0u, e0, e1, hfull);
+            }
+        }
+        q.next(init_args().sh);
+    }
+    rec.finish(first);
+}
+
+// The pixels left over, a wavefront looking through args.ppw <= 64 consecutive
+// pixels: pools with over 127 photons in a bin from two planes of bytes
+// (args.wide: they fit), the rest from the lists.
+__global__ __launch_bounds__(64 * INIT_WAVES, INIT_OCC) void k_init_rest(InitArgs args)
 {
     extern __shared__ v4i smem[];
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int chunk = args.ppw;
     const long long first = ((long long)blockIdx.x * nw + wv) * chunk;
-    bool mine = lane < chunk && first + lane < args.sh.P && in_class(args.m, first + lane);
-    if (mine) mine = args.all || args.s.cnt[first + lane] == INIT_LEFT;
+    const bool mine = lane < chunk && first + lane < args.sh.P && in_class(args.m, first + lane) &&
+                      args.s.cnt[first + lane] == INIT_LEFT;
     unsigned long long todo = __ballot(mine);
     if (!todo) return;                      // (no workgroup barriers here)
     const InitPool<0, true> P = init_pool<0, true>(args.m, smem + (size_t)wv * (args.area / 16));
@@ -1130,30 +1250,23 @@ __global__ __launch_bounds__(64 * INIT_WAVES) void k_init_rest(InitArgs args)
         InitPixel q;
         q.at((uint32_t)(first + __builtin_ctzll(todo)), A.sh);
         const PoolRows W = q.rows(A.sh, A.p.r_init, A.off, A.ent);
-        const uint32_t e0 = A.off[q.pix], e1 = A.off[q.pix + 1];
+        const uint32_t e0 = A.off[q.pix], e1 = A.off[q.pix + 1], n = wave_reduce<OpAdd>(W.re - W.rs);
         const float G = gain_at(A.gain, q.pix);
         InitRecords rec;
         rec.clear();
-        if (!(G > 0.f)) {
-            rec.set_mode(0, PIX_DEAD);
-        } else {
-            Peaks pk;
-            pk.clear();
-            bool dense = args.wide && wave_reduce<OpAdd>(W.re - W.rs) <= 65536u;
-            if (dense) {
-                uint32_t nt = 0;
-                dense = !fill_planes(P, W, A.off, q.pix, A.sh.cols, q.i, q.j, A.sh.rows, m.T, m.o, nt);
-                const uint32_t ntot = wave_reduce<OpAdd>(nt);
-                dense = dense && ntot <= 1u << 24;       // the products' sums stay below 2^31
-                if (dense) dense_search(P, ntot, pk);
-            }
-            if (!dense) {
-                const long long fr = q.pix / ((long long)A.sh.rows * A.sh.cols);
-                lists_search(m, A.p, A.sh, A.off, A.ent, fr, q.i, q.j, reinterpret_cast<unsigned long long*>(P.Z), pk);
-            }
-            wave_sync();
-            rec.set(0, pk, G, e0 + lane < e1 ? A.ent[e0 + lane] : 0u, e0, e1, hfull);
+        Peaks pk;
+        pk.clear();
+        bool dense = A.wide && n <= 65536u;
+        if (dense) {
+            uint32_t nt = 0;
+            dense = !fill_planes(P, W, A.off, q.pix, A.sh.cols, q.i, q.j, A.sh.rows, m.T, m.o, nt);
+            const uint32_t ntot = wave_reduce<OpAdd>(nt);
+            dense = dense && ntot <= 1u << 24;           // the products' sums stay below 2^31
+            if (dense) dense_search(P, ntot, pk);
         }
+        if (!dense) list_search_any(W, n, P.Z, pk);
+        wave_sync();
+        rec.set(0, pk, G, e0 + lane < e1 ? A.ent[e0 + lane] : 0u, e0, e1, hfull);
         rec.finish(q.pix);
     }
 }
@@ -1352,37 +1465,71 @@ static int init_waves(size_t area, size_t tables)
 static int pixels_per_wave(long long P) { return P >= 131072 ? 8 : P >= 32768 ? 4 : P >= 16384 ? 2 : 1; }
 static_assert(INIT_PPW_MAX >= 8, "a wavefront's pixels have a lane per peak");
 
-template <int KS>
-static hipError_t launch_ks(InitArgs a, hipStream_t st)
+// A launch of one of the kernels over pixels, `area` bytes of LDS per wavefront.
+static_assert(init_dense_area(1024 * PICK_REGS, 4, 1) + 2 * 4 * 64 * 16 <= 65536, "a pool beside the weights");
+template <class Kernel>
+static hipError_t launch_pixels(Kernel kernel, InitArgs a, size_t area, size_t tables, hipStream_t st)
 {
-    const size_t tables = (size_t)2 * KS * 64 * 16;
+    a.area = (int)((area + 15) / 16 * 16);
     const int nw = init_waves(a.area, tables);
     a.ppw = pixels_per_wave(a.sh.P);
     const long long per = (long long)nw * a.ppw;
-    hipLaunchKernelGGL(k_init<KS>, dim3((unsigned)((a.sh.P + per - 1) / per)), dim3(64 * nw), nw * a.area + tables, st,
-                       a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((a.sh.P + per - 1) / per)), dim3(64 * nw), nw * a.area + tables, st, a);
     return hipGetLastError();
+}
+
+// Average pool up to which a launch's pixels take the list search, where the
+// weights' steps are not in registers (L > 241 or T > 8192).  The dense search
+// costs by bins and steps, the list search by entries.  20 k pixels, pools of
+// 30 / 100 / 400 entries, lists against dense, us: 8200 bins, 19-bin IRF 126 /
+// 441 / 1243 against 388 / 236 / 161; 20000 bins 117 / 366 / 1256 against 1286 /
+// 1239 / 442; 8192 bins, 501-bin IRF 112 / 161 / 420 against 276 / 259 / 265; 4613
+// bins, 2001-bin IRF 193 / 351 / 1434 against 561 / 462 / 498.  One choice for the
+// launch: a line drawn pixel by pixel lets pools near it take both kernels'
+// time (206 us where the one takes 147 and the other 136).
+static uint32_t list_mean(int T, int ks)
+{
+    return (uint32_t)std::min<long long>(INIT_LIST, (long long)T * T * (std::min(ks, 16) + 1) / 3000000);
 }
 
 hipError_t launch_init(const DevModel& m, const DevParams& p, const Shape& sh, const uint32_t* off,
                        const uint32_t* ent, const float* gain, DevState s, hipStream_t st)
 {
     if (sh.P == 0) return hipSuccess;
-    InitArgs a{m, p, sh, off, ent, gain, s, 1, (int)init_area(m.T, m.qa ? m.ks : 0, p.r_init, 1), m.qa ? 0 : 1, 0};
+    InitArgs a{m, p, sh, off, ent, gain, s, 1, 0, ~0u, (uint32_t)INIT_LIST, (uint32_t)INIT_LIST, 0, 0};
+    const size_t lists = init_list_area(m.T, INIT_LIST), tables = (size_t)2 * m.ks * 64 * 16;
+    if (!m.qa) {
+        const hipError_t e = launch_pixels(k_init_lists, a, lists, 0, st);
+        if (e != hipSuccess) return e;
+        // larger pools in fewer wavefronts: 10 k pixels, pools of 1510 entries of
+        // 40000 bins 5.6 ms, 11.6 ms read from memory for every block
+        a.limit = ~0u;
+        a.cap = INIT_LONG_LIST;
+        a.left = 1;
+        return launch_pixels(k_init_lists, a, init_list_area(m.T, INIT_LONG_LIST), 0, st);
+    }
+    const size_t pool = init_dense_area(m.T, m.ks, 1);
     hipError_t e = hipSuccess;
-    switch (!m.qa ? -1 : m.T > 1024 * PICK_REGS ? 0 : m.ks) {
-    case -1: break;
-    case 1: e = launch_ks<1>(a, st); break;
-    case 2: e = launch_ks<2>(a, st); break;
-    case 3: e = launch_ks<3>(a, st); break;
-    case 4: e = launch_ks<4>(a, st); break;
-    default: e = launch_ks<0>(a, st); break;
+    switch (m.T > 1024 * PICK_REGS ? 0 : m.ks) {
+    case 1: e = launch_pixels(k_init<1>, a, pool, tables, st); break;
+    case 2: e = launch_pixels(k_init<2>, a, pool, tables, st); break;
+    case 3: e = launch_pixels(k_init<3>, a, pool, tables, st); break;
+    case 4: e = launch_pixels(k_init<4>, a, pool, tables, st); break;
+    default:
+        a.mean = list_mean(m.T, m.ks);
+        if (a.mean >= 32) {                    // (below, hardly a pool: not worth the launch)
+            e = launch_pixels(k_init_lists, a, lists, 0, st);
+            if (e != hipSuccess) return e;
+            a.left = 1;
+        }
+        e = launch_pixels(k_init<0>, a, pool, 0, st);
     }
     if (e != hipSuccess) return e;
     // the pixels left over: enough wavefronts to fill the chip if that is all
     // of them, at most 64 pixels each (one count per lane)
-    a.wide = m.qa && init_area(m.T, m.ks, p.r_init, 2) <= 65536;
-    a.area = (int)init_area(m.T, a.wide ? m.ks : 0, p.r_init, 2);
+    const size_t planes = init_dense_area(m.T, m.ks, 2);
+    a.wide = planes <= 65536;
+    a.area = (int)(((a.wide ? std::max(planes, lists) : lists) + 15) / 16 * 16);
     const int nw = init_waves(a.area, 0);
     a.ppw = (int)std::max(1ll, std::min(64ll, sh.P / 8192));
     const long long per = (long long)nw * a.ppw;

@@ -14,8 +14,11 @@ constexpr int KM = RT3D_K_MAX;
 // Observation model tables on the device (built on the host in FP64).
 struct DevModel {
     const float4*  cr;    // Catmull-Rom segment k-1 (samples k..k+1): cubic coefficients (c0, c1, c2, c3)
-    const int32_t* q;     // log-matched-filter weights, 16 fractional bits
-    const int32_t* qst;   // range-maximum table of q: qst[l * L + k] = max q[k .. k + 2^l - 1]
+    // log-matched-filter weights q, 16 fractional bits, between zeros on each side
+    // (lag x at q[LIST_PAD + x]), and their largest over 64 lags: qwin[x] = max of
+    // lags x - 63 .. x
+    const int32_t* q;
+    const int32_t* qwin;
     // q as digits for the integer matrix cores, q = 2^qshift qc - 128 e1 - e0:
     // [qc, e1, e0][ks steps of 64 lags][64 lanes][16 bytes], lane i + 16 g,
     // byte b of step s holding row i's value of lag 64 s + 16 g + b - i

@@ -36,7 +36,7 @@ struct IrfTables {
     float4* d_cr = nullptr;
     double* d_stab = nullptr;
     int32_t* d_q = nullptr;
-    int32_t* d_qst = nullptr;
+    int32_t* d_qwin = nullptr;
     int8_t* d_qa = nullptr;            // q as matrix-core digits (nullptr: the dense search does not apply)
     int qshift = 0, qmax = 0;
     double* d_hbar = nullptr;
@@ -326,18 +326,13 @@ rt3d_status build_irf(const double* irf, uint32_t irf_len, int32_t irf_origin, i
     std::vector<int32_t> q(L);
     const double inv_eps = p->sbr_guess * (double)T;
     for (int k = 0; k < L; ++k) q[k] = (int32_t)std::llround(std::log1p(t.hbar[k] * inv_eps) * 65536.0);
-    // range-maximum table of q: level l holds max q[k .. k + 2^l - 1]
-    int nlev = 1;
-    while ((1 << nlev) <= L) ++nlev;
-    std::vector<int32_t> qst((size_t)nlev * L);
-    for (int k = 0; k < L; ++k) qst[k] = q[k];
-    for (int l = 1; l < nlev; ++l)
-        for (int k = 0; k < L; ++k) {
-            const int a = qst[(size_t)(l - 1) * L + k];
-            const int k2 = k + (1 << (l - 1));
-            const int b = k2 < L ? qst[(size_t)(l - 1) * L + k2] : a;
-            qst[(size_t)l * L + k] = std::max(a, b);
-        }
+    // the same between zeros, and the largest of 64 lags (DevModel::q, qwin)
+    std::vector<int32_t> qpad((size_t)L + 2 * LIST_PAD, 0), qwin((size_t)L + 63);
+    std::copy(q.begin(), q.end(), qpad.begin() + LIST_PAD);
+    for (int x = 0; x < L + 63; ++x) {
+        const auto from = qpad.begin() + LIST_PAD - 63 + x;
+        qwin[x] = *std::max_element(from, from + 64);
+    }
     // the weights as digits for the integer matrix cores (DevModel::qa): qc =
     // ceil(q / 2^qshift) up to 127, the rest e = 2^qshift qc - q in two
     // digits up to 127 (six bits in the lower one left weights above 15.9 out,
@@ -365,27 +360,27 @@ rt3d_status build_irf(const double* irf, uint32_t irf_len, int32_t irf_origin, i
     hipError_t e = hipMalloc(&t.d_cr, sizeof(float4) * cr.size());
     if (e == hipSuccess && !qa.empty()) e = hipMalloc(&t.d_qa, qa.size());
     if (e == hipSuccess && !qa.empty()) e = hipMemcpy(t.d_qa, qa.data(), qa.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc(&t.d_q, sizeof(int32_t) * q.size());
-    if (e == hipSuccess) e = hipMalloc(&t.d_qst, sizeof(int32_t) * qst.size());
+    if (e == hipSuccess) e = hipMalloc(&t.d_q, sizeof(int32_t) * qpad.size());
+    if (e == hipSuccess) e = hipMalloc(&t.d_qwin, sizeof(int32_t) * qwin.size());
     if (e == hipSuccess) e = hipMalloc(&t.d_hbar, sizeof(double) * L);
     if (e == hipSuccess && t.s_np > 0) e = hipMalloc(&t.d_stab, sizeof(double) * t.s_tab.size());
     if (e == hipSuccess && t.s_np > 0)
         e = hipMemcpy(t.d_stab, t.s_tab.data(), sizeof(double) * t.s_tab.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(t.d_cr, cr.data(), sizeof(float4) * cr.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(t.d_q, q.data(), sizeof(int32_t) * q.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(t.d_qst, qst.data(), sizeof(int32_t) * qst.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(t.d_q, qpad.data(), sizeof(int32_t) * qpad.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(t.d_qwin, qwin.data(), sizeof(int32_t) * qwin.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(t.d_hbar, t.hbar.data(), sizeof(double) * L, hipMemcpyHostToDevice);
     return e == hipSuccess ? RT3D_OK : RT3D_E_DEVICE;
 }
 
 void free_irf(IrfTables& t)
 {
-    for (void* ptr : {(void*)t.d_cr, (void*)t.d_stab, (void*)t.d_q, (void*)t.d_qst, (void*)t.d_qa, (void*)t.d_hbar})
+    for (void* ptr : {(void*)t.d_cr, (void*)t.d_stab, (void*)t.d_q, (void*)t.d_qwin, (void*)t.d_qa, (void*)t.d_hbar})
         if (ptr) (void)hipFree(ptr);
     t.d_cr = nullptr;
     t.d_stab = nullptr;
     t.d_q = nullptr;
-    t.d_qst = nullptr;
+    t.d_qwin = nullptr;
     t.d_qa = nullptr;
     t.d_hbar = nullptr;
 }
@@ -442,7 +437,7 @@ DevModel dev_model(const rt3d_ctx* c, int k = 0, const uint8_t* cls = nullptr, c
     DevModel m{};
     m.cr = t.d_cr;
     m.q = t.d_q;
-    m.qst = t.d_qst;
+    m.qwin = t.d_qwin;
     m.qa = t.d_qa;
     m.ks = init_ks(t.L);
     m.qshift = t.qshift;
