@@ -18,11 +18,12 @@
 // the counts and every slot of the tile with a halo in LDS in one round of
 // loads (depths in FP64, normals; a second round for the live slots only,
 // after the counts, cost more time than the bytes it saved), then one thread
-// per live point, listed by pixel, fits and projects it, accumulating the
-// sphere moments over the window from LDS in FP32, in coordinates local to the
-// query (depth differences formed in FP64); under the orthographic map the
-// halo covers only the pixels whose lateral offset stays below h
-// (apss_moments), under the pinhole camera see k_apss_pinhole.
+// per live point, listed by pixel (tiles of many points: one per pixel, its
+// points at once), fits and projects it, accumulating the sphere moments over
+// the window from LDS in FP32, in coordinates local to the query (depth
+// differences formed in FP64); under the orthographic map the halo covers only
+// the pixels whose lateral offset stays below h (apss_moments), under the
+// pinhole camera see k_apss_pinhole.
 // Windows whose staged tile does not fit in 64 KB of LDS take a variant with
 // eight lanes per pixel reading the state from global memory, the partial
 // moment sets meeting in a fixed wavefront-shuffle tree.
@@ -68,20 +69,83 @@ int apss_staged_halo(double h_apss, double p_xy, int R)
 
 // The orthographic map, staged halo p.apss_Rs.  carry: also copy the count,
 // background and intensities to `out` (else `out` receives only the depths and
-// normals of the live slots).  A thread per point leaves no lane to a pixel
-// without points and no slot to wait for another: 636 k pixels of 1.4 points
-// take 41 us (the planes read and written at the rate of a copy would take 22),
-// against 49 us for a thread per pixel that kept the moments of all its slots;
-// a point grid of 74 k pixels 12 us against 17.
-constexpr int APT = 512;
-__global__ __launch_bounds__(APT, 4) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in, DevState out,
-                                                      int only_above, int carry)
+// normals of the live slots).  A tile of at most APSS_SPARSE points takes a
+// thread per point, which leaves no lane to a pixel without points and no slot
+// to wait for another; with more, a thread per pixel takes all its points past
+// each neighbour at once, which then is read once for all of them.  The sums
+// are the same in either.  636 k pixels of 1.5 points, windows of 1 / 2 / 5 rings:
+// 43 / 76 / 380 us by points, 47 / 91 / 445 by pixels (the planes read and written
+// at the rate of a copy would take 22); 262 k pixels of 2.8 points right after
+// the initialisation, 1 / 2 rings: 36 / 66 us by points, 27 / 45 by pixels.
+// Four wavefronts per SIMD, nothing spilled (five: 4% slower on dense tiles but
+// for 636 k pixels with 1 ring, 4% faster).  512 threads instead of 256 are up to
+// 7% (1 ring) and 25% (5 rings) faster by points, but leave a thread per pixel
+// half of the wavefronts: two slots a thread took 20% longer there.
+constexpr int APSS_SPARSE = 448;   // points of a tile of 256 pixels
+
+// LDS bytes of the orthographic kernel: depths, normals, counts, the list.
+inline size_t apss_staged_bytes(int R)
+{
+    const size_t NS = (ATX + 2 * (size_t)R) * (ATY + 2 * (size_t)R);
+    return NS * (KM * sizeof(double) + 3 * KM * sizeof(float) + sizeof(uint8_t)) + APSS_SPARSE * sizeof(uint16_t);
+}
+
+// The moments of a pixel's n points (depths tq) at once, its neighbours in the
+// window's order: each neighbour is read once.
+__device__ __forceinline__ void apss_moments_slots(const double* tl, const float* nl, const uint8_t* cl, int NS, int SX,
+                                                   int xc, int R, float h2, float pxy, double dz,
+                                                   const double (&tq)[KM], int n, Moments (&s)[KM])
+{
+    const float inv_h2 = 1.f / h2;
+    for (int di = -R; di <= R; ++di) {
+        const float yy = (float)di * pxy;
+        for (int dj = -R; dj <= R; ++dj) {
+            const float yx = (float)dj * pxy;
+            const float dl = fmaf(yx, yx, yy * yy);
+            if (!(dl < h2)) continue;
+            const int x = xc + di * SX + dj;
+            const int cc = cl[x];
+#pragma unroll
+            for (int k = 0; k < KM; ++k) {
+                if (k >= cc) break;
+                const double t2 = tl[k * NS + x];
+                const float nx = nl[(0 * KM + k) * NS + x];
+                const float ny = nl[(1 * KM + k) * NS + x];
+                const float nz = nl[(2 * KM + k) * NS + x];
+                const float yn = fmaf(yx, nx, yy * ny);
+#pragma unroll
+                for (int q = 0; q < KM; ++q) {
+                    if (q >= n) break;
+                    const float yz = (float)((t2 - tq[q]) * dz);
+                    const float d2 = fmaf(yz, yz, dl);
+                    if (!(d2 < h2)) continue;
+                    float a = 1.f - d2 * inv_h2;
+                    a = a * a;
+                    const float w = a * a;
+                    s[q].W += w;
+                    s[q].Px = fmaf(w, yx, s[q].Px);
+                    s[q].Py = fmaf(w, yy, s[q].Py);
+                    s[q].Pz = fmaf(w, yz, s[q].Pz);
+                    s[q].Nx = fmaf(w, nx, s[q].Nx);
+                    s[q].Ny = fmaf(w, ny, s[q].Ny);
+                    s[q].Nz = fmaf(w, nz, s[q].Nz);
+                    s[q].PN = fmaf(w, fmaf(yz, nz, yn), s[q].PN);
+                    s[q].PP = fmaf(w, d2, s[q].PP);
+                    s[q].nn += 1.f;
+                }
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(ATX * ATY, 4) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in, DevState out,
+                                                            int only_above, int carry)
 {
     extern __shared__ double apss_lds[];
     const int R = p.apss_Rs, SX = ATX + 2 * R, NS = SX * (ATY + 2 * R);
     double* tl = apss_lds;                                      // [KM][NS] depths
     float* nl = reinterpret_cast<float*>(tl + KM * NS);         // [3][KM][NS] normals
-    int* cl = reinterpret_cast<int*>(nl + 3 * KM * NS);         // [NS] counts (0 outside the frame)
+    uint8_t* cl = reinterpret_cast<uint8_t*>(nl + 3 * KM * NS); // [NS] counts (0 outside the frame)
     const int tile0 = (int)xcd_block(blockIdx.x, gridDim.x);
     const int g = tile_group(tg, tile0);
     const Shape sh = group_shape(tg, g);
@@ -97,8 +161,8 @@ __global__ __launch_bounds__(APT, 4) void k_apss_tile(DevModel m, DevParams p, T
     // stage the counts and every slot of the tile and its halo (without
     // waiting for the counts)
     __shared__ int wave_points[ATX * ATY / 64];
-    uint16_t* pl = reinterpret_cast<uint16_t*>(cl + NS);        // [KM ATX ATY] points
-    for (int x = threadIdx.x; x < NS; x += APT) {
+    uint16_t* pl = reinterpret_cast<uint16_t*>(cl + NS);        // [APSS_SPARSE] points (NS is even)
+    for (int x = threadIdx.x; x < NS; x += ATX * ATY) {
         const int i2 = i0 - R + x / SX, j2 = j0 - R + x % SX;
         int c = 0;
         if (i2 >= 0 && i2 < sh.rows && j2 >= 0 && j2 < sh.cols) {
@@ -117,40 +181,56 @@ __global__ __launch_bounds__(APT, 4) void k_apss_tile(DevModel m, DevParams p, T
 #pragma unroll
             for (int k = 0; k < KM; ++k) tl[k * NS + x] = no_depth();
         }
-        cl[x] = c;
+        cl[x] = (uint8_t)c;
     }
     __syncthreads();
-    int c = 0;
-    if (threadIdx.x < ATX * ATY) {
-        const int ty = threadIdx.x / ATX, tx = threadIdx.x % ATX, i = i0 + ty, j = j0 + tx;
-        const bool inside = i < sh.rows && j < sh.cols;
-        c = inside ? cl[(ty + R) * SX + tx + R] : 0;
-        if (carry && inside) {
-            const long long pix = fbase + (long long)i * sh.cols + j;
-            out.cnt[pix] = (uint8_t)c;
-            out.b[pix] = in.b[pix];
+    const int ty = threadIdx.x / ATX, tx = threadIdx.x % ATX;
+    const bool inside = i0 + ty < sh.rows && j0 + tx < sh.cols;
+    const int xc = (ty + R) * SX + tx + R, c = inside ? cl[xc] : 0;
+    const long long pix = fbase + (long long)(i0 + ty) * sh.cols + j0 + tx;
+    if (carry && inside) {
+        out.cnt[pix] = (uint8_t)c;
+        out.b[pix] = in.b[pix];
 #pragma unroll
-            for (int k = 0; k < KM; ++k) out.r[k * S + pix] = in.r[k * S + pix];
-        }
+        for (int k = 0; k < KM; ++k) out.r[k * S + pix] = in.r[k * S + pix];
     }
-    const int points = list_points(c, wave_points, pl);
+    const int points = list_points(c, wave_points, pl, APSS_SPARSE);
     const float h = (float)p.h_apss, h2 = h * h;
-    const double dz = p.dz, reach = 1.001 * p.h_apss / dz;
-    for (int q = threadIdx.x; q < points; q += APT) {
-        const int pk = pl[q], k = pk % KM, px = pk / KM, ty = px / ATX, tx = px % ATX;
-        const int xc = (ty + R) * SX + tx + R;
-        const long long pix = fbase + (long long)(i0 + ty) * sh.cols + j0 + tx;
-        const int cq = cl[xc];
-        double tn = tl[k * NS + xc];
+    const double dz = p.dz, reach = 1.001 * p.h_apss / dz, tmax = (double)(m.T - 1);
+    auto finish = [&](int k, int xc, long long pix, double tq, bool fit, const Moments& v) {
+        double tn = tq;
         float on[3] = {nl[(0 * KM + k) * NS + xc], nl[(1 * KM + k) * NS + xc], nl[(2 * KM + k) * NS + xc]};
-        if (!(only_above >= 0 && cq <= only_above)) {
-            const Moments v = apss_moments(tl, NS, SX, xc, R, h2, (float)p.p_xy, dz, reach, tn, TileNormals{nl, NS});
-            apss_project(v.nn >= (float)p.m_min, v.W, v.Px, v.Py, v.Pz, v.Nx, v.Ny, v.Nz, v.PN, v.PP, h, h2, dz,
-                         (double)(m.T - 1), tn, on);
-        }
+        apss_project(fit && v.nn >= (float)p.m_min, v.W, v.Px, v.Py, v.Pz, v.Nx, v.Ny, v.Nz, v.PN, v.PP, h, h2, dz,
+                     tmax, tn, on);
         out.t[k * S + pix] = tn;
 #pragma unroll
         for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];
+    };
+    if (points > APSS_SPARSE) {
+        if (c == 0) return;
+        const bool fit = !(only_above >= 0 && c <= only_above);
+        double tq[KM];
+        Moments v[KM];
+#pragma unroll
+        for (int q = 0; q < KM; ++q) {
+            tq[q] = tl[q * NS + xc];
+            v[q] = Moments{};
+        }
+        if (fit) apss_moments_slots(tl, nl, cl, NS, SX, xc, R, h2, (float)p.p_xy, dz, tq, c, v);
+#pragma unroll
+        for (int q = 0; q < KM; ++q) {
+            if (q >= c) break;
+            finish(q, xc, pix, tq[q], fit, v[q]);
+        }
+        return;
+    }
+    for (int q = threadIdx.x; q < points; q += ATX * ATY) {
+        const int pk = pl[q], k = pk % KM, qy = pk / KM / ATX, qx = pk / KM % ATX, xq = (qy + R) * SX + qx + R;
+        const double tq = tl[k * NS + xq];
+        const bool fit = !(only_above >= 0 && cl[xq] <= only_above);
+        Moments v{};
+        if (fit) v = apss_moments(tl, NS, SX, xq, R, h2, (float)p.p_xy, dz, reach, tq, TileNormals{nl, NS});
+        finish(k, xq, fbase + (long long)(i0 + qy) * sh.cols + j0 + qx, tq, fit, v);
     }
 }
 
@@ -507,10 +587,9 @@ hipError_t launch_apss_tiles(const DevModel& m, const DevParams& p, const Tiles&
                            st, m, p, tg, in, out, only_above, (int)carry);
         return hipGetLastError();
     }
-    const size_t lds = apss_tile_bytes(p.apss_Rs) + KM * ATX * ATY * sizeof(uint16_t);
-    if (p.apss_Rs <= APSS_ROW && lds <= 65536) {
-        hipLaunchKernelGGL(k_apss_tile, dim3((unsigned)tg.tile0[tg.n]), dim3(APT), lds, st, m, p, tg,
-                           in, out, only_above, (int)carry);
+    if (p.apss_Rs <= APSS_ROW) {
+        hipLaunchKernelGGL(k_apss_tile, dim3((unsigned)tg.tile0[tg.n]), dim3(ATX * ATY), apss_staged_bytes(p.apss_Rs), st, m, p,
+                           tg, in, out, only_above, (int)carry);
         return hipGetLastError();
     }
     for (int g = 0; g < tg.n; ++g) {

@@ -18,8 +18,8 @@ static_assert(KM * (2 * APSS_ROW + 1) <= 64, "a row's slots: a bit each");
 // Lists the points of a tile of 256 pixels by pixel and slot (KM pixel + slot),
 // so that a thread can take a point: thread x < 256 gives its pixel's count c,
 // the others 0.  Every thread of the workgroup; returns the number of points,
-// the list complete.
-__device__ __forceinline__ int list_points(int c, int (&wave_points)[4], uint16_t* pl)
+// the list complete (left out when there are more than cap).
+__device__ __forceinline__ int list_points(int c, int (&wave_points)[4], uint16_t* pl, int cap = KM * 256)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int place = (int)wave_incl_scan((uint32_t)c);
@@ -32,6 +32,7 @@ __device__ __forceinline__ int list_points(int c, int (&wave_points)[4], uint16_
         place += q < w ? wave_points[q] : 0;
         points += wave_points[q];
     }
+    if (points > cap) return points;
     for (int k = 0; k < c; ++k) pl[place + k] = (uint16_t)(threadIdx.x * KM + k);
     __syncthreads();
     return points;
