@@ -397,6 +397,11 @@ bool iter_fits(const DevParams& p, int rb)
            iter_apss_bytes(p.apss_Rs) <= 32768;
 }
 
+long long iter_tiles(const Shape& sh)
+{
+    return (long long)sh.F * ((sh.rows + ITY - 1) / ITY) * ((sh.cols + ITX - 1) / ITX);
+}
+
 bool iter_tiles_add(Tiles& tg, long long base, const Shape& sh) { return tiles_add(tg, base, sh, ITX, ITY); }
 
 template <int LPP, bool TLDS>

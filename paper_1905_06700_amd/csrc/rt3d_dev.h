@@ -696,6 +696,7 @@ struct IterArgs {
     bool filter;
 };
 bool iter_fits(const DevParams& p, int rb);
+long long iter_tiles(const Shape& sh);
 bool iter_tiles_add(Tiles& tg, long long base, const Shape& sh);
 hipError_t launch_iter(const IterArgs& a, const Tiles& tg, int part, hipStream_t st);
 hipError_t launch_apss(const DevModel& m, const DevParams& p, const Shape& sh, DevState in,

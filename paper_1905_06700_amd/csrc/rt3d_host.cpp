@@ -645,19 +645,25 @@ CnnBuffers cnn_at(const CnnBuffers& b, long long base)
 
 // Whether the iterations run as three launches on tiles (k_iter.hip): APSS on
 // the orthographic map, one IRF, no step of the iteration timed by itself, and
-// at most ITER_PIXELS pixels.  Whole calls, three launches against six, us: one
-// frame of 20 k pixels 738 / 965, 40 k 839 / 1021, 80 k 1339 / 1393 (42 entries
-// per pixel), 1467 / 1594 (4 entries); two of 80 k 2225 / 1951 and 2429 / 2350,
-// with four lanes per pixel: above, the steps' own kernels with more workgroups
-// per CU are the faster ones.
-constexpr long long ITER_PIXELS = LANES8_PIXELS;
+// at most ITER_TILES tiles (eight workgroups per CU).  Whole calls of 44 entries
+// per pixel, three launches against six, us: one frame of 32 x 32 (32 tiles) 580 /
+// 890, 141 x 141 (648) 692 / 1021, 200 x 200 (1250) 868 / 1164, 256 x 256 (2048)
+// 1235 / 1399, 300 x 300 (2850) 1603 / 1685, 362 x 362 (4186) 2170 / 2134; with 6
+// entries 256 x 256 1050 / 1084, 300 x 300 1343 / 1278, 362 x 362 1810 / 1601.  Past
+// the line the steps' own kernels with more workgroups per CU are the faster
+// ones.  Tiles, not pixels: thin and tiny frames fill few lanes of theirs (a line
+// of 1 x 5000, 625 tiles: 568 / 762; 20000 x 1, 5000 tiles: 1889 / 991; 6000 of
+// 3 x 3: 2218 / 2015).
+constexpr long long ITER_TILES = 2048;
 
-bool iter_eligible(const rt3d_ctx* c, const Shape& sh, const uint8_t* cls)
+bool iter_eligible(const rt3d_ctx* c, const std::vector<Group>& groups, const uint8_t* cls)
 {
     const bool timed = c->prof_id == RT3D_KERNEL_DEPTH || c->prof_id == RT3D_KERNEL_APSS ||
                        c->prof_id == RT3D_KERNEL_INTENSITY || c->prof_id == RT3D_KERNEL_IFILTER ||
                        c->prof_id == RT3D_KERNEL_BKG || c->prof_id == RT3D_KERNEL_BFILTER;
-    return c->p.denoiser == RT3D_DENOISE_APSS && !cls && !(c->p.persp > 0) && !timed && sh.P <= ITER_PIXELS &&
+    long long tiles = 0;
+    for (const Group& g : groups) tiles += iter_tiles(g.sh);
+    return c->p.denoiser == RT3D_DENOISE_APSS && !cls && !(c->p.persp > 0) && !timed && tiles <= ITER_TILES &&
            iter_fits(dev_params(c), c->rb);
 }
 
@@ -1169,7 +1175,7 @@ rt3d_status rt3d_reconstruct(rt3d_ctx* c, const rt3d_input* in, rt3d_output* out
                     launch_loop(m, p, sh, off, ent, in->gain, w.A, w.B, w.btmp, c->d_bw, c->rb, c->p.n_iter, st));
     } else {
         DevState cur = w.A, alt = w.B;
-        if (iter_eligible(c, sh, cls)) {
+        if (iter_eligible(c, groups, cls)) {
             s = iterate_tiles(c, sh, groups, off, ent, in->gain, cur, alt, w.btmp, c->p.n_iter, st);
             if (s != RT3D_OK) return s;
         } else {
@@ -1513,7 +1519,8 @@ rt3d_status rt3d_debug_step(rt3d_ctx* c, int32_t step, const uint32_t* off, cons
         Workspace w;
         rt3d_status s = need_ws(c, sh.P, w);
         if (s != RT3D_OK) return s;
-        const bool small = iter_eligible(c, sh, cls);
+        const std::vector<Group> groups{Group{0, sh}};
+        const bool small = iter_eligible(c, groups, cls);
         DevState cur = O, alt = w.B;
         if (c->p.denoiser == RT3D_DENOISE_APSS) {
             // the planes that change buffers an odd number of times start in
@@ -1523,7 +1530,6 @@ rt3d_status rt3d_debug_step(rt3d_ctx* c, int32_t step, const uint32_t* off, cons
             if (!small) std::swap(cur.cnt, alt.cnt);
         }
         RT3D_HIP(c, launch_copy_state(sh, dev_state(in), cur, st));
-        const std::vector<Group> groups{Group{0, sh}};
         s = small ? iterate_tiles(c, sh, groups, off, ent, gain, cur, alt, w.btmp, 1, st)
                   : iterate(c, sh, groups, off, ent, gain, cur, alt, w.btmp, &w.cnn, cls, st);
         if (s != RT3D_OK) return s;
