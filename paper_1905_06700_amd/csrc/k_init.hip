@@ -1543,8 +1543,15 @@ hipError_t launch_init_normals(const DevParams& p, const Shape& sh, DevState s, 
     // rings that can hold a neighbour
     int R = p.apss_R;
     while (R > 0 && !((R * p.p_xy) * (R * p.p_xy) < p.h_apss * p.h_apss)) --R;
-    if (!(p.persp > 0.0) && R <= NORMALS_R) {
-        const Tiles tg = tiles_of(sh);
+    // Tiles where a frame fills them, or where a grid of them is small (what it
+    // costs then is its chain of reads): pixels a tile >= 24, or >= 4 with at most
+    // 2048 tiles.  Tiles against pixels, us: 1000 frames of 1 x 1 and more 16 to
+    // 200 / 10 to 12, 10000 of 2 x 2 41 / 22, 1 x 131072 34 / 17, 2000 of 3 x 3 15 / 41,
+    // 1 x 20000 11 / 15, 10000 of 5 x 5 53 / 68, 2 x 60000 26 to 68 / 29 to 59.
+    const Tiles tg = tiles_of(sh);
+    const long long tiles = tg.tile0[1];
+    const bool full = sh.P >= 24 * tiles || (sh.P >= 4 * tiles && tiles <= 2048);
+    if (!(p.persp > 0.0) && R <= NORMALS_R && full) {
         hipLaunchKernelGGL(k_init_normals_tile, dim3((unsigned)tg.tile0[1]), dim3(NT_THREADS), normals_tile_bytes(R),
                            st, p, sh, s, R);
         return hipGetLastError();
