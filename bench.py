@@ -121,11 +121,16 @@ MATRIX_INT8_PEAK_TOPS = 16 * 16 * 64 * 2 / 16 * 4 * 256 * 2.4e9 / 1e12
 # Kernel groups timed one at a time by the library's event timer.
 GROUPS = ["compact", "init", "normals", "depth", "apss", "intensity", "ifilter", "bkg", "bfilter", "output"]
 
-# Library sources each group's code lives in (for matching stored byte counters).
-GROUP_SOURCES = {"compact": ["k_compact.hip"], "init": ["k_init.hip"], "normals": ["k_init.hip"],
-                 "depth": ["k_steps.hip"], "intensity": ["k_steps.hip"], "bkg": ["k_steps.hip"],
-                 "apss": ["k_apss.hip"], "merge": ["k_apss.hip"], "ifilter": ["k_filter.hip"],
-                 "bfilter": ["k_filter.hip"], "output": ["k_filter.hip", "k_compact.hip"]}
+# Library sources each group's code lives in, with the headers it takes code
+# from (for matching stored byte counters; rt3d_dev.h is in every group).
+STEP_SOURCES = ["k_steps.hip", "rt3d_steps.h"]
+POINT_SOURCES = ["k_apss.hip", "rt3d_points.h"]
+INIT_SOURCES = ["k_init.hip", "rt3d_init.h", "rt3d_points.h"]
+GROUP_SOURCES = {"compact": ["k_compact.hip"], "init": INIT_SOURCES, "normals": INIT_SOURCES,
+                 "depth": STEP_SOURCES, "intensity": STEP_SOURCES, "bkg": STEP_SOURCES,
+                 "apss": POINT_SOURCES, "merge": POINT_SOURCES, "ifilter": ["k_filter.hip", "rt3d_points.h"],
+                 "bfilter": ["k_filter.hip", "rt3d_points.h"],
+                 "output": ["k_filter.hip", "rt3d_points.h", "k_compact.hip"]}
 
 
 def algorithmic_bytes(kernel, F, N, T, E, pts):
