@@ -18,8 +18,8 @@
 // the counts and every slot of the tile with a halo in LDS in one round of
 // loads (depths in FP64, normals; a second round for the live slots only,
 // after the counts, cost more time than the bytes it saved), then one thread
-// per live point, listed by pixel (tiles of many points: one per pixel, its
-// points at once), fits and projects it, accumulating the sphere moments over
+// per live point, listed by pixel (tiles of many points: one per two slots of a
+// pixel), fits and projects it, accumulating the sphere moments over
 // the window from LDS in FP32, in coordinates local to the query (depth
 // differences formed in FP64); under the orthographic map the halo covers only
 // the pixels whose lateral offset stays below h (apss_moments), under the
@@ -71,17 +71,22 @@ int apss_staged_halo(double h_apss, double p_xy, int R)
 // background and intensities to `out` (else `out` receives only the depths and
 // normals of the live slots).  A tile of at most APSS_SPARSE points takes a
 // thread per point, which leaves no lane to a pixel without points and no slot
-// to wait for another; with more, a thread per pixel takes all its points past
-// each neighbour at once, which then is read once for all of them.  The sums
-// are the same in either.  636 k pixels of 1.5 points, windows of 1 / 2 / 5 rings:
-// 43 / 76 / 380 us by points, 47 / 91 / 445 by pixels (the planes read and written
-// at the rate of a copy would take 22); 262 k pixels of 2.8 points right after
-// the initialisation, 1 / 2 rings: 36 / 66 us by points, 27 / 45 by pixels.
-// Four wavefronts per SIMD, nothing spilled (five: 4% slower on dense tiles but
-// for 636 k pixels with 1 ring, 4% faster).  512 threads instead of 256 are up to
-// 7% (1 ring) and 25% (5 rings) faster by points, but leave a thread per pixel
-// half of the wavefronts: two slots a thread took 20% longer there.
-constexpr int APSS_SPARSE = 448;   // points of a tile of 256 pixels
+// to wait for another; a fuller one, whose list would take a second round of
+// threads, takes a thread per two slots of a pixel, past each neighbour at once.
+// The sums are the same in either.  Windows of 1 / 2 / 5 rings, us: 636 k pixels of
+// 1.4 points 41 / 70 / 163 (the planes read and written at the rate of a copy
+// would take 22), of 2.8 points right after the initialisation 57 / 100 / 213, a
+// thread per point 76 / 145 / 366; 262 k pixels of 2.8 points 28 / 48 / 98 against
+// 36 / 65 / 160; 74 k pixels of 1.5 points 15 / 25 / 55.
+// 256 threads with a thread per pixel, its four slots at once, fill 111 registers:
+// dense tiles 57 / 101 / 257 us and 26 / 45 / 124, but 43 / 75 / 196 and 17 / 30 / 67
+// on the sparse ones, whose points then need two rounds.  The neighbours' loop
+// stays rolled: unrolled it takes 112 registers, two workgroups per CU instead of
+// three (49 us where this takes 41).
+constexpr int APT = 512;
+constexpr int APSS_SPARSE = APT;        // points of a tile of 256 pixels
+constexpr int APSS_PAIR = 2;            // slots of a pixel a thread takes on the others
+static_assert(APT == ATX * ATY * KM / APSS_PAIR, "a thread per pair");
 
 // LDS bytes of the orthographic kernel: depths, normals, counts, the list.
 inline size_t apss_staged_bytes(int R)
@@ -90,11 +95,12 @@ inline size_t apss_staged_bytes(int R)
     return NS * (KM * sizeof(double) + 3 * KM * sizeof(float) + sizeof(uint8_t)) + APSS_SPARSE * sizeof(uint16_t);
 }
 
-// The moments of a pixel's n points (depths tq) at once, its neighbours in the
+// The moments of n points of a pixel (depths tq) at once, its neighbours in the
 // window's order: each neighbour is read once.
 __device__ __forceinline__ void apss_moments_slots(const double* tl, const float* nl, const uint8_t* cl, int NS, int SX,
                                                    int xc, int R, float h2, float pxy, double dz,
-                                                   const double (&tq)[KM], int n, Moments (&s)[KM])
+                                                   const double (&tq)[APSS_PAIR], int n,
+                                                   Moments (&s)[APSS_PAIR])
 {
     const float inv_h2 = 1.f / h2;
     for (int di = -R; di <= R; ++di) {
@@ -105,16 +111,15 @@ __device__ __forceinline__ void apss_moments_slots(const double* tl, const float
             if (!(dl < h2)) continue;
             const int x = xc + di * SX + dj;
             const int cc = cl[x];
-#pragma unroll
-            for (int k = 0; k < KM; ++k) {
-                if (k >= cc) break;
+#pragma unroll 1
+            for (int k = 0; k < cc; ++k) {
                 const double t2 = tl[k * NS + x];
                 const float nx = nl[(0 * KM + k) * NS + x];
                 const float ny = nl[(1 * KM + k) * NS + x];
                 const float nz = nl[(2 * KM + k) * NS + x];
                 const float yn = fmaf(yx, nx, yy * ny);
 #pragma unroll
-                for (int q = 0; q < KM; ++q) {
+                for (int q = 0; q < APSS_PAIR; ++q) {
                     if (q >= n) break;
                     const float yz = (float)((t2 - tq[q]) * dz);
                     const float d2 = fmaf(yz, yz, dl);
@@ -138,8 +143,8 @@ __device__ __forceinline__ void apss_moments_slots(const double* tl, const float
     }
 }
 
-__global__ __launch_bounds__(ATX * ATY, 4) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in, DevState out,
-                                                            int only_above, int carry)
+__global__ __launch_bounds__(APT, 6) void k_apss_tile(DevModel m, DevParams p, Tiles tg, DevState in, DevState out,
+                                                      int only_above, int carry)
 {
     extern __shared__ double apss_lds[];
     const int R = p.apss_Rs, SX = ATX + 2 * R, NS = SX * (ATY + 2 * R);
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(ATX * ATY, 4) void k_apss_tile(DevModel m, DevParam
     // waiting for the counts)
     __shared__ int wave_points[ATX * ATY / 64];
     uint16_t* pl = reinterpret_cast<uint16_t*>(cl + NS);        // [APSS_SPARSE] points (NS is even)
-    for (int x = threadIdx.x; x < NS; x += ATX * ATY) {
+    for (int x = threadIdx.x; x < NS; x += APT) {
         const int i2 = i0 - R + x / SX, j2 = j0 - R + x % SX;
         int c = 0;
         if (i2 >= 0 && i2 < sh.rows && j2 >= 0 && j2 < sh.cols) {
@@ -185,10 +190,10 @@ __global__ __launch_bounds__(ATX * ATY, 4) void k_apss_tile(DevModel m, DevParam
     }
     __syncthreads();
     const int ty = threadIdx.x / ATX, tx = threadIdx.x % ATX;
-    const bool inside = i0 + ty < sh.rows && j0 + tx < sh.cols;
-    const int xc = (ty + R) * SX + tx + R, c = inside ? cl[xc] : 0;
-    const long long pix = fbase + (long long)(i0 + ty) * sh.cols + j0 + tx;
+    const bool inside = ty < ATY && i0 + ty < sh.rows && j0 + tx < sh.cols;
+    const int c = inside ? cl[(ty + R) * SX + tx + R] : 0;
     if (carry && inside) {
+        const long long pix = fbase + (long long)(i0 + ty) * sh.cols + j0 + tx;
         out.cnt[pix] = (uint8_t)c;
         out.b[pix] = in.b[pix];
 #pragma unroll
@@ -207,24 +212,27 @@ __global__ __launch_bounds__(ATX * ATY, 4) void k_apss_tile(DevModel m, DevParam
         for (int a = 0; a < 3; ++a) out.n[(a * KM + k) * S + pix] = on[a];
     };
     if (points > APSS_SPARSE) {
-        if (c == 0) return;
-        const bool fit = !(only_above >= 0 && c <= only_above);
-        double tq[KM];
-        Moments v[KM];
+        const int qy = ty % ATY, xq = (qy + R) * SX + tx + R, k0 = ty / ATY * APSS_PAIR;
+        const int cq = i0 + qy < sh.rows && j0 + tx < sh.cols ? cl[xq] : 0;
+        if (cq <= k0) return;
+        const long long pix = fbase + (long long)(i0 + qy) * sh.cols + j0 + tx;
+        const bool fit = !(only_above >= 0 && cq <= only_above);
+        double tq[APSS_PAIR];
+        Moments v[APSS_PAIR];
 #pragma unroll
-        for (int q = 0; q < KM; ++q) {
-            tq[q] = tl[q * NS + xc];
+        for (int q = 0; q < APSS_PAIR; ++q) {
+            tq[q] = tl[(k0 + q) * NS + xq];
             v[q] = Moments{};
         }
-        if (fit) apss_moments_slots(tl, nl, cl, NS, SX, xc, R, h2, (float)p.p_xy, dz, tq, c, v);
+        if (fit) apss_moments_slots(tl, nl, cl, NS, SX, xq, R, h2, (float)p.p_xy, dz, tq, cq - k0, v);
 #pragma unroll
-        for (int q = 0; q < KM; ++q) {
-            if (q >= c) break;
-            finish(q, xc, pix, tq[q], fit, v[q]);
+        for (int q = 0; q < APSS_PAIR; ++q) {
+            if (k0 + q >= cq) break;
+            finish(k0 + q, xq, pix, tq[q], fit, v[q]);
         }
         return;
     }
-    for (int q = threadIdx.x; q < points; q += ATX * ATY) {
+    for (int q = threadIdx.x; q < points; q += APT) {
         const int pk = pl[q], k = pk % KM, qy = pk / KM / ATX, qx = pk / KM % ATX, xq = (qy + R) * SX + qx + R;
         const double tq = tl[k * NS + xq];
         const bool fit = !(only_above >= 0 && cl[xq] <= only_above);
@@ -588,8 +596,8 @@ hipError_t launch_apss_tiles(const DevModel& m, const DevParams& p, const Tiles&
         return hipGetLastError();
     }
     if (p.apss_Rs <= APSS_ROW) {
-        hipLaunchKernelGGL(k_apss_tile, dim3((unsigned)tg.tile0[tg.n]), dim3(ATX * ATY), apss_staged_bytes(p.apss_Rs), st, m, p,
-                           tg, in, out, only_above, (int)carry);
+        hipLaunchKernelGGL(k_apss_tile, dim3((unsigned)tg.tile0[tg.n]), dim3(APT), apss_staged_bytes(p.apss_Rs), st, m, p, tg,
+                           in, out, only_above, (int)carry);
         return hipGetLastError();
     }
     for (int g = 0; g < tg.n; ++g) {

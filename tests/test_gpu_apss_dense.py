@@ -1,4 +1,4 @@
-"""APSS tiles of many points (a thread per pixel, its points at once) against the
+"""APSS tiles of many points (a thread per two slots of a pixel) against the
 same points spread over four tiles of few (a thread per point): both sum in the
 window's order, so depths and normals are the same bits (the parity tests hold
 the latter to the oracle).  Tiles at and next to the line between the two, full
@@ -41,7 +41,7 @@ def state(points, at, seed):
     return st, px, live
 
 
-@pytest.mark.parametrize("points", [447, 448, 449, 512, 700, 1024])
+@pytest.mark.parametrize("points", [447, 448, 449, 512, 513, 700, 1024])
 @pytest.mark.parametrize("p_xy", [1.0, 0.8, 0.6, 0.45, 0.38])
 def test_dense_tile_equals_sparse_tiles(points, p_xy):
     ctx = rt3d.Context(IRF.probs, T, dz=0.1, p_xy=p_xy, m_min=3)
