@@ -26,6 +26,7 @@
 namespace rt3d {
 
 constexpr int ITX = 8, ITY = 4;         // tile: columns, rows (16 x 4: the same at 1 k pixels, 3% slower at 20 k)
+static_assert(ITX * ITY == ITER_TILE_PIXELS, "the host's rule counts in tiles");
 constexpr int IPX = ITX * ITY;          // pixels of a tile
 static_assert(KM == 4, "a pixel's slots: a quad of lanes");
 
@@ -399,7 +400,7 @@ bool iter_fits(const DevParams& p, int rb)
 
 long long iter_tiles(const Shape& sh)
 {
-    return (long long)sh.F * ((sh.rows + ITY - 1) / ITY) * ((sh.cols + ITX - 1) / ITX);
+    return tile_count(sh, ITX, ITY);
 }
 
 bool iter_tiles_add(Tiles& tg, long long base, const Shape& sh) { return tiles_add(tg, base, sh, ITX, ITY); }

@@ -151,6 +151,12 @@ __host__ __device__ inline Shape group_shape(const Tiles& tg, int g)
     return sh;
 }
 
+// Tiles of tx columns x ty rows that cover sh's frames.
+inline long long tile_count(const Shape& sh, int tx, int ty)
+{
+    return (long long)sh.F * ((sh.rows + ty - 1) / ty) * ((sh.cols + tx - 1) / tx);
+}
+
 // Appends group (base, sh) to tg, in tiles of tx columns x ty rows; false when tg
 // is full.
 inline bool tiles_add(Tiles& tg, long long base, const Shape& sh, int tx = TILE, int ty = TILE)
@@ -163,7 +169,7 @@ inline bool tiles_add(Tiles& tg, long long base, const Shape& sh, int tx = TILE,
     tg.rows[g] = sh.rows;
     tg.cols[g] = sh.cols;
     tg.S = sh.S;
-    const long long nt = (long long)sh.F * ((sh.rows + ty - 1) / ty) * ((sh.cols + tx - 1) / tx);
+    const long long nt = tile_count(sh, tx, ty);
     tg.tile0[g + 1] = tg.tile0[g] + (int)nt;
     return true;
 }
@@ -696,6 +702,7 @@ struct IterArgs {
     bool filter;
 };
 bool iter_fits(const DevParams& p, int rb);
+constexpr int ITER_TILE_PIXELS = 32;
 long long iter_tiles(const Shape& sh);
 bool iter_tiles_add(Tiles& tg, long long base, const Shape& sh);
 hipError_t launch_iter(const IterArgs& a, const Tiles& tg, int part, hipStream_t st);

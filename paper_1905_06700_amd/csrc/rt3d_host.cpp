@@ -645,25 +645,39 @@ CnnBuffers cnn_at(const CnnBuffers& b, long long base)
 
 // Whether the iterations run as three launches on tiles (k_iter.hip): APSS on
 // the orthographic map, one IRF, no step of the iteration timed by itself, and
-// at most ITER_TILES tiles (eight workgroups per CU).  Whole calls of 44 entries
-// per pixel, three launches against six, us: one frame of 32 x 32 (32 tiles) 580 /
-// 890, 141 x 141 (648) 692 / 1021, 200 x 200 (1250) 868 / 1164, 256 x 256 (2048)
-// 1235 / 1399, 300 x 300 (2850) 1603 / 1685, 362 x 362 (4186) 2170 / 2134; with 6
-// entries 256 x 256 1050 / 1084, 300 x 300 1343 / 1278, 362 x 362 1810 / 1601.  Past
-// the line the steps' own kernels with more workgroups per CU are the faster
-// ones.  Tiles, not pixels: thin and tiny frames fill few lanes of theirs (a line
-// of 1 x 5000, 625 tiles: 568 / 762; 20000 x 1, 5000 tiles: 1889 / 991; 6000 of
-// 3 x 3: 2218 / 2015).
-constexpr long long ITER_TILES = 2048;
+// few tiles of 8 x 4 pixels: past the line the steps' own kernels with more
+// workgroups per CU are the faster ones.  Whole calls of 6 / 50 / 310 entries per
+// pixel, three launches against six, us: 256 x 256 (2048 tiles) 1,050 / 1,225 /
+// 1,956 against 1,083 / 1,393 / 2,019; 80 frames of 32 x 32 (2560) 1,195 / 1,423 /
+// 2,276 against 1,217 / 1,579 / 2,325; 300 x 300 (2850) 1,337 / 1,595 / 2,528
+// against 1,278 / 1,659 / 2,427; 100 frames of 32 x 32 (3200) 1,434 / 1,737 / 2,783
+// against 1,329 / 1,738 / 2,587; 360 x 360 (4050) 1,737 / 2,098 / 3,309 against
+// 1,585 / 2,070 / 3,112.  Tiles, not pixels: frames of few rows or columns fill few
+// lanes of theirs.  A column of 10000 pixels (2500 tiles, 625 of the steps' own)
+// takes 982 / 1,122 / 1,547 against 770 / 852 / 1,085, so tiles less than half full
+// have the lower line, unless the steps' kernels have about as many (2500 frames
+// of one pixel 806 / 889 / 1,137 against 956 / 1,049 / 1,275; a row of 17000, 2125
+// tiles, 800 / 886 / 1,200 against 860 / 937 / 1,248).
+constexpr long long ITER_TILES = 2720, ITER_TILES_THIN = 2048;
+
+bool few_iter_tiles(const std::vector<Group>& groups)
+{
+    long long tiles = 0, step_tiles = 0, pixels = 0;
+    for (const Group& g : groups) {
+        tiles += iter_tiles(g.sh);
+        step_tiles += tile_count(g.sh, TILE, TILE);
+        pixels += g.sh.P;
+    }
+    const bool full = 2 * pixels >= ITER_TILE_PIXELS * tiles;
+    return tiles <= (full || tiles <= 2 * step_tiles ? ITER_TILES : ITER_TILES_THIN);
+}
 
 bool iter_eligible(const rt3d_ctx* c, const std::vector<Group>& groups, const uint8_t* cls)
 {
     const bool timed = c->prof_id == RT3D_KERNEL_DEPTH || c->prof_id == RT3D_KERNEL_APSS ||
                        c->prof_id == RT3D_KERNEL_INTENSITY || c->prof_id == RT3D_KERNEL_IFILTER ||
                        c->prof_id == RT3D_KERNEL_BKG || c->prof_id == RT3D_KERNEL_BFILTER;
-    long long tiles = 0;
-    for (const Group& g : groups) tiles += iter_tiles(g.sh);
-    return c->p.denoiser == RT3D_DENOISE_APSS && !cls && !(c->p.persp > 0) && !timed && tiles <= ITER_TILES &&
+    return c->p.denoiser == RT3D_DENOISE_APSS && !cls && !(c->p.persp > 0) && !timed && few_iter_tiles(groups) &&
            iter_fits(dev_params(c), c->rb);
 }
 
