@@ -1480,16 +1480,24 @@ static hipError_t launch_pixels(Kernel kernel, InitArgs a, size_t area, size_t t
 
 // Average pool up to which a launch's pixels take the list search, where the
 // weights' steps are not in registers (L > 241 or T > 8192).  The dense search
-// costs by bins and steps, the list search by entries.  20 k pixels, pools of
-// 30 / 100 / 400 entries, lists against dense, us: 8200 bins, 19-bin IRF 126 /
-// 441 / 1243 against 388 / 236 / 161; 20000 bins 117 / 366 / 1256 against 1286 /
-// 1239 / 442; 8192 bins, 501-bin IRF 112 / 161 / 420 against 276 / 259 / 265; 4613
-// bins, 2001-bin IRF 193 / 351 / 1434 against 561 / 462 / 498.  One choice for the
-// launch: a line drawn pixel by pixel lets pools near it take both kernels'
+// costs by bins and steps (and by the tiles it scores: more in sparse pools), the
+// list search by entries and a little by bins.  20 k pixels, pools of 30 / 100 /
+// 200 / 400 entries, lists against dense, us: 8200 bins, 19-bin IRF 131 / 452 /
+// 686 / 1270 against 381 / 230 / 159 / 159, 137-bin IRF 137 / 264 / 463 / 924 against
+// 238 / 162 / 168 / 185; 20000 bins 118 / 375 / 795 / 1266 against 1247 / 1197 / 436
+// / 422 and 123 / 259 / 370 / 647 against 795 / 420 / 412 / 430; 32768 bins 139 /
+// 369 / 905 / 1476 against 3261 / 3578 / 1312 / 1037 and 149 / 330 / 417 / 697
+// against 2065 / 1022 / 1023 / 1064; 501-bin IRF, 4613 bins 111 / 172 / 276 / 584
+// against 140 / 132 / 133 / 135, 8192 bins 115 / 165 / 237 / 437 against 273 / 255 /
+// 255 / 259; 2001-bin IRF, 4613 bins 203 / 363 / 739 / 1417 against 558 / 460 / 437 /
+// 497.  Both lines are fitted to where such pairs cross, within 15% of the better
+// one of 321 calls but for one (1.32 times at 32768 bins, 19-bin IRF).  One choice
+// for the launch: a line drawn pixel by pixel lets pools near it take both kernels'
 // time (206 us where the one takes 147 and the other 136).
 static uint32_t list_mean(int T, int ks)
 {
-    return (uint32_t)std::min<long long>(INIT_LIST, (long long)T * T * (std::min(ks, 16) + 1) / 3000000);
+    if (ks == 1) return (uint32_t)(T / 130);
+    return (uint32_t)std::min((double)INIT_LIST, 2.6e-5 * T * sqrt((double)T) * std::min(ks, 16));
 }
 
 hipError_t launch_init(const DevModel& m, const DevParams& p, const Shape& sh, const uint32_t* off,

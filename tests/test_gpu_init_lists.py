@@ -51,6 +51,7 @@ CASES = {
     "sparse_T8193": lambda: (photons(10, 9, 9, 8193, GAUSS, 1.5, 0.5), GAUSS, dict(r_init=1)),
     "dense_T8193": lambda: (photons(11, 9, 9, 8193, GAUSS, 8.0, 90.0), GAUSS, dict(r_init=1)),
     "both_sides": lambda: (pools(12, 20000, TAIL, [5, 40, 250, 300, 500, 533, 534, 1000, 1024, 1025, 9, 9]), TAIL, {}),
+    "past_1024": lambda: (pools(15, 20000, TAIL, [5, 40, 150, 219, 220, 221, 9, 9, 1023, 1024, 1025] + [9] * 12), TAIL, {}),
     "sparse_L2001": lambda: (photons(13, 7, 8, 4613, WIDE, 20.0, 20.0), WIDE, dict(k_init=3)),
     "dense_L2001": lambda: (photons(14, 7, 8, 4613, WIDE, 20.0, 400.0), WIDE, dict(k_init=3)),
 }
