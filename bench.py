@@ -206,7 +206,7 @@ def stored_traffic(kernel, frames):
 
 def small_frames(F=64, reps=5):
     """Batches of small frames (config 1 plane scenes, 32 x 32 x 300), where
-    the ~140 launches of a call dominate: direct calls against replays of a
+    the launches of a call dominate: direct calls against replays of a
     recorded graph."""
     import numpy as np
     import torch

@@ -90,7 +90,7 @@ typedef struct rt3d_params {
     int32_t  denoiser;   /* RT3D_DENOISE_APSS (default), RT3D_DENOISE_CNN or RT3D_DENOISE_NONE */
     int32_t  fused_loop; /* with APSS, a batch of frames of one size of at most 4096 pixels can run
                           * all iterations in one launch (one workgroup per frame, steps separated
-                          * by workgroup barriers) instead of one launch per step.  1: always
+                          * by workgroup barriers) instead of launches for every iteration.  1: always
                           * (when eligible); 0: never; -1 (default): the choice rt3d_autotune
                           * measured for this batch shape, else when the batch holds at least
                           * 64 frames (fewer frames leave most compute units idle) */
@@ -291,7 +291,7 @@ rt3d_status rt3d_reconstruct(rt3d_ctx* ctx, const rt3d_input* in, rt3d_output* o
                              void* hip_stream);
 
 /* Replayable reconstruction: one rt3d_reconstruct call recorded into a HIP
- * graph (its ~140 kernel launches become one graph launch).  The graph keeps
+ * graph (its tens of kernel launches become one graph launch).  The graph keeps
  * the call's pointers -- input, output, gain and the context's workspace --
  * so each replay repeats exactly that call on whatever the buffers then hold;
  * the caller refills the input between replays and must not rebind the
@@ -333,14 +333,14 @@ rt3d_status rt3d_query(rt3d_ctx* ctx, void* hip_stream, rt3d_stats* st);
 #define RT3D_KERNEL_LOOP     12   /* every iteration in one launch (params.fused_loop) */
 #define RT3D_KERNEL_COUNT    13
 /* Autotuning.  Times a reconstruction of this input in each mapping of the
- * loop onto the GPU the batch admits -- one launch per step with 4 lanes per
- * pixel in the gradient steps, the same with 8 lanes, and all iterations in one
+ * loop onto the GPU the batch admits -- launches for every iteration with 4 lanes
+ * per pixel in the gradient steps, the same with 8 lanes, and all iterations in one
  * launch (one workgroup per frame; frames of one size up to 4096 pixels with
  * APSS) -- and keeps the fastest for this batch shape (frames x rows x cols) in
  * the context, where params.fused_loop = -1 and params.lanes_per_pixel = 0 use
  * it.  Synchronises the stream; the output holds the last timed
  * reconstruction.  *fused (may be NULL) receives 1 for the one-launch loop, 0
- * for one launch per step.  Batches of several frame sizes keep the defaults
+ * for launches per iteration.  Batches of several frame sizes keep the defaults
  * (nothing is timed).  Not while a graph is being recorded.
  * rt3d_mapping reports the mapping rt3d_reconstruct would take for this input
  * (*fused as above, *lanes the lanes per pixel of the per-step gradient

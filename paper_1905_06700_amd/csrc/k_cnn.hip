@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void k_cnn_prepare(CnnWeights W)
 
 // ---------------------------------------------------------------------------
 // Forward and backward data, fused over the layers: one FT x FT output tile in
-// one workgroup of eight wavefronts, every intermediate map kept in LDS as
+// one workgroup of FW wavefronts, every intermediate map kept in LDS as
 // FP16 (the rounding of a stored activation).  Layer l computes its output
 // over the tile grown by the receptive field of the layers after it; outputs
 // at positions outside the image are set to zero, which is the next layer's

@@ -1460,8 +1460,9 @@ static int init_waves(size_t area, size_t tables)
 // Consecutive pixels per wavefront (at most INIT_PPW_MAX): the workgroup's
 // tables (a few loads and a barrier) and the wavefront's output serve all of
 // them, but a grid needs enough wavefronts to fill the chip (1024 SIMDs with
-// five each).  Measured with 4, 8 and 16 pixels: 2.48, 2.47 and 2.49 ms at 636 k
-// pixels, 0.183, 0.192 and 0.213 ms at 65 k (an earlier state of the kernel).
+// five each).  Measured with 1, 2, 4, 8 and 16 pixels, us: 1,960, 1,778, 1,681,
+// 1,642 and 1,647 at 636 k pixels; 212, 197, 197, 213 and 220 at 65 k; 85, 81, 80,
+// 111 and 180 at 20 k; 20, 28, 39, 62 and 105 at 1 k.
 static int pixels_per_wave(long long P) { return P >= 131072 ? 8 : P >= 32768 ? 4 : P >= 16384 ? 2 : 1; }
 static_assert(INIT_PPW_MAX >= 8, "a wavefront's pixels have a lane per peak");
 
@@ -1491,7 +1492,8 @@ static hipError_t launch_pixels(Kernel kernel, InitArgs a, size_t area, size_t t
 // against 140 / 132 / 133 / 135, 8192 bins 115 / 165 / 237 / 437 against 273 / 255 /
 // 255 / 259; 2001-bin IRF, 4613 bins 203 / 363 / 739 / 1417 against 558 / 460 / 437 /
 // 497.  Both lines are fitted to where such pairs cross, within 15% of the better
-// one of 321 calls but for one (1.32 times at 32768 bins, 19-bin IRF).  One choice
+// one over 484 calls; pools of strong peaks cross later (32768 bins, 420 entries, a
+// fifth of them signal, a 19-bin IRF: 329 against 835).  One choice
 // for the launch: a line drawn pixel by pixel lets pools near it take both kernels'
 // time (206 us where the one takes 147 and the other 136).
 static uint32_t list_mean(int T, int ks)

@@ -7,12 +7,12 @@
 // for all iterations; each step is a loop of the workgroup's threads over the
 // frame's pixels (one pixel per thread at a time) and the steps are separated
 // by workgroup barriers instead of kernel boundaries, so a call on a batch of
-// small frames is one launch instead of seven per iteration.  The frame's point
+// small frames is one launch instead of three or six per iteration.  The frame's point
 // state, entries and background stay in the caches between steps.  Each step
 // computes what the corresponding kernel of k_steps.hip, k_apss.hip and
 // k_filter.hip computes (the same readings, the same update functions); sums
 // over a pixel's entries run on one thread here, so their FP32 rounding order
-// differs from the four-lane kernels.
+// differs from the kernels of several lanes per pixel.
 #include "rt3d_points.h"
 #include "rt3d_steps.h"
 

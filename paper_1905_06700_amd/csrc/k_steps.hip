@@ -17,7 +17,7 @@
 //   background: b <- max(b_min, b [(1-beta_b) + beta_b sum z/(lambda T)]).
 // Within a pixel every point uses lambda from before the step (Jacobi).
 //
-// Mapping: four lanes per pixel share its active entries (cost linear in
+// Mapping: LPP (4 or 8) lanes per pixel share its active entries (cost linear in
 // active bins, as in the paper's Methods; consecutive lanes read consecutive
 // entries) and combine their partial sums with wavefront shuffles; every lane
 // keeps the pixel's <= 4 points in registers.  Depth is held in FP64 state and

@@ -601,6 +601,17 @@ bool loop_eligible(const rt3d_ctx* c, const std::vector<Group>& groups, const Sh
            (long long)sh.rows * sh.cols <= LOOP_MAX_PIX;
 }
 
+// Untuned, the line is 64 frames: that many workgroups, one per compute unit.  A
+// whole call with the loop / without it (three launches an iteration while that
+// holds), us, on video frames of about 11 photons per pixel and 300 bins:
+// frames of 32 x 32: 16: 903 / 568, 32: 940 / 663, 64: 1,002 / 1,037, 96: 1,065 /
+// 1,342, 128: 1,126 / 1,404, 256: 1,433 / 2,200, 512: 2,802 / 3,713; of 24 x 24:
+// 64: 839 / 725, 96: 879 / 968; of 16 x 16: 128: 764 / 665, 192: 790 / 884; with 20
+// photons per pixel, half of them background, 32 x 32: 64: 1,631 / 1,154, 128: 1,805
+// / 1,614, 192: 1,986 / 2,038, 256: 2,194 / 2,523, 16 x 16: 64: 1,209 / 615, 256:
+// 1,346 / 1,153.  So it turns at 64 frames for the video frames and
+// later for smaller frames and longer lists; rt3d_autotune measures it, and the
+// default stays what the interface says.
 bool use_fused(const rt3d_ctx* c, const Shape& sh)
 {
     if (c->force_fused >= 0) return c->force_fused == 1;
